@@ -50,17 +50,24 @@ constexpr int32_t kLocal = 0x40000000;     // LDS link to an entry of the same t
 constexpr int32_t kUnset = 0x7FFFFFFF;     // LDS cube slot not yet written
 constexpr int kMaxChase = 1 << 22;         // bound of every pointer walk
 constexpr int kUfThreads = 1024;
-constexpr int kUfLdsNodes = 5120;          // union-find nodes kept in LDS with their keys (40 KiB + 40 KiB)
-constexpr int kUfLdsEdges = 4096;          // union-find live edges kept in LDS (3 x 16 KiB)
-constexpr int kUfLdsWords = 40880;         // the union-find's LDS (160 KiB less its other shared words), int32
-constexpr int kUfLdsNodesOnly = kUfLdsWords / 2;   // nodes whose par, moe alone fit in LDS
+constexpr int kUfLdsNodes = 40000;         // union-find nodes kept in LDS (a word each)
+constexpr int kUfK = 8;                    // edges a thread of a batch of the union-find
+constexpr int kUfLdsWords = 40600;         // the union-find's LDS, int32 (160 KiB less its other shared words)
+constexpr int kUfWideNodes = 20440;        // the wide rounds (PH_WIDE) take forests of more nodes
 constexpr int kSortThreads = 1024;
-constexpr int kSortCap = 4096;             // keys sorted entirely in LDS (32 KiB)
+constexpr int kSortCap = 4096;             // keys sorted entirely in LDS (two buffers of 34 KiB)
+constexpr int64_t kSortMultiVoxels = 1 << 16;   // long lists sorted by several workgroups from this size on
+constexpr int kSortMultiInstances = 32;    // ... in batches of up to this many instances
+constexpr int kSortRun = 2048;             // keys of their runs
+constexpr int kSideBySideInstances = 64;   // batches of up to this many run the images' dual beside H0
+constexpr int kOutParts = 64;              // workgroups that write the pairs, over all instances
 constexpr int kMaxRounds = 48;             // parallel rounds before the sequential finish
-constexpr int kWideRounds = 32;            // union-find rounds over many workgroups (PH_WIDE)
+constexpr int kWideRounds = 4;             // union-find rounds over many workgroups (PH_WIDE)
 constexpr int64_t kWideVoxels = 1 << 20;   // ... for instances of this many voxels
 constexpr int kWideBlocks = 2048, kWideThreads = 256;
-constexpr int32_t kFired = 1 << 30;        // wide rounds: an edge fired this round (above every node index)
+constexpr int kWidePer = 2, kWideSeg = kWidePer * kWideThreads;   // edges a thread, a segment
+constexpr int kRestNodes = 20000;          // nodes the finish in one workgroup holds (two words of LDS each)
+constexpr int kWidePosBits = 28;           // walk positions of a wide forest (the round's tag above)
 constexpr int32_t kInf = 0x7FFFFFFF;
 constexpr int kMaxInstances = 65535;       // instances of one call: the y extent of a grid
 // Halo key of a pixel outside the image.  Pixel keys are capped one below it (only the NaN bit
@@ -1154,144 +1161,274 @@ __device__ __forceinline__ int block_flag_scan(int flag, int *s_wsum, int *total
 }
 
 // ======================================================================== sort ====
-// Sort one list per instance ascending.  which: 0 = KEEP edges (in place), 1 = KEEP squares
-// (in place), 2 = H0 node keys copied to a sorted array.  Lists that fit in LDS are sorted
-// there by a bitonic network; longer ones are sorted in LDS-sized runs by the same network
-// and the runs merged pairwise in global memory, a tile of outputs at a time through LDS
-// (merge path: each tile's share of the two runs is found by one binary search per tile).
-// Keys are unique (the pixel and code are part of them), so every order is total.
+// Sort the lists of every instance ascending: 0 KEEP edges (in place), 1 KEEP squares (in
+// place), 2 the H0 node keys (copied to a sorted array), 3 the dual node keys, descending (in
+// place from entry 1 on; entry 0 is the cell at infinity).  Each node's place in its order is
+// kept as its rank (H0: rank0[id] = r for the r-th key; dual: rankT[id] = r + 1, the cell at
+// infinity being 0), by which the resolve passes name the nodes: in both union-finds the elder
+// of two is then the smaller number, and no kernel compares node keys again.  rank0 and rankT
+// lie in the union-finds' par arrays, which those set up after the resolve passes.
+//
+// A list of up to kSortCap keys is sorted in LDS by one workgroup: each thread sorts E keys in
+// registers, then merge passes double the runs; in a pass thread t finds by binary search
+// (merge path) where outputs E t .. E t + E - 1 of its pair of runs begin, and merges them into
+// its registers.  What bounds it is the vector instructions of the one compute unit, and merging
+// takes a fifth of those of the bitonic network that stood here (78 compare-exchange stages of
+// 4096 keys; 16 workgroup waves on four SIMDs): 64 volumes 96^3 and 64 images 512^2 43 -> 26 us,
+// 512 images of 64^2 to 512^2 89 -> 44 us (with a fourth list, the dual nodes).
+// Longer lists are sorted in runs of kSortCap keys.  With one workgroup a list (R = 1) the runs
+// are merged pairwise through LDS tiles; with more, each run has a workgroup of its own and
+// k_sort_merge merges all of them at once.
+// Keys are unique (the pixel and code are part of them), so every order is total, and no key
+// (and no complement of a dual node's) is ~0, the padding.
 
-__device__ __forceinline__ uint64_t shfl_xor64(uint64_t x, int m) {
-    const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)x, m, 64);
-    const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(x >> 32), m, 64);
-    return ((uint64_t)hi << 32) | lo;
+// Compare-exchange of two keys held in registers
+__device__ __forceinline__ void cmp_swap(uint64_t &a, uint64_t &b) {
+    const bool sw = b < a;
+    const uint64_t lo = sw ? b : a, hi = sw ? a : b;
+    a = lo;
+    b = hi;
 }
 
-// Bitonic sort of s[0, P) ascending (P a power of two, 2 <= P <= 4 * blockDim.x; s holds
-// 4 * blockDim.x keys, padding included) by the whole block.  Thread t holds keys 4t .. 4t + 3
-// in registers.  A compare-exchange whose partner is in the same thread is done in registers,
-// in the same wave by lane shuffles, and only one in another wave goes through LDS: those
-// stages alternate between s and s2, with one barrier each.  On return x holds the thread's
-// four keys of the sorted sequence.  All threads of the block must call it.
-__device__ void bitonic_regs(uint64_t *s, uint64_t *s2, int P, uint64_t (&x)[4]) {
-    const int t = threadIdx.x;
+// Slot of key i in LDS: one key of padding after every 16, so that the threads of a wave, E keys
+// apart, fall on different banks.
+__device__ __forceinline__ int pad_slot(int i) { return i + (i >> 4); }
+constexpr int pad_size(int n) { return n + (n >> 4) + 2; }   // slot n included
+
+// Merge sort of the block's keys by the whole block, E keys a thread: on entry x holds keys
+// E t .. E t + E - 1 of the list (padding ~0 past m), on return the same places of the sorted
+// list.  s: two buffers of pad_size(E kSortThreads) keys; the passes alternate between them, with
+// one barrier each.  All threads must call it.
+template <int E>
+__device__ __forceinline__ void merge_sort_block(uint64_t *s, int m, uint64_t (&x)[E]) {
+    const int at = E * (int)threadIdx.x;
+    // odd-even transposition sorts the thread's own keys
 #pragma unroll
-    for (int e = 0; e < 4; ++e) x[e] = s[4 * t + e];
-    bool flip = false;
-    for (int k = 2; k <= P; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            uint64_t y[4];
-            if (j >= 256) {                          // partner in another wave
-                uint64_t *b = flip ? s2 : s;
-                flip = !flip;
+    for (int r = 0; r < E; ++r)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) b[4 * t + e] = x[e];
-                lds_barrier();
+        for (int e = r & 1; e + 1 < E; e += 2) cmp_swap(x[e], x[e + 1]);
+    const int mp = (m + E - 1) / E * E;            // the list with the last thread's padding
+    uint64_t *b = s;
+    for (int w = E; w < mp; w <<= 1) {
+        if (at < mp) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) y[e] = b[(4 * t + e) ^ j];
-            } else if (j >= 4) {                     // another lane of the wave
+            for (int e = 0; e < E; ++e) b[pad_slot(at + e)] = x[e];
+        }
+        lds_barrier();
+        if (at < mp) {
+            const int ps = at & ~(2 * w - 1), d = at - ps;
+            const int lb = mp - ps - w < w ? mp - ps - w : w;
+            if (lb > 0) {                          // (a run without a partner stays as it is)
+                const int A = ps, B = ps + w;
+                int lo = d > lb ? d - lb : 0, hi = d < w ? d : w;
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (b[pad_slot(A + mid)] < b[pad_slot(B + d - 1 - mid)]) lo = mid + 1;
+                    else hi = mid;
+                }
+                // next key of each run, and the runs' ends
+                int ia = A + lo, ib = B + d - lo;
+                const int ea = B, eb = B + lb;
+                // (read before the test: a branch would serialise the reads; slot mp lies in the buffer)
+                uint64_t ka = b[pad_slot(ia)], kb = b[pad_slot(ib)];
+                ka = ia < ea ? ka : ~0ull;
+                kb = ib < eb ? kb : ~0ull;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) y[e] = shfl_xor64(x[e], j >> 2);
-            } else if (j == 2) {
-                y[0] = x[2]; y[1] = x[3]; y[2] = x[0]; y[3] = x[1];
-            } else {
-                y[0] = x[1]; y[1] = x[0]; y[2] = x[3]; y[3] = x[2];
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int i = 4 * t + e;
-                const bool keep_min = ((i & j) == 0) == ((i & k) == 0);
-                const bool lt = x[e] < y[e];
-                x[e] = keep_min == lt ? x[e] : y[e];
+                for (int e = 0; e < E; ++e) {
+                    const bool ta = ka < kb;
+                    x[e] = ta ? ka : kb;
+                    if (e + 1 < E) {
+                        const int i = (ta ? ia : ib) + 1;
+                        uint64_t nk = b[pad_slot(i)];
+                        nk = i < (ta ? ea : eb) ? nk : ~0ull;
+                        ia = ta ? i : ia;
+                        ib = ta ? ib : i;
+                        ka = ta ? nk : ka;
+                        kb = ta ? kb : nk;
+                    }
+                }
             }
         }
+        b = b == s ? s + pad_size(E * kSortThreads) : s;
     }
 }
 
-// Sort of one list of instance I (WHICH: 0 KEEP edges, 1 KEEP squares, 2 node keys), m keys,
-// by the whole block.  The list is a template argument, so each instantiation is straight-line
-// code: with the list chosen by a run-time argument, the gfx950 build of an earlier sort kernel
-// took the node-key branch without setting the scalar register pair that holds the count's
-// address, and loaded the count from near address 0.  The caller loads every count first.
-// a list the wide sort kernels take under PH_WIDE (k_sort_runs, k_sort_merge)
-__device__ __forceinline__ bool sort_is_wide(const Inst &I, int m) {
-    return I.N >= kWideVoxels && m > kSortCap && !I.h1;
+// The lists: what is sorted, where to, and through which scratch
+struct SortLists {
+    uint64_t *src, *dst, *scr;
+    int64_t cap;
+    int m;
+};
+// one of four values, taken by value: a conditional on the record's fields would select an
+// address, and keep the record in private memory
+__device__ __forceinline__ int64_t pick(int w, int64_t a, int64_t b, int64_t c, int64_t d) {
+    return w == 0 ? a : (w == 1 ? b : (w == 2 ? c : d));
+}
+__device__ __forceinline__ SortLists sort_lists_of(uint8_t *__restrict__ ws, const Inst &I, const int32_t *cnt, int w) {
+    // every count is loaded on every path: with the count's address chosen by the list, the
+    // gfx950 build of an earlier sort kernel left the scalar register pair that holds the
+    // address unset on one branch, and loaded the count from near address 0
+    const int mE = cnt[CNT_E], mF = cnt[CNT_F], mN = cnt[CNT_M0], mT = cnt[CNT_MT];
+    SortLists L;
+    const int64_t src = pick(w, I.o_keyE, I.o_keyF, I.o_n0key, I.o_nTkey + 8);
+    const int64_t scr = pick(w, I.o_scratch, I.o_live, I.o_ra, I.o_ea);
+    L.src = arr<uint64_t>(ws, src);
+    L.dst = arr<uint64_t>(ws, pick(w, src, src, I.o_n0sorted, src));
+    L.scr = arr<uint64_t>(ws, scr);
+    L.cap = pick(w, I.E, I.F, I.M0cap, I.MTcap - 1);
+    L.m = (int)pick(w, mE, mF, mN, mT - 1);
+    return L;
 }
 
-template <int WHICH>
-__device__ __forceinline__ void sort_list(uint8_t *__restrict__ ws, const Inst &I, int32_t *cnt, int m,
-                                          uint64_t *s, uint64_t *s2) {
-    uint64_t *src = arr<uint64_t>(ws, WHICH == 0 ? I.o_keyE : (WHICH == 1 ? I.o_keyF : I.o_n0key));
-    uint64_t *dst = WHICH == 2 ? arr<uint64_t>(ws, I.o_n0sorted) : src;
-    const int64_t cap = WHICH == 0 ? I.E : (WHICH == 1 ? I.F : I.M0cap);
-    if (m > cap) { if (threadIdx.x == 0) set_err(cnt, PH_EINTERNAL); return; }
-    if (m <= 0) return;
-    if (m <= kSortCap) {
-        static_assert(kSortCap == 4 * kSortThreads, "four keys per thread");
-        int P = 2;
-        while (P < m) P <<= 1;
-        for (int t = threadIdx.x; t < kSortCap; t += blockDim.x) s[t] = t < m ? src[t] : ~0ull;
-        __syncthreads();
-        uint64_t x[4];
-        bitonic_regs(s, s2, P, x);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (4 * (int)threadIdx.x + e < m) dst[4 * threadIdx.x + e] = x[e];
-        __syncthreads();                         // s, s2 are free for the caller's next sort
+// Key k (as sorted: a dual node's complemented) has place r of list w: store it, and the rank
+// of its node.  first: no smaller key of the list belongs to the same vertex (3D H1 keeps each
+// vertex's first KEEP edge).
+__device__ __forceinline__ void sort_emit(uint8_t *__restrict__ ws, const Inst &I, int32_t *cnt, int w,
+                                          uint64_t *dst, int64_t r, uint64_t k, bool first) {
+    const uint64_t key = w == 3 ? ~k : k;
+    dst[r] = key;
+    if (w < 2) {
+        if (w == 0 && I.h1 && first && key_pix(key) < (uint64_t)I.N) arr<int32_t>(ws, I.o_kpos)[key_pix(key)] = (int32_t)r;
         return;
     }
-    // long list: LDS-sized runs, then merge passes between dst and the list's own scratch
-    uint64_t *scr = arr<uint64_t>(ws, WHICH == 0 ? I.o_scratch : (WHICH == 1 ? I.o_live : I.o_ra));
-    for (int base = 0; base < m; base += kSortCap) {
-        const int len = (m - base) < kSortCap ? (m - base) : kSortCap;
-        int P = 2;
-        while (P < len) P <<= 1;
-        for (int t = threadIdx.x; t < kSortCap; t += blockDim.x) s[t] = t < len ? src[base + t] : ~0ull;
-        __syncthreads();
-        uint64_t x[4];
-        bitonic_regs(s, s2, P, x);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (4 * (int)threadIdx.x + e < len) dst[base + 4 * threadIdx.x + e] = x[e];
-        __syncthreads();
+    const uint32_t v = key_pix(key);
+    const int code = (int)key_code(key);
+    if (w == 2) {
+        const int64_t id = v < (uint64_t)I.N ? -((int64_t)arr<int32_t>(ws, I.o_par0)[v] + 1) : -1;
+        if (id >= 0 && id < I.M0cap) arr<int32_t>(ws, I.o_uf0)[id] = (int32_t)r;
+        else set_err(cnt, PH_EINTERNAL);
+        return;
     }
-    const uint64_t *a = dst;
-    uint64_t *b = scr;
-    int *s_split = (int *)s2;                        // split points of a batch of tiles
-    for (int64_t w = kSortCap; w < m; w <<= 1) {
-        const int64_t ntiles = (m + kSortCap - 1) / kSortCap;
-        for (int64_t tb = 0; tb < ntiles; tb += kSortThreads) {
-            const int64_t nb = ntiles - tb < kSortThreads ? ntiles - tb : kSortThreads;
+    // the top cell's first corner: v + (offset - 1) / 2 on each axis it spans
+    const int HW = I.H * I.W, z = (int)(v / (uint32_t)HW), rem = (int)v - z * HW, y = rem / I.W, xx = rem - y * I.W;
+    const bool is2d = I.ndim == 2;
+    const int cz = is2d ? 0 : z + (off_of(code, 0) - 1) / 2, cy = y + (off_of(code, 1) - 1) / 2,
+              cx = xx + (off_of(code, 2) - 1) / 2;
+    const bool ok = (is2d ? code >= 11 && code <= 14 : code >= 19 && code <= 26 && cz >= 0 && cz < I.D - 1) && cy >= 0 &&
+                    cy < I.H - 1 && cx >= 0 && cx < I.W - 1;
+    const int64_t id = ok ? -((int64_t)arr<int32_t>(ws, I.o_parT)[(cz * (I.H - 1) + cy) * (I.W - 1) + cx] + 1) : -1;
+    if (id >= 1 && id < I.MTcap) arr<int32_t>(ws, I.o_ufT)[id] = (int32_t)r + 1;
+    else set_err(cnt, PH_EINTERNAL);
+}
+
+// One run: keys [base, base + len) of the list, sorted, to the same places of out (or, when the
+// run is the whole list, to their final ones).
+template <int E>
+__device__ __forceinline__ void sort_run(uint8_t *__restrict__ ws, const Inst &I, int32_t *cnt, int w, const SortLists &L,
+                                         int64_t base, int len, uint64_t *out, bool whole, uint64_t *s) {
+    const uint64_t flip = w == 3 ? ~0ull : 0ull;
+    const int at = E * (int)threadIdx.x;
+    uint64_t x[E];
+    // through LDS, so that the loads are coalesced
+    for (int t = threadIdx.x; t < E * kSortThreads; t += kSortThreads)
+        s[pad_slot(t)] = t < len ? L.src[base + t] ^ flip : ~0ull;
+    lds_barrier();
+#pragma unroll
+    for (int e = 0; e < E; ++e) x[e] = s[pad_slot(at + e)];
+    lds_barrier();
+    merge_sort_block<E>(s, len, x);
+    // and back
+    lds_barrier();
+#pragma unroll
+    for (int e = 0; e < E; ++e) s[pad_slot(at + e)] = x[e];
+    lds_barrier();
+    for (int t = threadIdx.x; t < len; t += kSortThreads) {
+        const uint64_t k = s[pad_slot(t)];
+        if (whole) sort_emit(ws, I, cnt, w, out, t, k, t == 0 || (s[pad_slot(t - 1)] >> kCodeBits) != (k >> kCodeBits));
+        else out[base + t] = k;
+    }
+    __syncthreads();                             // s is free for the next run
+}
+
+// Merge passes k_sort_merge makes over a list of m keys, of at most `passes` launched
+// (0: one workgroup sorts the list): one pass up to 16 runs, else as many as are launched.
+// A key's place in one pass takes one binary search in each other run of its group, so two
+// passes over sqrt(runs) runs each beat one over all once there are more than about 16.
+__device__ __forceinline__ int sort_passes(int runs, int passes) {
+    return runs <= 1 ? 0 : (runs <= 16 ? (passes < 1 ? passes : 1) : passes);
+}
+
+// The sorts of every instance in one launch: grid (R, n, 4), blockIdx.y = instance, z = list, so
+// the lists of all instances are sorted side by side.  Each list has a scratch of its own: the
+// sort scratch (KEEP edges), the live-edge arrays (KEEP squares), the root arrays (H0 nodes) and
+// the edges' endpoint array (dual nodes: at most half as many as edges wherever a list outgrows
+// one run), all written only afterwards.
+// rl: keys of a run, at most kSortCap (all of it where one workgroup sorts the list).
+// passes: k_sort_merge launches that follow (0: none; a long list is merged here).
+__global__ __launch_bounds__(kSortThreads, 8) void k_sort_lists(uint8_t *__restrict__ ws, int n, int rl, int passes) {
+    __shared__ uint64_t s[2 * pad_size(kSortCap)];
+    __shared__ int s_flag;
+    const int i = blockIdx.y, w = blockIdx.z;
+    const Inst I = ((const Inst *)ws)[i];           // one batch of loads, before any atomic
+    int32_t *cnt = (int32_t *)(ws + off_cnt(n)) + i * CNT_WORDS;
+    const SortLists L = sort_lists_of(ws, I, cnt, w);
+    if (threadIdx.x == 0) s_flag = failed(cnt);
+    lds_barrier();
+    if (s_flag) return;
+    const int m = L.m;                           // (a list has fewer than 2^29 keys)
+    // runs of equal length for k_sort_merge (a short last one's keys would have long searches in
+    // all the others); merged here they are whole tiles
+    const int runs = (m + rl - 1) / rl, run = passes > 0 && runs > 0 ? (m + runs - 1) / runs : rl;
+    const int base0 = blockIdx.x * run;
+    if ((int)blockIdx.x >= runs || base0 >= m) return;
+    if (m > L.cap) { if (threadIdx.x == 0) set_err(cnt, PH_EINTERNAL); return; }
+    // the keys of one run by the fewest a thread that hold it
+    auto sort = [&](int64_t base, int len, uint64_t *out, bool whole) {
+        if (len <= 2 * kSortThreads) sort_run<2>(ws, I, cnt, w, L, base, len, out, whole, s);
+        else sort_run<4>(ws, I, cnt, w, L, base, len, out, whole, s);
+    };
+    // an odd number of merge passes ends in dst when the runs start from the scratch.  With one
+    // workgroup a list they start in place (as sorted: a dual node's complemented)
+    const int np = sort_passes(runs, passes);
+    uint64_t *out = np & 1 ? L.scr : L.dst;
+    for (int64_t base = base0; base < m; base += (int64_t)gridDim.x * run) {
+        const int len = (int)((m - base) < run ? (m - base) : run);
+        sort(base, len, out, runs == 1);
+    }
+    if (runs == 1) return;
+    if (passes > 0) return;
+    // one workgroup a list: merge pairs of runs, a tile of kTile outputs at a time through LDS
+    // (merge path: each tile's share of the two runs by one binary search, each thread's four
+    // outputs by another in LDS)
+    constexpr int kTile = 4 * kSortThreads;
+    const uint64_t *a = L.dst;
+    uint64_t *b = L.scr;
+    int *s_split = (int *)(s + kTile);               // split points of a batch of tiles
+    static_assert(2 * pad_size(kSortCap) >= kTile + (kSortThreads + 2) / 2 && kSortCap == kTile, "tile and split points fit");
+    for (int wd = run; wd < m; wd <<= 1) {
+        const int ntiles = (m + kTile - 1) / kTile;
+        for (int tb = 0; tb < ntiles; tb += kSortThreads) {
+            const int nb = ntiles - tb < kSortThreads ? ntiles - tb : kSortThreads;
             // tile k starts at output o = (tb + k) T of its pair [ps, ps + 2w): the number of
             // left-run keys among the pair's first o - ps outputs (merge path); k = nb too, the
             // batch's end (used only when the batch's last tile ends inside its pair)
             for (int k = threadIdx.x; k <= nb; k += blockDim.x) {
-                const int64_t o = (tb + k) * kSortCap, ps = o / (2 * w) * (2 * w);
+                const int o = (tb + k) * kTile, ps = o / (2 * wd) * (2 * wd);
                 if (o >= m) { s_split[k] = 0; continue; }   // past the list: never read
-                const int64_t la = (m - ps) < w ? (m - ps) : w;
-                const int64_t lb = (m - ps - la) < w ? (m - ps - la) : w;
-                const int64_t d = o - ps;
-                int64_t lo = d > lb ? d - lb : 0, hi = d < la ? d : la;
+                const int la = (m - ps) < wd ? (m - ps) : wd;
+                const int lb = (m - ps - la) < wd ? (m - ps - la) : wd;
+                const int d = o - ps;
+                int lo = d > lb ? d - lb : 0, hi = d < la ? d : la;
                 while (lo < hi) {
-                    const int64_t mid = (lo + hi) >> 1;
-                    if (a[ps + mid] < a[ps + w + d - 1 - mid]) lo = mid + 1;
+                    const int mid = (lo + hi) >> 1;
+                    if (a[ps + mid] < a[ps + wd + d - 1 - mid]) lo = mid + 1;
                     else hi = mid;
                 }
                 s_split[k] = (int)lo;
             }
             __syncthreads();
-            for (int64_t k = 0; k < nb; ++k) {
-                const int64_t o0 = (tb + k) * kSortCap, ps = o0 / (2 * w) * (2 * w);
-                const int64_t la = (m - ps) < w ? (m - ps) : w;
-                const int64_t lb = (m - ps - la) < w ? (m - ps - la) : w;
-                const int64_t pend = ps + la + lb;
-                const int64_t o1 = o0 + kSortCap < pend ? o0 + kSortCap : pend;
-                const int64_t i0 = s_split[k], j0 = o0 - ps - i0;
+            for (int k = 0; k < nb; ++k) {
+                const int o0 = (tb + k) * kTile, ps = o0 / (2 * wd) * (2 * wd);
+                const int la = (m - ps) < wd ? (m - ps) : wd;
+                const int lb = (m - ps - la) < wd ? (m - ps - la) : wd;
+                const int pend = ps + la + lb;
+                const int o1 = o0 + kTile < pend ? o0 + kTile : pend;
+                const int i0 = s_split[k], j0 = o0 - ps - i0;
                 // the tile's end: the next tile's split inside the same pair, else the pair's end
-                const int64_t i1 = o1 == pend ? la : s_split[k + 1];
+                const int i1 = o1 == pend ? la : s_split[k + 1];
                 const int na = (int)(i1 - i0), nt = (int)(o1 - o0), nb2 = nt - na;
                 for (int t = threadIdx.x; t < nt; t += blockDim.x)
-                    s[t] = t < na ? a[ps + i0 + t] : a[ps + w + j0 + (t - na)];
+                    s[t] = t < na ? a[ps + i0 + t] : a[ps + wd + j0 + (t - na)];
                 __syncthreads();
                 // thread t writes outputs 4t .. 4t + 3 of the tile: its split in LDS, then a
                 // short sequential merge
@@ -1316,170 +1453,162 @@ __device__ __forceinline__ void sort_list(uint8_t *__restrict__ ws, const Inst &
         a = b;
         b = (uint64_t *)t;
     }
-    if (a != dst)
-        for (int64_t t = threadIdx.x; t < m; t += blockDim.x) dst[t] = a[t];
-    __syncthreads();
+    // a holds the sorted keys; in dst they are stored over themselves, so the neighbour's
+    // vertex is read before the barrier that precedes the stores of a chunk
+    for (int t0 = 0; t0 < m; t0 += blockDim.x) {
+        const int t = t0 + threadIdx.x;
+        const uint64_t k = t < m ? a[t] : 0, prev = t > 0 && t < m ? a[t - 1] : 0;
+        __syncthreads();
+        if (t < m) sort_emit(ws, I, cnt, w, L.dst, t, k, t == 0 || (prev >> kCodeBits) != (k >> kCodeBits));
+    }
 }
 
-// The three sorts of every instance in one launch: block (i, w) sorts list w of instance i, so
-// the lists of all instances are sorted side by side.  A list longer than the LDS merges
-// through scratch of its own: the sort scratch (KEEP edges), the live-edge arrays (KEEP
-// squares) and the root arrays (node keys), which the union-find only uses afterwards.
-// wide: the call sorts long lists with k_sort_runs and k_sort_merge (sort_is_wide), which this
-// launch leaves to them.
-__global__ __launch_bounds__(kSortThreads) void k_sort_lists(uint8_t *__restrict__ ws, int n, int wide) {
-    __shared__ uint64_t s[kSortCap];
-    __shared__ uint64_t s2[kSortCap];
-    const int i = blockIdx.x, w = blockIdx.y;
+// Merge pass of the lists longer than one run: grid (blocks, n, 4).  The runs are taken in
+// groups (all of them in one pass, or the square root of their number in each of two); a
+// key's place among its group is its own in its run plus the number of smaller keys in each
+// other run.  A workgroup places kMergeThreads consecutive keys of one run at a time: the part
+// of another run their searches can end in lies between the places of the first and the last of
+// them, about as many keys as they are, found by two lanes for 32 runs at once; those parts
+// are loaded into LDS together and searched there, four at a time (searched in global memory
+// from the start, each of the 11 to 13 steps waits for the L2: 31k keys in 16 runs 44 us, so
+// 17 us).  With the runs, 316^2 noise takes 35 us (one workgroup a list: 319 us), the 24k edges
+// of a 2048^2 8-bit field 40 us (274 us).  Passes alternate between the list's scratch and its place, and the last ends in place.
+constexpr int kMergeThreads = 256;
+constexpr int kMergeRuns = 32;             // runs searched together
+constexpr int kMergeWindow = 6144;         // keys of their windows held in LDS (48 KiB)
+
+// keys of a[0, n) below k
+__device__ __forceinline__ int keys_below(const uint64_t *a, int n, uint64_t k) {
+    int lo = 0, hi = n;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (a[mid] < k) lo = mid + 1;
+        else hi = mid;
+    }
+    return lo;
+}
+
+__global__ __launch_bounds__(kMergeThreads) void k_sort_merge(uint8_t *__restrict__ ws, int n, int run_max,
+                                                             int passes, int pass) {
+    __shared__ uint64_t s_win[kMergeWindow + 1];
+    __shared__ int s_lo[kMergeRuns], s_at[kMergeRuns + 1];
+    __shared__ int s_flag;
+    const int i = blockIdx.y, w = blockIdx.z;
     const Inst I = ((const Inst *)ws)[i];           // one batch of loads, before any atomic
     int32_t *cnt = (int32_t *)(ws + off_cnt(n)) + i * CNT_WORDS;
-    if (block_failed(cnt)) return;
-    const int mE = cnt[CNT_E], mF = cnt[CNT_F], mN = cnt[CNT_M0];
-    if (wide) {                                  // (an oversized count stays sort_list's error)
-        const int m = w == 0 ? mE : (w == 1 ? mF : mN);
-        if (sort_is_wide(I, m) && m <= (w == 0 ? I.E : (w == 1 ? I.F : I.M0cap))) return;
-    }
-    if (w == 0) {
-        sort_list<0>(ws, I, cnt, mE, s, s2);
-        if (I.h1 && I.ndim == 3) {
-            // 3D H1: the sorted position of each vertex's first KEEP edge (a vertex's KEEP edges
-            // are adjacent in the sorted list, by code)
-            const uint64_t *kE = arr<uint64_t>(ws, I.o_keyE);
-            int32_t *kpos = arr<int32_t>(ws, I.o_kpos);
-            for (int t = threadIdx.x; t < mE; t += blockDim.x) {
-                const uint32_t wv = key_pix(kE[t]);
-                if ((t == 0 || key_pix(kE[t - 1]) != wv) && wv < I.N) kpos[wv] = t;
-            }
-        }
-    } else if (w == 1) {
-        sort_list<1>(ws, I, cnt, mF, s, s2);
-    } else {
-        sort_list<2>(ws, I, cnt, mN, s, s2);
-    }
-}
-
-// ------------------------------------------------------------------ wide sort --
-// Under PH_WIDE a list longer than kSortCap keys of an instance of kWideVoxels or more voxels
-// (not under PH_H1) is sorted by the whole GPU: k_sort_runs sorts each of its kSortCap-key runs
-// in a workgroup of its own, then pass p of k_sort_merge merges the pairs of runs of
-// kSortCap << p keys, one workgroup an output tile of kSortCap keys (the merge-path tiles of
-// sort_list), from the list's output to its scratch on even passes and back on odd ones.
-// The first pass with nothing to merge copies a result left in the scratch back.  Grids
-// (blocks, n, 3): blockIdx.z = the list (KEEP edges, KEEP squares, H0 node keys).
-struct SortLists {
-    uint64_t *src, *dst, *scr;
-    int64_t cap;
-    int m;
-};
-__device__ __forceinline__ SortLists sort_lists_of(uint8_t *__restrict__ ws, const Inst &I, const int32_t *cnt, int w) {
-    SortLists L;
-    L.src = arr<uint64_t>(ws, w == 0 ? I.o_keyE : (w == 1 ? I.o_keyF : I.o_n0key));
-    L.dst = w == 2 ? arr<uint64_t>(ws, I.o_n0sorted) : L.src;
-    L.scr = arr<uint64_t>(ws, w == 0 ? I.o_scratch : (w == 1 ? I.o_live : I.o_ra));
-    L.cap = w == 0 ? I.E : (w == 1 ? I.F : I.M0cap);
-    L.m = cnt[w == 0 ? CNT_E : (w == 1 ? CNT_F : CNT_M0)];
-    return L;
-}
-
-// the list this block works on, or m = 0 (s_flag: the instance failed earlier)
-__device__ __forceinline__ SortLists sort_wide_list(uint8_t *__restrict__ ws, int n, int *s_flag) {
-    const int i = blockIdx.y;
-    const Inst &I = ((const Inst *)ws)[i];
-    int32_t *cnt = (int32_t *)(ws + off_cnt(n)) + i * CNT_WORDS;
-    if (threadIdx.x == 0) *s_flag = failed(cnt);
-    __syncthreads();
-    SortLists L = sort_lists_of(ws, I, cnt, blockIdx.z);
-    if (*s_flag || !sort_is_wide(I, L.m) || L.m > L.cap) L.m = 0;   // (an oversized count: k_sort_lists reports it)
-    return L;
-}
-
-__global__ __launch_bounds__(kSortThreads) void k_sort_runs(uint8_t *__restrict__ ws, int n) {
-    __shared__ uint64_t s[kSortCap];
-    __shared__ uint64_t s2[kSortCap];
-    __shared__ int s_flag;
-    const SortLists L = sort_wide_list(ws, n, &s_flag);
+    const SortLists L = sort_lists_of(ws, I, cnt, w);
     const int m = L.m;
-    for (int64_t base = (int64_t)blockIdx.x * kSortCap; base < m; base += (int64_t)gridDim.x * kSortCap) {
-        const int len = (int)((m - base) < kSortCap ? (m - base) : kSortCap);
-        int P = 2;
-        while (P < len) P <<= 1;
-        for (int t = threadIdx.x; t < kSortCap; t += blockDim.x) s[t] = t < len ? L.src[base + t] : ~0ull;
-        __syncthreads();
-        uint64_t x[4];
-        bitonic_regs(s, s2, P, x);
+    if (m <= run_max || m > L.cap) return;       // (k_sort_lists reports an oversized count)
+    if (threadIdx.x == 0) s_flag = failed(cnt);
+    lds_barrier();
+    if (s_flag) return;
+    const int runs = (m + run_max - 1) / run_max, run = (m + runs - 1) / runs;   // as k_sort_lists cut them
+    const int np = sort_passes(runs, passes);
+    if (pass >= np) return;
+    int fan = runs;                              // runs of a group: the smallest f with f^np >= runs
+    if (np == 2)
+        for (fan = 2; fan * fan < runs;) ++fan;
+    const int rl = pass == 0 ? run : fan * run, gl = pass == np - 1 ? m : rl * fan;   // keys of a run, a group
+    const uint64_t *a = (np - pass) & 1 ? L.scr : L.dst;
+    uint64_t *b = (np - pass) & 1 ? L.dst : L.scr;
+    const int steps = (rl + kMergeThreads - 1) / kMergeThreads, all = (m + rl - 1) / rl * steps;
+    for (int c = blockIdx.x; c < all; c += gridDim.x) {
+        const int r0 = c / steps * rl, t0 = r0 + c % steps * kMergeThreads;
+        if (t0 >= m) continue;                   // (past the end of a short last run)
+        const int g0 = r0 / gl * gl, g1 = g0 + gl < m ? g0 + gl : m;
+        const int r1 = r0 + rl < g1 ? r0 + rl : g1, tl = t0 + kMergeThreads <= r1 ? t0 + kMergeThreads - 1 : r1 - 1;
+        const int t = t0 + (int)threadIdx.x;
+        const uint64_t k = t <= tl ? a[t] : 0;
+        const uint64_t kfirst = a[t0], klast = a[tl];
+        int place = t - r0;                      // smaller keys of the group
+        bool first = t > tl || t == r0 || (a[t - 1] >> kCodeBits) != (k >> kCodeBits);
+        for (int q = g0; q < g1; q += kMergeRuns * rl) {
+            __syncthreads();                     // the last runs' windows have been read
+            static_assert(2 * kMergeRuns == 64, "one wave finds the windows");
+            if (threadIdx.x < 2 * kMergeRuns) {
+                // run j's window: from the key before the first one's place (the neighbour that
+                // may be of its vertex) to the last one's place; empty for the keys' own run
+                const int j = threadIdx.x & (kMergeRuns - 1), qs = q + j * rl;
+                const int len = qs < g1 && qs != r0 ? (g1 - qs < rl ? g1 - qs : rl) : 0;
+                int x = keys_below(a + qs, len, threadIdx.x < kMergeRuns ? kfirst : klast);
+                if (threadIdx.x < kMergeRuns && x > 0) --x;
+                const int end = __shfl(x, j + kMergeRuns, 64);
+                const int size = threadIdx.x < kMergeRuns ? end - x : 0;   // (never negative: first <= last)
+                const int upto = (int)wave_incl_sum((uint32_t)size);
+                if (threadIdx.x < kMergeRuns) {
+                    s_lo[j] = x;
+                    s_at[j] = upto - size;
+                    if (j == kMergeRuns - 1) s_at[kMergeRuns] = upto;
+                }
+            }
+            __syncthreads();
+            const int nr = (g1 - q + rl - 1) / rl < kMergeRuns ? (g1 - q + rl - 1) / rl : kMergeRuns;
+            // the windows one after another, kMergeWindow keys at a time (once, but for the keys
+            // of a short run); a key's places in the parts of a window add up
+            const int total = s_at[kMergeRuns];
+            for (int v0 = 0; v0 < total; v0 += kMergeWindow) {
+                if (v0) __syncthreads();         // the last part has been read
+                // part of window j: keys [p, e) of it, at slot s_at[j] + p - v0
+                auto part = [&](int j, int &p, int &e) {
+                    const int at = s_at[j], len = s_at[j + 1] - at;
+                    p = v0 - at > 0 ? v0 - at : 0;
+                    e = v0 + kMergeWindow - at < len ? v0 + kMergeWindow - at : len;
+                };
+                // a wave loads every fourth window
+                for (int j = threadIdx.x >> 6; j < nr; j += kMergeThreads / 64) {
+                    int p, e;
+                    part(j, p, e);
+                    const uint64_t *src = a + q + j * rl + s_lo[j];
+                    const int at = s_at[j] - v0;
+                    for (int x = p + __lane_id(); x < e; x += 64) s_win[at + x] = src[x];
+                }
+                __syncthreads();
+                if (t > tl) continue;
+                for (int j0 = 0; j0 < nr; j0 += 4) {
+                    int lo[4], hi[4], at[4], len = 0;   // places inside the parts
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (4 * (int)threadIdx.x + e < len) L.dst[base + 4 * threadIdx.x + e] = x[e];
-        __syncthreads();
+                    for (int j = 0; j < 4; ++j) {
+                        int p, e;
+                        part(j0 + j, p, e);
+                        lo[j] = 0;
+                        hi[j] = e > p ? e - p : 0;      // (0 past the last run)
+                        at[j] = e > p ? s_at[j0 + j] + p - v0 : 0;
+                        len = hi[j] > len ? hi[j] : len;
+                    }
+                    for (; len > 0; len >>= 1) {        // each step halves every search still open
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            // (branch-free, so the four reads are in flight together; a search
+                            // that has ended reads a slot it does not use)
+                            const int mid = (lo[j] + hi[j]) >> 1;
+                            const bool open = lo[j] < hi[j], less = s_win[at[j] + mid] < k;
+                            lo[j] = open && less ? mid + 1 : lo[j];
+                            hi[j] = open && !less ? mid : hi[j];
+                        }
+                    }
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        place += lo[j];
+                        if (w == 0 && I.h1 && lo[j] > 0)
+                            first = first && (s_win[at[j] + lo[j] - 1] >> kCodeBits) != (k >> kCodeBits);
+                    }
+                }
+            }
+            for (int j = 0; j < nr; ++j) place += s_lo[j];
+        }
+        if (t <= tl) {
+            if (pass == np - 1) sort_emit(ws, I, cnt, w, b, g0 + place, k, first);
+            else b[g0 + place] = k;
+        }
     }
 }
 
-__global__ __launch_bounds__(kSortThreads) void k_sort_merge(uint8_t *__restrict__ ws, int n, int pass) {
-    __shared__ uint64_t s[kSortCap];
-    __shared__ int64_t s_split[2];
-    __shared__ int s_flag;
-    const SortLists L = sort_wide_list(ws, n, &s_flag);
-    const int64_t m = L.m;
-    if (m == 0) return;
-    int np = 0;                                  // merge passes the list needs
-    while (((int64_t)kSortCap << np) < m) ++np;
-    if (pass >= np) {
-        if (pass == np && (np & 1))             // the last merge wrote the scratch
-            for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < m; t += (int64_t)gridDim.x * blockDim.x)
-                L.dst[t] = L.scr[t];
-        return;
-    }
-    const int64_t w = (int64_t)kSortCap << pass;
-    const uint64_t *a = pass & 1 ? L.scr : L.dst;
-    uint64_t *b = pass & 1 ? L.dst : L.scr;
-    const int64_t ntiles = (m + kSortCap - 1) / kSortCap;
-    for (int64_t k = blockIdx.x; k < ntiles; k += gridDim.x) {
-        // tile k: outputs [o0, o1) of its pair [ps, ps + la + lb); its first and last splits
-        // (left-run keys among the pair's first o - ps outputs, by merge path)
-        const int64_t o0 = k * kSortCap, ps = o0 / (2 * w) * (2 * w);
-        const int64_t la = (m - ps) < w ? (m - ps) : w;
-        const int64_t lb = (m - ps - la) < w ? (m - ps - la) : w;
-        const int64_t pend = ps + la + lb;
-        const int64_t o1 = o0 + kSortCap < pend ? o0 + kSortCap : pend;
-        if (threadIdx.x < 2) {
-            const int64_t o = threadIdx.x == 0 ? o0 : o1;
-            int64_t split = la;
-            if (o < pend) {
-                const int64_t d = o - ps;
-                int64_t lo = d > lb ? d - lb : 0, hi = d < la ? d : la;
-                while (lo < hi) {
-                    const int64_t mid = (lo + hi) >> 1;
-                    if (a[ps + mid] < a[ps + w + d - 1 - mid]) lo = mid + 1;
-                    else hi = mid;
-                }
-                split = lo;
-            }
-            s_split[threadIdx.x] = split;
-        }
-        __syncthreads();
-        const int64_t i0 = s_split[0], j0 = o0 - ps - i0;
-        const int na = (int)(s_split[1] - i0), nt = (int)(o1 - o0), nb2 = nt - na;
-        for (int t = threadIdx.x; t < nt; t += blockDim.x)
-            s[t] = t < na ? a[ps + i0 + t] : a[ps + w + j0 + (t - na)];
-        __syncthreads();
-        // thread t writes outputs 4t .. 4t + 3 of the tile: its split in LDS, then a short
-        // sequential merge
-        const int d = 4 * (int)threadIdx.x;
-        if (d < nt) {
-            int lo = d > nb2 ? d - nb2 : 0, hi = d < na ? d : na;
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (s[mid] < s[na + d - 1 - mid]) lo = mid + 1;
-                else hi = mid;
-            }
-            int ia = lo, ib = d - lo;
-            for (int e = 0; e < 4 && d + e < nt; ++e) {
-                const bool take_a = ib >= nb2 || (ia < na && s[ia] < s[na + ib]);
-                b[o0 + d + e] = take_a ? s[ia++] : s[na + ib++];
-            }
-        }
-        __syncthreads();
-    }
+// A forest of M nodes and m edges that takes the wide rounds (k_uf_wide) under PH_WIDE
+__device__ __forceinline__ bool uf_is_wide(const Inst &I, int M, int m) {
+    const int64_t L = I.E > I.F ? I.E : I.F;
+    // (the segments' sizes and the ranks of uf_rest follow the m positions in the live-edge array)
+    return I.N >= kWideVoxels && M > kUfWideNodes && M <= L && I.MTcap <= I.M0cap && m < 1 << kWidePosBits &&
+           m + m / kWideSeg + 1 + kRestNodes <= L;
 }
 
 // ===================================================================== resolve ====
@@ -1517,22 +1646,30 @@ __device__ __forceinline__ void chase2(const int32_t *__restrict__ p, int64_t x0
     if (a1) { set_err(cnt, PH_EINTERNAL); r1 = -1; }
 }
 
-// Add a per-thread count to a counter with one atomic per wave (all lanes of the wave call it).
-__device__ __forceinline__ void wave_count(int32_t *counter, int v) {
-    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
-    if (__lane_id() == 0 && v) atomicAdd(counter, v);
+// Add a per-thread count to a counter with one atomic a workgroup of 256 threads (every thread
+// calls it): thousands of atomics on one word queue up, and cost more than the walks they count.
+__device__ __forceinline__ void block_count(int32_t *counter, int v, int *s_sum) {
+    v = (int)wave_incl_sum((uint32_t)v);
+    if (__lane_id() == 63) s_sum[threadIdx.x >> 6] = v;
+    lds_barrier();
+    if (threadIdx.x == 0) {
+        v = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+        if (v) atomicAdd(counter, v);
+    }
 }
 
 // H0: the two endpoints of every sorted KEEP edge of instance i, as H0 nodes (local minima).
 // The blocks of one instance are blockIdx.x of gridDim.x; the links followed are counted.
-__device__ __forceinline__ void resolve_edges(uint8_t *__restrict__ ws, int n, int i) {
+__device__ __forceinline__ void resolve_edges(uint8_t *__restrict__ ws, int n, int i, bool wide, int *s_sum) {
     const Inst I = ((const Inst *)ws)[i];           // one batch of loads, before any atomic
     int32_t *cnt = (int32_t *)(ws + off_cnt(n)) + i * CNT_WORDS;
-    if (failed(cnt)) return;
+    if (block_failed(cnt)) return;
     const int m = cnt[CNT_E], M0 = cnt[CNT_M0];
     if (m > I.E) { set_err(cnt, PH_EINTERNAL); return; }
     const uint64_t *keyE = arr<uint64_t>(ws, I.o_keyE);
     const int32_t *par0 = arr<int32_t>(ws, I.o_par0);
+    const int32_t *rank0 = arr<int32_t>(ws, I.o_uf0);
+    const bool ids = wide && uf_is_wide(I, M0, m);  // the wide rounds keep the nodes' own numbers
     int32_t *ea = arr<int32_t>(ws, I.o_ea), *eb = arr<int32_t>(ws, I.o_eb);
     const int64_t HW = (int64_t)I.H * I.W;
     int hops = 0;
@@ -1546,24 +1683,29 @@ __device__ __forceinline__ void resolve_edges(uint8_t *__restrict__ ws, int n, i
         const int64_t u = v + off_of(code, 0) * HW + off_of(code, 1) * (int64_t)I.W + off_of(code, 2);
         int a, b;
         chase2(par0, v, u, true, true, I.N, M0, cnt, a, b, hops);
-        ea[r] = a;
-        eb[r] = b;
+        ea[r] = a < 0 || ids ? a : rank0[a];
+        eb[r] = b < 0 || ids ? b : rank0[b];
     }
-    wave_count(&cnt[CNT_HOPS0], hops);
+    block_count(&cnt[CNT_HOPS0], hops, s_sum);
 }
 
 // Top dimension: the two cofacets of every facet of instance i walked by the dual union-find,
-// as dual nodes (0 = the cell at infinity).  2D walks the KEEP edges that H0 did not use.
-__device__ __forceinline__ void resolve_facets(uint8_t *__restrict__ ws, int n, int i) {
+// as dual nodes (0 = the cell at infinity).  An image's facets are its KEEP edges; pruned: but
+// for those that H0 used.  (The dual union-find pairs the same without the pruning: the sides
+// of an edge that H0 used are joined by facets before it in the dual's walk, so it is never a
+// component's first facet.)
+__device__ __forceinline__ void resolve_facets(uint8_t *__restrict__ ws, int n, int i, bool pruned, bool wide,
+                                               int *s_sum) {
     const Inst I = ((const Inst *)ws)[i];           // one batch of loads, before any atomic
     int32_t *cnt = (int32_t *)(ws + off_cnt(n)) + i * CNT_WORDS;
-    if (failed(cnt)) return;
+    if (block_failed(cnt)) return;
     const bool is2d = I.ndim == 2;
     const int m = is2d ? cnt[CNT_E] : cnt[CNT_F], MT = cnt[CNT_MT];
     if (m > (is2d ? I.E : I.F) || MT > I.MTcap) { set_err(cnt, PH_EINTERNAL); return; }
     const uint64_t *key = arr<uint64_t>(ws, is2d ? I.o_keyE : I.o_keyF);
     const int32_t *neg0 = arr<int32_t>(ws, I.o_neg0);
-    const int32_t *parT = arr<int32_t>(ws, I.o_parT);
+    const int32_t *parT = arr<int32_t>(ws, I.o_parT), *rankT = arr<int32_t>(ws, I.o_ufT);
+    const bool ids = wide && uf_is_wide(I, MT, m);
     int32_t *fa = arr<int32_t>(ws, I.o_fa), *fb = arr<int32_t>(ws, I.o_fb);
     const int D = I.D, H = I.H, W = I.W;
     const int64_t HW = (int64_t)H * W;
@@ -1571,7 +1713,7 @@ __device__ __forceinline__ void resolve_facets(uint8_t *__restrict__ ws, int n, 
     for (int r0 = blockIdx.x * 256; r0 < m; r0 += gridDim.x * 256) {    // whole waves iterate
         const int r = r0 + threadIdx.x;
         if (r >= m) continue;
-        if (is2d && neg0[r]) { fa[r] = -1; fb[r] = -1; continue; }   // cross-pruned
+        if (pruned && neg0[r]) { fa[r] = -1; fb[r] = -1; continue; }   // cross-pruned
         const uint64_t k = key[r];
         const int64_t v = key_pix(k);
         const int code = key_code(k);
@@ -1598,21 +1740,22 @@ __device__ __forceinline__ void resolve_facets(uint8_t *__restrict__ ws, int n, 
         }
         int a, b;
         chase2(parT, top[0], top[1], in[0], in[1], I.T, MT, cnt, a, b, hops);
-        fa[r] = a;
-        fb[r] = b;
+        fa[r] = a > 0 && !ids ? rankT[a] : a;
+        fb[r] = b > 0 && !ids ? rankT[b] : b;
     }
-    wave_count(&cnt[CNT_HOPST], hops);
+    block_count(&cnt[CNT_HOPST], hops, s_sum);
 }
 
 // Resolve passes, blockIdx.y = instance.  Stage 0: blockIdx.z = 0 the KEEP edges of every
-// instance, z = 1 (with the top dimension) the facets of the volumes, whose dual does not wait
-// for H0.  Stage 1: the facets of the images, which need the edges H0 used.
-__global__ __launch_bounds__(256) void k_resolve(uint8_t *__restrict__ ws, int n, int stage, int htop) {
+// instance, z = 1 (with the top dimension) the facets of the volumes, and of the images unless a
+// stage 1 follows for them (staged), once the edges that H0 used are known.
+__global__ __launch_bounds__(256) void k_resolve(uint8_t *__restrict__ ws, int n, int stage, int staged, int htop, int wide) {
+    __shared__ int s_sum[4];
     const int i = blockIdx.y;
     const bool vol = ((const Inst *)ws)[i].ndim == 3;
-    if (stage == 0 && blockIdx.z == 0) resolve_edges(ws, n, i);
-    else if (stage == 0 && htop && vol) resolve_facets(ws, n, i);
-    else if (stage == 1 && !vol) resolve_facets(ws, n, i);
+    if (stage == 0 && blockIdx.z == 0) resolve_edges(ws, n, i, wide, s_sum);
+    else if (stage == 0 && htop && (vol || !staged)) resolve_facets(ws, n, i, false, wide, s_sum);
+    else if (stage == 1 && !vol) resolve_facets(ws, n, i, true, wide, s_sum);
 }
 
 // ================================================================== union-find ====
@@ -1626,9 +1769,8 @@ __global__ __launch_bounds__(256) void k_resolve(uint8_t *__restrict__ ws, int n
 // earlier edges).  The globally first live edge always fires, so rounds make progress; the
 // few edges left after kMaxRounds are finished in order by one thread, which is exact for
 // the same reason.
-// Node-array access: LDS arrays are coherent inside the block; global ones are read with
-// device-scope loads so a value another wave wrote (or an atomic updated) is never served
-// from a stale L1 line.
+// Global node arrays are read with device-scope loads so a value another wave wrote (or an
+// atomic updated) is never served from a stale L1 line.
 template <bool GLOBAL>
 __device__ __forceinline__ int32_t ld_node(int32_t *p) {
     if (GLOBAL) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1640,69 +1782,59 @@ __device__ __forceinline__ void st_node(int32_t *p, int32_t v) {
     else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// The round loop.  GN: the node arrays (par, moe) live in global memory, else in LDS; GL: the
-// live-edge arrays (walk position q, and the current roots A, B of the edge's two ends) live in
-// global memory, else in LDS; KG: the node keys are read from global memory, else copied to
-// LDS (s_key).  A fired edge is marked by complementing its q; compaction keeps the edges whose
-// ends still lie in different components and moves them down in place.
-// cont (global arrays only): the instance went through the wide rounds (k_uf_wide): par,
-// the deaths and the killers hold their state, and A[q], B[q] each edge's roots there (A[q] < 0:
-// done); the rounds go on from it.
-template <bool DUAL, bool GN, bool GL, bool KG = GN>
-__device__ __forceinline__ void uf_body(uint8_t *__restrict__ ws, int n, int32_t *par, int32_t *moe,
-                                        int32_t *live, int32_t *A, int32_t *B, uint64_t *s_key, int *s_wsum,
-                                        bool cont = false) {
-    const int i = blockIdx.x;
-    const Inst I = ((const Inst *)ws)[i];           // one batch of loads, before any atomic
-    int32_t *cnt = (int32_t *)(ws + off_cnt(n)) + i * CNT_WORDS;
-    const bool is2d = I.ndim == 2;
-    const int m = DUAL ? (is2d ? cnt[CNT_E] : cnt[CNT_F]) : cnt[CNT_E];
-    const int M = DUAL ? cnt[CNT_MT] : cnt[CNT_M0];
-    const int32_t *ea = arr<int32_t>(ws, DUAL ? I.o_fa : I.o_ea);
-    const int32_t *eb = arr<int32_t>(ws, DUAL ? I.o_fb : I.o_eb);
-    const uint64_t *gkey = arr<uint64_t>(ws, DUAL ? I.o_nTkey : I.o_n0key);
-    const uint64_t *nkey = KG ? gkey : s_key;       // node keys, else copied to LDS with the nodes
-    int32_t *neg0 = arr<int32_t>(ws, I.o_neg0);
-    int32_t *death0 = arr<int32_t>(ws, I.o_death0);
-    int32_t *killer = arr<int32_t>(ws, I.o_killer);
+// What one union-find works on (walk position q of an edge: its place r for H0, m - 1 - r for
+// the dual) and writes: each dying node's edge (death0) or each edge's victim (killer), and for
+// 3D H1 the edges H0 used (neg0).
+struct Forest {
+    bool dual;
+    int m, M;
+    const int32_t *ea, *eb;        // the edges' ends, by place
+    const int32_t *rank;           // wide forests: the nodes' ranks; else null, the nodes are ranks
+    int32_t *death0, *killer, *neg0;
+    __device__ __forceinline__ int edge_of(int q) const { return dual ? m - 1 - q : q; }
+    __device__ __forceinline__ int rank_of(int x) const { return rank ? rank[x] : x; }
+    // the node of rank `dead` dies on the edge of place r
+    __device__ __forceinline__ void fire(int dead, int r) const {
+        if (dual) killer[r] = dead;
+        else {
+            death0[dead] = r;
+            neg0[r] = 1;
+        }
+    }
+};
 
-    // elder(x, y): x entered earlier in the walk order
-    auto elder = [&](int x, int y) -> bool {
-        if (DUAL) return x == 0 || (y != 0 && nkey[x] > nkey[y]);
-        return nkey[x] < nkey[y];
-    };
+// The rounds out of the workspace: the general path, for forests that uf_lds cannot hold.  The
+// live-edge arrays hold the walk position q and the current roots A, B of the edge's two ends.
+// The elder of two nodes is the one of smaller rank.  A fired edge is marked by complementing
+// its q; compaction keeps the edges whose ends still lie in different components and moves them
+// down in place.
+// cont: the instance went through the wide rounds (k_uf_wide): par, the deaths and the killers
+// hold their state, and A[q], B[q] the roots of each edge left there (A[q] < 0: done); the
+// rounds go on from it.
+__device__ __forceinline__ void uf_body(const Forest &f, int32_t *cnt, int32_t *par, int32_t *moe, int32_t *live,
+                                        int32_t *A, int32_t *B, int *s_wsum, bool cont) {
+    const int m = f.m, M = f.M;
     auto find = [&](int x) -> int {
         for (int it = 0; it < kMaxChase; ++it) {
-            const int p = ld_node<GN>(&par[x]);
+            const int p = ld_node<true>(&par[x]);
             if (p == x) return x;
-            const int g = ld_node<GN>(&par[p]);
-            if (g != p) st_node<GN>(&par[x], g);       // path halving (any ancestor is valid)
+            const int g = ld_node<true>(&par[p]);
+            if (g != p) st_node<true>(&par[x], g);     // path halving (any ancestor is valid)
             x = g;
         }
         set_err(cnt, PH_EINTERNAL);
         return x;
     };
-    auto edge_of = [&](int q) { return DUAL ? m - 1 - q : q; };
-    // all state in LDS: the round barriers order LDS only (the rounds' global stores, the
-    // deaths and killers, are each written once and read after the kernel)
-    constexpr bool kLds = !GN && !GL;
-    auto fire = [&](int dead, int into, int r) {
-        st_node<GN>(&par[dead], into);
-        if (DUAL) killer[r] = dead;
-        else { death0[dead] = r; neg0[r] = 1; }
-    };
-
     for (int x = threadIdx.x; x < M; x += blockDim.x) {
-        if (!cont) st_node<GN>(&par[x], x);
-        st_node<GN>(&moe[x], kInf);
-        if (!KG) s_key[x] = gkey[x];
+        if (!cont) st_node<true>(&par[x], x);
+        st_node<true>(&moe[x], kInf);
     }
     if (cont) {
-    } else if (DUAL) {
-        for (int r = threadIdx.x; r < m; r += blockDim.x) killer[r] = -1;
+    } else if (f.dual) {
+        for (int r = threadIdx.x; r < m; r += blockDim.x) f.killer[r] = -1;
     } else {
-        for (int r = threadIdx.x; r < m; r += blockDim.x) neg0[r] = 0;
-        for (int x = threadIdx.x; x < M; x += blockDim.x) death0[x] = -1;
+        for (int r = threadIdx.x; r < m; r += blockDim.x) f.neg0[r] = 0;
+        for (int x = threadIdx.x; x < M; x += blockDim.x) f.death0[x] = -1;
     }
     __syncthreads();                                // the init stores land before any round's
 
@@ -1715,19 +1847,19 @@ __device__ __forceinline__ void uf_body(uint8_t *__restrict__ ws, int n, int32_t
         if (q < m && cont) {
             a = A[q];
             b = B[q];
-            flag = a >= 0 && !(a & kFired);
+            flag = a >= 0;
         } else if (q < m) {
-            const int r = edge_of(q);
-            a = ea[r];
-            b = eb[r];
+            const int r = f.edge_of(q);
+            a = f.ea[r];
+            b = f.eb[r];
             flag = a >= 0 && b >= 0 && a < M && b < M && a != b;
         }
         int tot;
-        const int pos = block_flag_scan<kLds>(flag, s_wsum, &tot);
+        const int pos = block_flag_scan(flag, s_wsum, &tot);
         if (flag) { live[L + pos] = q; A[L + pos] = a; B[L + pos] = b; }
         L += tot;
     }
-    block_sync<kLds>();
+    __syncthreads();
 
     int round = 0;
     for (; round < kMaxRounds && L > 0; ++round) {
@@ -1738,25 +1870,25 @@ __device__ __forceinline__ void uf_body(uint8_t *__restrict__ ws, int n, int32_t
             B[t] = y;
             if (x != y) { atomicMin(&moe[x], q); atomicMin(&moe[y], q); }
         }
-        block_sync<kLds>();
+        __syncthreads();
         for (int t = threadIdx.x; t < L; t += blockDim.x) {
             const int x = A[t], y = B[t];
             if (x == y) continue;
             const int q = live[t];
-            int dead = -1, into = -1;
-            if (ld_node<GN>(&moe[x]) == q && elder(y, x)) { dead = x; into = y; }
-            else if (ld_node<GN>(&moe[y]) == q && elder(x, y)) { dead = y; into = x; }
-            if (dead >= 0) {
-                fire(dead, into, edge_of(q));
+            const int rx = f.rank_of(x), ry = f.rank_of(y);
+            const int dead = rx > ry ? x : y, into = rx > ry ? y : x;   // only the younger can die
+            if (ld_node<true>(&moe[dead]) == q) {
+                st_node<true>(&par[dead], into);
+                f.fire(rx > ry ? rx : ry, f.edge_of(q));
                 live[t] = ~q;
             }
         }
-        block_sync<kLds>();
+        __syncthreads();
         for (int t = threadIdx.x; t < L; t += blockDim.x) {
-            st_node<GN>(&moe[A[t]], kInf);
-            st_node<GN>(&moe[B[t]], kInf);
+            st_node<true>(&moe[A[t]], kInf);
+            st_node<true>(&moe[B[t]], kInf);
         }
-        block_sync<kLds>();
+        __syncthreads();
         int L2 = 0;
         for (int base = 0; base < L; base += blockDim.x) {
             const int t = base + threadIdx.x;
@@ -1768,244 +1900,561 @@ __device__ __forceinline__ void uf_body(uint8_t *__restrict__ ws, int n, int32_t
                 flag = a != b && q >= 0;
             }
             int tot;
-            const int pos = block_flag_scan<kLds>(flag, s_wsum, &tot);   // every read of the chunk is done
+            const int pos = block_flag_scan(flag, s_wsum, &tot);         // every read of the chunk is done
             if (flag) { live[L2 + pos] = q; A[L2 + pos] = a; B[L2 + pos] = b; }
             L2 += tot;
         }
-        block_sync<kLds>();
+        __syncthreads();
         L = L2;
     }
     if (threadIdx.x == 0) {
-        cnt[DUAL ? CNT_ROUNDST : CNT_ROUNDS0] = round + (cont ? cnt[DUAL ? CNT_ROUNDST : CNT_ROUNDS0] : 0);
-        if (L > 0) cnt[CNT_SEQ] += L;
+        int32_t *rounds = &cnt[f.dual ? CNT_ROUNDST : CNT_ROUNDS0];
+        *rounds = round + (cont ? *rounds : 0);
+        if (L > 0) atomicAdd(&cnt[CNT_SEQ], L);
         for (int t = 0; t < L; ++t) {               // sequential finish, walk order
             const int q = live[t];
             const int x = find(A[t]), y = find(B[t]);
             if (x == y) continue;
-            const int dead = elder(y, x) ? x : y, into = dead == x ? y : x;
-            fire(dead, into, edge_of(q));
+            const int rx = f.rank_of(x), ry = f.rank_of(y);
+            st_node<true>(&par[rx > ry ? x : y], rx > ry ? y : x);
+            f.fire(rx > ry ? rx : ry, f.edge_of(q));
         }
     }
+}
+
+// The rounds of a forest of up to kUfLdsNodes nodes, out of LDS and registers: one word a node,
+// which for a root is its moe (kRoot, a tag that falls from round to round, an edge's place in
+// its batch: nothing needs clearing) and else its parent, so that a walk's last read brings the
+// root and its moe together; K edges a thread in registers (edge t + k kUfThreads of a batch in
+// ab[k] of thread t: its two current roots, 16 bits each, or kDone once it has fired or joins one
+// component), so a round touches no memory outside the compute unit.  Edges beyond a batch are
+// taken a batch after another in the walk's order: the rounds of a batch make the pairs that the
+// walk would make up to its end, and most edges of a later batch join one component already.
+// Node 0, the eldest, never dies and takes no atomics (its component grows to hold most edges'
+// ends).  The edges are taken kUfGroup at a time, so that the steps of their walks to the roots
+// are in flight together.  It is bound by the LDS reads of the walks: 31k edges and 20k nodes
+// (316^2 noise) 270 us with the edges in the workspace, 211 us with par and moe in words of
+// their own and batches of 32k edges, about 130 us so (batches of 4k to 16k edges: within 15 %).
+// MAPPED: the forest is what the wide rounds left (uf_rest): edge e of m joins the two nodes
+// packed in f.ea[e], numbered anyhow below M (s_rank: their ranks), and has walk position pos[e].
+constexpr uint32_t kDone = ~0u;
+constexpr uint32_t kRoot = 1u << 31;
+constexpr int kUfGroup = 2;
+constexpr int kUfPlaceBits = 14;           // an edge's place in its batch
+constexpr uint32_t kUfTags = (1u << (31 - kUfPlaceBits)) - 2;   // rounds of all batches
+constexpr int kUfLdsEdges = 1 << 24;       // edges of a forest: 48 rounds in each of 2048 batches
+
+// x, of unknown value to the compiler from here on: what is computed from it inside a loop is
+// not moved out (uf_lds would hold every edge's position in registers across its rounds)
+__device__ __forceinline__ int opaque(int x) {
+#if defined(__AMDGCN__)
+    asm volatile("" : "+v"(x));
+#endif
+    return x;
+}
+
+template <int K, bool MAPPED>
+__device__ __forceinline__ void uf_lds(const Forest &f, int m, int M, int32_t *cnt, uint32_t *s_node, const uint32_t *s_rank,
+                                       const int32_t *pos, int *s_wsum, int *s_any, int32_t *live, int32_t *A, int32_t *B) {
+    const int tid = threadIdx.x;
+    constexpr int kBatch = K * kUfThreads;
+    static_assert(kBatch <= 1 << kUfPlaceBits && (uint64_t)kUfLdsEdges / (8 * kUfThreads) * kMaxRounds < kUfTags, "places and tags");
+    auto rank_of = [&](uint32_t x) { return MAPPED ? s_rank[x] : x; };
+    auto place_of = [&](int e) { return f.edge_of(MAPPED ? pos[e] : e); };
+    auto get = [&](uint32_t x) { return __hip_atomic_load(&s_node[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
+    auto put = [&](uint32_t x, uint32_t v) { __hip_atomic_store(&s_node[x], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
+    for (int x = tid; x < M; x += kUfThreads) {
+        s_node[x] = ~0u;
+        if (!MAPPED && !f.dual) f.death0[x] = -1;
+    }
+    int rounds = 0;
+    for (int q0 = 0; q0 < m; q0 += kBatch) {
+        uint32_t ab[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int q = q0 + tid + k * kUfThreads;
+            ab[k] = kDone;
+            if (MAPPED) {
+                if (q < m) ab[k] = (uint32_t)f.ea[q];
+            } else if (q < m) {
+                const int r = f.edge_of(q), a = f.ea[r], b = f.eb[r];
+                if (a >= 0 && b >= 0 && a < M && b < M && a != b) ab[k] = (uint32_t)a | (uint32_t)b << 16;
+                if (f.dual) f.killer[r] = -1;
+                else f.neg0[r] = 0;
+            }
+        }
+        if (tid < 2) s_any[tid] = 0;
+        __syncthreads();                            // the init stores land before any round's
+        int round = 0;
+        bool left = true;                           // edges are left after the rounds
+        for (; round < kMaxRounds; ++round) {
+            const uint32_t tag = kRoot | (kUfTags - (uint32_t)(rounds + round)) << kUfPlaceBits;
+            const int t = opaque(tid);
+            bool any = false;
+#pragma unroll
+            for (int k0 = 0; k0 < K; k0 += kUfGroup) {
+                bool on = false;
+#pragma unroll
+                for (int j = 0; j < kUfGroup; ++j) on |= ab[k0 + j] != kDone;
+                if (!on) continue;
+                // both ends of the group's edges walk to their roots together, halving the paths
+                // (any ancestor is valid); w: the word at x
+                uint32_t x[2 * kUfGroup], w[2 * kUfGroup];
+#pragma unroll
+                for (int j = 0; j < kUfGroup; ++j) {
+                    const uint32_t v = ab[k0 + j];
+                    x[2 * j] = v == kDone ? 0u : v & 0xFFFFu;
+                    x[2 * j + 1] = v == kDone ? 0u : v >> 16;
+                }
+#pragma unroll
+                for (int j = 0; j < 2 * kUfGroup; ++j) w[j] = get(x[j]);
+                for (;;) {
+                    bool more = false;
+#pragma unroll
+                    for (int j = 0; j < 2 * kUfGroup; ++j) more |= !(w[j] & kRoot);
+                    if (!more) break;
+                    uint32_t p[2 * kUfGroup];
+#pragma unroll
+                    for (int j = 0; j < 2 * kUfGroup; ++j) p[j] = get(w[j] & kRoot ? x[j] : w[j]);
+#pragma unroll
+                    for (int j = 0; j < 2 * kUfGroup; ++j) {
+                        if (w[j] & kRoot) {
+                            w[j] = p[j];               // (a fresher moe)
+                        } else {
+                            if (!(p[j] & kRoot)) put(x[j], p[j]);
+                            x[j] = w[j];
+                            w[j] = p[j];
+                        }
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < kUfGroup; ++j) {
+                    const uint32_t a = x[2 * j], b = x[2 * j + 1], v = tag | (uint32_t)(t + (k0 + j) * kUfThreads);
+                    const bool in = ab[k0 + j] != kDone && a != b;
+                    ab[k0 + j] = in ? a | b << 16 : kDone;
+                    any |= in;
+                    // (a root's moe is settled early by its first edges: the read word tells)
+                    if (in && (MAPPED || a != 0) && v < w[2 * j]) atomicMin(&s_node[a], v);
+                    if (in && (MAPPED || b != 0) && v < w[2 * j + 1]) atomicMin(&s_node[b], v);
+                }
+            }
+            if (any) s_any[round & 1] = 1;
+            lds_barrier();
+            left = s_any[round & 1] != 0;
+            if (!left) break;
+            if (tid == 0) s_any[(round + 1) & 1] = 0;
+            // only the younger of an edge's roots can die on it; all the words are read together
+            // (a root's word still names its edge when another root has meanwhile died into it)
+            uint32_t w[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const uint32_t a = ab[k] == kDone ? 0u : ab[k] & 0xFFFFu, b = ab[k] == kDone ? 0u : ab[k] >> 16;
+                w[k] = get(rank_of(a) > rank_of(b) ? a : b);
+            }
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                if (ab[k] == kDone || w[k] != (tag | (uint32_t)(t + k * kUfThreads))) continue;
+                const uint32_t a = ab[k] & 0xFFFFu, b = ab[k] >> 16, ra = rank_of(a), rb = rank_of(b);
+                put(ra > rb ? a : b, ra > rb ? b : a);
+                f.fire((int)(ra > rb ? ra : rb), place_of(q0 + t + k * kUfThreads));
+                ab[k] = kDone;
+            }
+            lds_barrier();
+        }
+        rounds += round;
+        if (!left) continue;
+        // kMaxRounds were not enough: the batch's edges left, in walk order, for one thread to finish
+        int L = 0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int flag = ab[k] != kDone;
+            int tot;
+            const int at = block_flag_scan(flag, s_wsum, &tot);
+            if (flag) {
+                live[L + at] = q0 + tid + k * kUfThreads;
+                A[L + at] = (int32_t)(ab[k] & 0xFFFFu);
+                B[L + at] = (int32_t)(ab[k] >> 16);
+            }
+            L += tot;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            if (L > 0) atomicAdd(&cnt[CNT_SEQ], L);
+            auto root = [&](uint32_t x) {
+                for (uint32_t w = s_node[x]; !(w & kRoot); w = s_node[x]) {
+                    if (!(s_node[w] & kRoot)) s_node[x] = s_node[w];
+                    x = w;
+                }
+                return x;
+            };
+            for (int t = 0; t < L; ++t) {
+                const uint32_t x = root((uint32_t)A[t]), y = root((uint32_t)B[t]);
+                if (x == y) continue;
+                const uint32_t rx = rank_of(x), ry = rank_of(y);
+                s_node[rx > ry ? x : y] = rx > ry ? y : x;
+                f.fire((int)(rx > ry ? rx : ry), place_of(live[t]));
+            }
+        }
+        __syncthreads();
+    }
+    if (tid == 0) cnt[f.dual ? CNT_ROUNDST : CNT_ROUNDS0] = rounds + (MAPPED ? kWideRounds : 0);
 }
 
 // ------------------------------------------------------------- wide union-find --
-// Under PH_WIDE an instance of kWideVoxels or more voxels with more nodes than one
-// workgroup's LDS holds (kUfLdsNodesOnly) first runs up to kWideRounds of the rounds above
-// spread over kWideBlocks workgroups, one phase a launch; k_unionfind then goes on from there
-// in one workgroup (uf_body with cont) if edges are left.  Phase 0 of round r counts the
-// edges it finds live (CNT_WLIVE0 / CNT_WLIVET + r % 2, one atomic a workgroup); a round that
-// finds none ends the work, and the later launches return at once.  An edge keeps its walk position q: A[q], B[q] hold its two
-// roots; A[q] = -1 once it is done (both ends in one component), A[q] | kFired in the round it
-// fires.  Round r lowers moe_r, one of two node arrays taken in turn (moe, and the live-edge
-// array the continuation fills later), to the edges' q.  Phase 0 of round r first restores to
-// kInf the entries of the other array that round r - 1 lowered (the two roots each edge still
-// names), then finds each live edge's roots and lowers theirs; phase 1 fires each root whose
-// minimum edge reaches an elder root.  These are the rounds of uf_body, taken by the whole grid.
-__device__ __forceinline__ bool uf_is_wide(const Inst &I, int M, int m) {
-    const int64_t L = I.E > I.F ? I.E : I.F;      // the second node array is a live-edge array
-    return I.N >= kWideVoxels && M > kUfLdsNodesOnly && M <= L;
-}
-
-// phase -1: initialise; 0, 1: the two phases of round `round`.  Grid (kWideBlocks, n, side)
-template <bool DUAL>
-__device__ __forceinline__ void uf_wide(uint8_t *__restrict__ ws, int n, int phase, int round, int *s_flag) {
-    const int i = blockIdx.y;
-    const Inst I = ((const Inst *)ws)[i];           // one batch of loads, before any atomic
-    int32_t *cnt = (int32_t *)(ws + off_cnt(n)) + i * CNT_WORDS;
-    const int M = DUAL ? cnt[CNT_MT] : cnt[CNT_M0];
-    const int m = DUAL ? (I.ndim == 2 ? cnt[CNT_E] : cnt[CNT_F]) : cnt[CNT_E];
-    if (threadIdx.x == 0) *s_flag = failed(cnt);
-    lds_barrier();
-    if (*s_flag || !uf_is_wide(I, M, m)) return;
-    if (M > (DUAL ? I.MTcap : I.M0cap) || m > (DUAL && I.ndim == 3 ? I.F : I.E)) {
-        if (threadIdx.x == 0 && blockIdx.x == 0 && phase < 0) set_err(cnt, PH_EINTERNAL);
-        return;
-    }
-    // wlive[r % 2]: nonzero when round r found a live edge.  Phase 1 of round r clears the
-    // other slot for round r + 1 (phase 0 of round r read it last); a round that found none
-    // leaves both at 0, so every later launch returns here.  One thread of a workgroup reads
-    // the flags (a word every workgroup reads at once is a hot spot).
-    int32_t *wlive = cnt + (DUAL ? CNT_WLIVET : CNT_WLIVE0);
-    const int t0 = blockIdx.x * blockDim.x + threadIdx.x;
-    if (phase >= 0) {
-        if (phase == 1 && t0 == 0) __hip_atomic_store(&wlive[(round + 1) & 1], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();                             // every thread has read s_flag[0]
-        if (threadIdx.x == 0) {
-            const int slot = phase == 0 ? (round - 1) & 1 : round & 1;
-            s_flag[0] = (phase == 0 && round == 0) ||
-                        __hip_atomic_load(&wlive[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-        }
-        __syncthreads();
-        if (!s_flag[0]) return;
-    }
-    int32_t *par = arr<int32_t>(ws, DUAL ? I.o_ufT : I.o_uf0);
-    int32_t *moe_even = arr<int32_t>(ws, DUAL ? I.o_moeT : I.o_moe0);
-    int32_t *moe_odd = arr<int32_t>(ws, DUAL ? I.o_live2 : I.o_live);
-    int32_t *cur = round & 1 ? moe_odd : moe_even, *prev = round & 1 ? moe_even : moe_odd;
+// Under PH_WIDE a forest of more than kUfWideNodes nodes, of an instance of kWideVoxels or more
+// voxels, first takes kWideRounds of the rounds above spread over the whole GPU; k_unionfind then
+// finishes what is left in one workgroup (uf_rest).  Two launches a round: phase 0 finds each
+// live edge's roots and lowers their moe, phase 1 fires the roots whose least edge reaches an
+// elder root.  An edge takes part as (walk position, root, root) in the segment of kWideSeg
+// positions it comes from; phase 0 drops the edges that have fired or join one component and
+// closes the gaps, in order, inside each segment, so the work shrinks with the live edges and
+// no workgroup waits for another.  moe needs no clearing: an entry is an edge's walk position
+// below a tag that falls from round to round.
+// Nodes keep the numbers the classify pass gave them (neighbours in space, so the walks stay in
+// few cache lines: in order of age each launch took twice as long) and are compared by rank;
+// the resolve passes leave them so.  The eldest node never dies and takes no atomics: its
+// component grows to hold most edges' ends, and one word taking an atomic per edge is a hot spot.
+// Noise of 2^20 pixels: after four rounds 13k of 210k nodes and 85k of 326k edges are left, which
+// one workgroup's LDS holds; more rounds here would end few nodes each.
+// The arrays of a wide forest: par and moe (which holds the left nodes' new numbers in the end);
+// the segments' edges (walk position, roots) and sizes; the same of all segments closed up, both
+// ends packed in one word (ends, pos); the ranks, and those of the nodes left by new number; the
+// eldest node, and the numbers of edges and nodes left.
+struct WideForest {
+    int32_t *par, *q, *a, *b, *size, *ends, *pos, *rank, *left, *eldest, *total, *nodes;
+    uint32_t *moe;
+};
+__device__ __forceinline__ WideForest wide_forest(uint8_t *__restrict__ ws, const Inst &I, int32_t *cnt, bool dual, int m) {
     const int64_t L = I.E > I.F ? I.E : I.F;
-    int32_t *A = DUAL ? arr<int32_t>(ws, I.o_scratch) : arr<int32_t>(ws, I.o_ra);
-    int32_t *B = DUAL ? arr<int32_t>(ws, I.o_scratch) + L : arr<int32_t>(ws, I.o_rb);
-    const uint64_t *nkey = arr<uint64_t>(ws, DUAL ? I.o_nTkey : I.o_n0key);
-    int32_t *neg0 = arr<int32_t>(ws, I.o_neg0);
-    int32_t *death0 = arr<int32_t>(ws, I.o_death0);
-    int32_t *killer = arr<int32_t>(ws, I.o_killer);
-    const int stride = gridDim.x * blockDim.x;
-    auto edge_of = [&](int q) { return DUAL ? m - 1 - q : q; };
-    if (phase < 0) {
-        const int32_t *ea = arr<int32_t>(ws, DUAL ? I.o_fa : I.o_ea);
-        const int32_t *eb = arr<int32_t>(ws, DUAL ? I.o_fb : I.o_eb);
-        if (t0 < 2) wlive[t0] = 0;
-        if (t0 == 0) cnt[DUAL ? CNT_ROUNDST : CNT_ROUNDS0] = 0;
-        for (int x = t0; x < M; x += stride) {
-            par[x] = x;
-            moe_even[x] = kInf;
-            moe_odd[x] = kInf;
-            if (!DUAL) death0[x] = -1;
-        }
-        for (int q = t0; q < m; q += stride) {
-            const int r = edge_of(q), a = ea[r], b = eb[r];
-            const bool ok = a >= 0 && b >= 0 && a < M && b < M && a != b;
-            A[q] = ok ? a : -1;
-            B[q] = b;
-            if (DUAL) killer[r] = -1;
-            else neg0[r] = 0;
-        }
-        return;
-    }
-    auto elder = [&](int x, int y) -> bool {
-        if (DUAL) return x == 0 || (y != 0 && nkey[x] > nkey[y]);
-        return nkey[x] < nkey[y];
-    };
-    // Phase 0 changes par only by path halving, which keeps every link pointing to an
-    // ancestor, and lowers moe only: a stale read of either (through the workgroup's cache) is
-    // an older ancestor or a higher moe, so the roots found and the atomics taken stay right.
-    auto find = [&](int x) -> int {
-        for (int it = 0; it < kMaxChase; ++it) {
-            const int p = ld_node<false>(&par[x]);
-            if (p == x) return x;
-            const int g = ld_node<false>(&par[p]);
-            if (g != p) st_node<true>(&par[x], g);     // path halving (any ancestor is valid)
-            x = g;
-        }
-        set_err(cnt, PH_EINTERNAL);
-        return x;
-    };
-    int live = 0;
-    // The eldest node (the cell at infinity; for H0 the node of the least key, first of the
-    // sorted node keys) never dies, so its moe is never needed: its component, which grows
-    // to hold most edges' ends, would otherwise take one atomic per edge on one word.
-    int eldest = 0;
-    if (!DUAL) {
-        if (threadIdx.x == 0) {
-            const uint64_t k0 = arr<uint64_t>(ws, I.o_n0sorted)[0];
-            const uint32_t p0 = key_pix(k0);
-            const int id = p0 < (uint32_t)I.N ? -(arr<int32_t>(ws, I.o_par0)[p0] + 1) : -1;
-            s_flag[1] = id >= 0 && id < M ? id : -1;     // -1: every root takes its atomics
-        }
-        __syncthreads();
-        eldest = s_flag[1];
-    }
-    for (int q = t0; q < m; q += stride) {
-        const int a = A[q];
-        if (a < 0) continue;
-        if (phase == 0) {
-            const int b = B[q];
-            if (round > 0) {                        // the entries round - 1 lowered
-                prev[a & ~kFired] = kInf;
-                prev[b] = kInf;
-            }
-            if (a & kFired) { A[q] = -1; continue; }
-            const int x = find(a), y = find(b);
-            if (x == y) { A[q] = -1; continue; }
-            A[q] = x;
-            B[q] = y;
-            ++live;
-            // a root's moe is settled early by its first edges: read before the atomic
-            if (x != eldest && q < ld_node<false>(&cur[x])) atomicMin(&cur[x], q);
-            if (y != eldest && q < ld_node<false>(&cur[y])) atomicMin(&cur[y], q);
-        } else {
-            const int x = a, y = B[q];
-            int dead = -1, into = -1;
-            if (cur[x] == q && elder(y, x)) { dead = x; into = y; }
-            else if (cur[y] == q && elder(x, y)) { dead = y; into = x; }
-            if (dead >= 0) {
-                st_node<true>(&par[dead], into);
-                const int r = edge_of(q);
-                if (DUAL) killer[r] = dead;
-                else { death0[dead] = r; neg0[r] = 1; }
-                A[q] = a | kFired;
-            }
-        }
-    }
-    if (phase == 0 && __syncthreads_or(live > 0) && threadIdx.x == 0) {
-        // the flag and the rounds counter, written only while not yet set (read first)
-        if (__hip_atomic_load(&wlive[round & 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
-            __hip_atomic_store(&wlive[round & 1], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        int32_t *rc = &cnt[DUAL ? CNT_ROUNDST : CNT_ROUNDS0];
-        if (__hip_atomic_load(rc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < round + 1) atomicMax(rc, round + 1);
-    }
+    const int d = dual ? 1 : 0;
+    WideForest w;
+    w.par = arr<int32_t>(ws, pick(d, I.o_uf0, I.o_ufT, 0, 0));
+    w.moe = arr<uint32_t>(ws, pick(d, I.o_moe0, I.o_moeT, 0, 0));
+    w.q = arr<int32_t>(ws, pick(d, I.o_live, I.o_live2, 0, 0));
+    w.size = w.q + m;
+    w.a = arr<int32_t>(ws, pick(d, I.o_ra, I.o_scratch, 0, 0));
+    w.b = arr<int32_t>(ws, pick(d, I.o_rb, I.o_scratch + 4 * L, 0, 0));
+    w.left = w.size + m / kWideSeg + 1;
+    w.ends = arr<int32_t>(ws, pick(d, I.o_ea, I.o_fa, 0, 0));    // (the edges' ends, read only by the set-up)
+    w.pos = arr<int32_t>(ws, pick(d, I.o_eb, I.o_fb, 0, 0));
+    w.rank = arr<int32_t>(ws, I.o_n0key + pick(d, 0, 4 * I.M0cap, 0, 0));   // (the unsorted node keys are not needed)
+    w.eldest = cnt + (dual ? CNT_WELDT : CNT_WELD0);
+    w.total = cnt + (dual ? CNT_WLEFTT : CNT_WLEFT0);
+    w.nodes = cnt + (dual ? CNT_WNODEST : CNT_WNODES0);
+    return w;
 }
 
-// blockIdx.y = instance; stage and blockIdx.z choose H0 or the dual as in k_unionfind
-__global__ __launch_bounds__(kWideThreads) void k_uf_wide(uint8_t *__restrict__ ws, int n, int stage, int htop,
+// phase -1: set up; 0, 1: the two phases of round `round` (in phase 0 of round kWideRounds, the
+// last, moe[x] = 0 marks the roots left); 2: the roots left numbered; 3: the segments closed up.
+// Grid (blocks, n, side): blockIdx.y = instance; stage and blockIdx.z choose H0 or the dual as
+// in k_unionfind.
+__global__ __launch_bounds__(kWideThreads) void k_uf_wide(uint8_t *__restrict__ ws, int n, int stage, int staged, int htop,
                                                           int phase, int round) {
-    __shared__ int s_flag[2];                    // the instance failed; the eldest H0 node
-    const bool vol = ((const Inst *)ws)[blockIdx.y].ndim == 3;
-    if (stage == 0 && blockIdx.z == 0) uf_wide<false>(ws, n, phase, round, s_flag);
-    else if ((stage == 0 && htop && vol) || (stage == 1 && !vol)) uf_wide<true>(ws, n, phase, round, s_flag);
-}
-
-// Instances with at most kUfLdsNodes nodes keep par, moe and the node keys in LDS, and with
-// at most kUfLdsEdges edges their live-edge arrays too; up to kUfLdsNodesOnly nodes keep par
-// and moe in the whole LDS (keys and live edges in the workspace); larger ones use the
-// workspace for everything.  The H0 and dual union-finds of one volume run side by side: the
-// dual keeps its live edges in the free second live array and its roots in the sort scratch
-// (8 max(L, N) bytes).  s_lds: kUfLdsWords int32 words, 8-byte aligned.
-template <bool DUAL>
-__device__ __forceinline__ void uf_run(uint8_t *__restrict__ ws, int n, int32_t *s_lds, int *s_wsum, bool wide) {
-    const int i = blockIdx.x;
+    __shared__ int s_cnt[kWidePer][kWideThreads / 64];
+    __shared__ int s_flag;
+    const int i = blockIdx.y, tid = threadIdx.x, lane = __lane_id(), wid = tid >> 6;
     const Inst I = ((const Inst *)ws)[i];           // one batch of loads, before any atomic
-    const int32_t *cnt = (const int32_t *)(ws + off_cnt(n)) + i * CNT_WORDS;
-    const int M = DUAL ? cnt[CNT_MT] : cnt[CNT_M0];
-    const int m = DUAL ? (I.ndim == 2 ? cnt[CNT_E] : cnt[CNT_F]) : cnt[CNT_E];
-    if (block_failed(cnt)) return;
-    if (M < 1 || M > (DUAL ? I.MTcap : I.M0cap) || m > (DUAL && I.ndim == 3 ? I.F : I.E)) {
-        if (threadIdx.x == 0) set_err((int32_t *)cnt, PH_EINTERNAL);
+    const bool is2d = I.ndim == 2, dual = stage == 1 || blockIdx.z == 1;
+    if (dual && (!htop || (is2d && (stage == 1) != (staged != 0)) || (stage == 1 && !is2d))) return;
+    int32_t *cnt = (int32_t *)(ws + off_cnt(n)) + i * CNT_WORDS;
+    const int mE = cnt[CNT_E], mF = cnt[CNT_F], m0 = cnt[CNT_M0], mT = cnt[CNT_MT];
+    const int M = dual ? mT : m0, m = !dual || is2d ? mE : mF;
+    const int segs = (m + kWideSeg - 1) / kWideSeg;
+    if ((int)blockIdx.x >= segs && phase != -1 && phase != 2) return;
+    if (tid == 0) s_flag = failed(cnt);
+    lds_barrier();
+    if (s_flag || !uf_is_wide(I, M, m)) return;
+    if (M > (dual ? I.MTcap : I.M0cap) || m > (dual && !is2d ? I.F : I.E)) {
+        if (tid == 0 && blockIdx.x == 0 && phase < 0) set_err(cnt, PH_EINTERNAL);
         return;
     }
-    int32_t *gpar = arr<int32_t>(ws, DUAL ? I.o_ufT : I.o_uf0), *gmoe = arr<int32_t>(ws, DUAL ? I.o_moeT : I.o_moe0);
-    const int64_t L = I.E > I.F ? I.E : I.F;
-    int32_t *glive = arr<int32_t>(ws, DUAL ? I.o_live2 : I.o_live);
-    int32_t *ga = DUAL ? arr<int32_t>(ws, I.o_scratch) : arr<int32_t>(ws, I.o_ra);
-    int32_t *gb = DUAL ? arr<int32_t>(ws, I.o_scratch) + L : arr<int32_t>(ws, I.o_rb);
-    // LDS carve for the small case: par, moe (kUfLdsNodes each), live, A, B (kUfLdsEdges each),
-    // then the node keys (8-byte aligned: the offset is even)
-    int32_t *s_par = s_lds, *s_moe = s_lds + kUfLdsNodes, *s_live = s_lds + 2 * kUfLdsNodes;
-    int32_t *s_a = s_live + kUfLdsEdges, *s_b = s_a + kUfLdsEdges;
-    uint64_t *s_key = (uint64_t *)(s_b + kUfLdsEdges);
-    static_assert((2 * kUfLdsNodes + 3 * kUfLdsEdges) % 2 == 0, "node keys 8-byte aligned");
-    static_assert(2 * kUfLdsNodes + 3 * kUfLdsEdges + 2 * kUfLdsNodes <= kUfLdsWords, "LDS carve");
-    if (wide && uf_is_wide(I, M, m)) {
-        // the wide rounds' last round found no live edge: nothing is left
-        if (cnt[(DUAL ? CNT_WLIVET : CNT_WLIVE0) + ((kWideRounds - 1) & 1)] == 0) return;
-        uf_body<DUAL, true, true>(ws, n, gpar, gmoe, glive, ga, gb, nullptr, s_wsum, true);
+    const WideForest w = wide_forest(ws, I, cnt, dual, m);
+    int32_t *death0 = arr<int32_t>(ws, I.o_death0), *killer = arr<int32_t>(ws, I.o_killer), *neg0 = arr<int32_t>(ws, I.o_neg0);
+    auto edge_of = [&](int q) { return dual ? m - 1 - q : q; };
+    if (phase < 0) {
+        for (int x = blockIdx.x * kWideThreads + tid; x < M; x += gridDim.x * kWideThreads) {
+            const int r = dual && x == 0 ? 0 : w.par[x];   // (the sort left the ranks in par)
+            w.rank[x] = r;
+            if (r == 0) *w.eldest = x;
+            w.par[x] = x;
+            w.moe[x] = ~0u;
+            if (!dual) death0[x] = -1;
+        }
     }
-    else if (M <= kUfLdsNodes && m <= kUfLdsEdges) uf_body<DUAL, false, false>(ws, n, s_par, s_moe, s_live, s_a, s_b, s_key, s_wsum);
-    else if (M <= kUfLdsNodes) uf_body<DUAL, false, true>(ws, n, s_par, s_moe, glive, ga, gb, s_key, s_wsum);
-    else if (M <= kUfLdsNodesOnly)
-        uf_body<DUAL, false, true, true>(ws, n, s_lds, s_lds + kUfLdsNodesOnly, glive, ga, gb, nullptr, s_wsum);
-    else uf_body<DUAL, true, true>(ws, n, gpar, gmoe, glive, ga, gb, nullptr, s_wsum);
+    if (phase == 2) {
+        // one atomic a workgroup and pass; new numbers in any order
+        for (int x0 = blockIdx.x * kWideThreads; x0 < M; x0 += gridDim.x * kWideThreads) {
+            const int x = x0 + tid;
+            const bool mark = x < M && w.moe[x] == 0;
+            const uint64_t vote = __ballot(mark);
+            __syncthreads();                         // the last pass's counts have been read
+            if (lane == 0) s_cnt[0][wid] = __popcll(vote);
+            __syncthreads();
+            int sum = 0, before = 0;
+            for (int v = 0; v < kWideThreads / 64; ++v) {
+                if (v < wid) before += s_cnt[0][v];
+                sum += s_cnt[0][v];
+            }
+            if (tid == 0) s_flag = sum ? atomicAdd(w.nodes, sum) : 0;
+            __syncthreads();
+            if (mark) {
+                const int id = s_flag + before + __popcll(vote & ((1ull << lane) - 1ull));
+                w.moe[x] = (uint32_t)id;
+                if (id < kRestNodes) w.left[id] = w.rank[x];
+            }
+        }
+        return;
+    }
+    const uint32_t tag = (uint32_t)(kWideRounds - round) << kWidePosBits;
+    const int eldest = phase == 0 ? *w.eldest : 0;
+    for (int sg = blockIdx.x; sg < segs; sg += gridDim.x) {
+        const int at = sg * kWideSeg, all = m - at < kWideSeg ? m - at : kWideSeg;
+        const int size = phase < 0 ? all : w.size[sg];
+        int q[kWidePer], a[kWidePer], b[kWidePer];
+        if (phase == 3) {
+            // the segment's first place: the sizes before it
+            int before = 0;
+            for (int k = tid; k < sg; k += kWideThreads) before += w.size[k];
+            const int upto = (int)wave_incl_sum((uint32_t)before);
+            __syncthreads();                         // the last segment's sums have been read
+            if (lane == 63) s_cnt[0][wid] = upto;
+            __syncthreads();
+            int first = 0;
+            for (int v = 0; v < kWideThreads / 64; ++v) first += s_cnt[0][v];
+            for (int e = tid; e < size; e += kWideThreads) {
+                w.pos[first + e] = w.q[at + e];
+                w.ends[first + e] = (int32_t)(w.moe[w.a[at + e]] | w.moe[w.b[at + e]] << 16);
+            }
+            if (sg == segs - 1 && tid == 0) *w.total = first + size;
+            continue;
+        }
+        if (phase == 1) {
+#pragma unroll
+            for (int j = 0; j < kWidePer; ++j) {
+                const int e = j * kWideThreads + tid;
+                q[j] = a[j] = b[j] = 0;
+                if (e < size) { q[j] = w.q[at + e]; a[j] = w.a[at + e]; b[j] = w.b[at + e]; }
+            }
+            uint32_t xa[kWidePer], xb[kWidePer];
+            int ra[kWidePer], rb[kWidePer];          // (equal: no root of the edge may die on it)
+#pragma unroll
+            for (int j = 0; j < kWidePer; ++j) {     // (an edge past the segment's end reads node 0)
+                xa[j] = w.moe[a[j]];
+                xb[j] = w.moe[b[j]];
+                ra[j] = rb[j] = 0;
+            }
+#pragma unroll
+            for (int j = 0; j < kWidePer; ++j) {
+                const int e = j * kWideThreads + tid;
+                const uint32_t v = tag | (uint32_t)q[j];
+                if (e >= size || (xa[j] != v && xb[j] != v)) continue;
+                ra[j] = w.rank[a[j]];
+                rb[j] = w.rank[b[j]];
+            }
+#pragma unroll
+            for (int j = 0; j < kWidePer; ++j) {
+                const int e = j * kWideThreads + tid;
+                const uint32_t v = tag | (uint32_t)q[j];
+                if (e >= size || (ra[j] > rb[j] ? xa[j] : xb[j]) != v || ra[j] == rb[j]) continue;   // only the younger can die
+                st_node<true>(&w.par[ra[j] > rb[j] ? a[j] : b[j]], ra[j] > rb[j] ? b[j] : a[j]);
+                const int r = edge_of(q[j]), dead = ra[j] > rb[j] ? ra[j] : rb[j];
+                if (dual) killer[r] = dead;
+                else { death0[dead] = r; neg0[r] = 1; }
+                w.a[at + e] = -1;                    // dropped by the next round
+            }
+            continue;
+        }
+        // phase -1 reads the resolved edges, phase 0 the segment; both keep the live ones
+        bool in[kWidePer];
+        if (phase < 0) {
+            const int32_t *ea = arr<int32_t>(ws, pick(dual, I.o_ea, I.o_fa, 0, 0)), *eb = arr<int32_t>(ws, pick(dual, I.o_eb, I.o_fb, 0, 0));
+#pragma unroll
+            for (int j = 0; j < kWidePer; ++j) {
+                const int e = j * kWideThreads + tid;
+                q[j] = at + e;
+                a[j] = b[j] = -1;
+                if (e < size) {
+                    const int r = edge_of(q[j]);
+                    a[j] = ea[r];
+                    b[j] = eb[r];
+                    if (dual) killer[r] = -1;
+                    else neg0[r] = 0;
+                }
+                in[j] = a[j] >= 0 && b[j] >= 0 && a[j] < M && b[j] < M && a[j] != b[j];
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < kWidePer; ++j) {
+                const int e = j * kWideThreads + tid;
+                q[j] = 0;
+                a[j] = b[j] = -1;
+                if (e < size) { q[j] = w.q[at + e]; a[j] = w.a[at + e]; b[j] = w.b[at + e]; }
+            }
+            // Every end walks to its root, all walks in step so that their loads are in flight
+            // together (a dropped edge's ends stand at the eldest).  Phase 0 changes par only by
+            // path halving, which keeps every link pointing to an ancestor, and lowers moe
+            // only: a stale read of either (through the workgroup's cache) is an older ancestor
+            // or a higher moe, so the roots found and the atomics taken stay right.
+#pragma unroll
+            for (int j = 0; j < kWidePer; ++j) {
+                in[j] = a[j] >= 0;
+                if (!in[j]) a[j] = b[j] = eldest;
+            }
+            bool more = true;
+            for (int it = 0; more && it < kMaxChase; ++it) {
+                int pa[kWidePer], pb[kWidePer], ga[kWidePer], gb[kWidePer];
+#pragma unroll
+                for (int j = 0; j < kWidePer; ++j) {
+                    pa[j] = ld_node<false>(&w.par[a[j]]);
+                    pb[j] = ld_node<false>(&w.par[b[j]]);
+                }
+#pragma unroll
+                for (int j = 0; j < kWidePer; ++j) {
+                    ga[j] = ld_node<false>(&w.par[pa[j]]);
+                    gb[j] = ld_node<false>(&w.par[pb[j]]);
+                }
+                more = false;
+#pragma unroll
+                for (int j = 0; j < kWidePer; ++j) {
+                    if (ga[j] != pa[j]) { st_node<true>(&w.par[a[j]], ga[j]); more = true; }
+                    if (gb[j] != pb[j]) { st_node<true>(&w.par[b[j]], gb[j]); more = true; }
+                    a[j] = ga[j];
+                    b[j] = gb[j];
+                }
+            }
+            if (more) set_err(cnt, PH_EINTERNAL);
+#pragma unroll
+            for (int j = 0; j < kWidePer; ++j) {
+                in[j] = in[j] && a[j] != b[j];
+                if (in[j] && round == kWideRounds) w.moe[a[j]] = w.moe[b[j]] = 0;
+            }
+            if (round < kWideRounds) {
+                uint32_t xa[kWidePer], xb[kWidePer];
+#pragma unroll
+                for (int j = 0; j < kWidePer; ++j) {
+                    // a root's moe is settled early by its first edges: read before the atomic
+                    xa[j] = (uint32_t)ld_node<false>((int32_t *)&w.moe[a[j]]);
+                    xb[j] = (uint32_t)ld_node<false>((int32_t *)&w.moe[b[j]]);
+                }
+#pragma unroll
+                for (int j = 0; j < kWidePer; ++j) {
+                    if (!in[j]) continue;
+                    const uint32_t v = tag | (uint32_t)q[j];
+                    if (a[j] != eldest && v < xa[j]) atomicMin(&w.moe[a[j]], v);
+                    if (b[j] != eldest && v < xb[j]) atomicMin(&w.moe[b[j]], v);
+                }
+            }
+        }
+        // close the gaps: edge (j, thread) keeps its order among the segment's
+        __syncthreads();                             // the last segment's counts have been read
+        uint64_t vote[kWidePer];
+#pragma unroll
+        for (int j = 0; j < kWidePer; ++j) {
+            vote[j] = __ballot(in[j]);
+            if (lane == 0) s_cnt[j][wid] = __popcll(vote[j]);
+        }
+        __syncthreads();                             // (and every edge of the segment is in registers)
+        int before = 0;
+#pragma unroll
+        for (int j = 0; j < kWidePer; ++j) {
+#pragma unroll
+            for (int v = 0; v < kWideThreads / 64; ++v) {
+                if (v == wid && in[j]) {
+                    const int to = at + before + __popcll(vote[j] & ((1ull << lane) - 1ull));
+                    w.q[to] = q[j];
+                    w.a[to] = a[j];
+                    w.b[to] = b[j];
+                }
+                before += s_cnt[j][v];
+            }
+        }
+        if (tid == 0) {
+            w.size[sg] = before;
+            if (before > 0 && phase == 0 && round < kWideRounds) cnt[dual ? CNT_ROUNDST : CNT_ROUNDS0] = round + 1;
+        }
+    }
+}
+
+// What the wide rounds left of a forest, by one workgroup: if the nodes fit in LDS with their
+// ranks (kRestNodes), uf_lds goes on; else uf_body.
+__device__ __forceinline__ void uf_rest(uint8_t *__restrict__ ws, const Inst &I, int32_t *cnt, Forest &f, uint32_t *s_mem,
+                                        int *s_wsum, int *s_any) {
+    const WideForest w = wide_forest(ws, I, cnt, f.dual, f.m);
+    const int total = *w.total, nodes = *w.nodes;
+    f.rank = w.rank;
+    if (total == 0) return;
+    if (nodes <= kRestNodes) {
+        for (int x = threadIdx.x; x < nodes; x += kUfThreads) s_mem[x] = (uint32_t)w.left[x];
+        f.ea = w.ends;
+        // (the sequential finish's lists: the segments' arrays, free now)
+        uf_lds<kUfK, true>(f, total, nodes, cnt, s_mem + kRestNodes, s_mem, w.pos, s_wsum, s_any, w.q, w.a, w.b);
+        return;
+    }
+    // each edge's roots to its walk position, and on in the workspace
+    int32_t *A = w.ends, *B = w.pos;
+    for (int q = threadIdx.x; q < f.m; q += kUfThreads) A[q] = -1;
+    __syncthreads();
+    for (int at = 0; at < f.m; at += kWideSeg)
+        for (int e = threadIdx.x; e < w.size[at / kWideSeg]; e += kUfThreads) {
+            A[w.q[at + e]] = w.a[at + e];
+            B[w.q[at + e]] = w.b[at + e];
+        }
+    __syncthreads();
+    uf_body(f, cnt, w.par, (int32_t *)w.moe, w.q, A, B, s_wsum, true);
 }
 
 // Union-find passes, blockIdx.x = instance.  Stage 0: blockIdx.y = 0 H0 of every instance,
-// y = 1 (with the top dimension) the dual of the volumes; stage 1: the dual of the images.
+// y = 1 (with the top dimension) the dual of the volumes, and of the images too unless a stage 1
+// follows for them (staged).  Forests that fit take uf_lds with the fewest registers that hold
+// their edges; larger ones use the workspace for everything.  H0 and the dual of one instance
+// run side by side: the dual keeps its live edges in the free second live array and its roots
+// in the sort scratch (8 max(L, N) bytes).
 // wide: the call ran the wide rounds (k_uf_wide) before this launch.
-__global__ __launch_bounds__(kUfThreads) void k_unionfind(uint8_t *__restrict__ ws, int n, int stage, int htop, int wide) {
-    __shared__ __align__(8) int32_t s_lds[kUfLdsWords];
+__global__ __launch_bounds__(kUfThreads) void k_unionfind(uint8_t *__restrict__ ws, int n, int stage, int staged, int htop,
+                                                          int wide) {
+    __shared__ uint32_t s_mem[kUfLdsWords];         // uf_lds's nodes; uf_rest: their ranks before
+    static_assert(kUfLdsNodes <= kUfLdsWords && 2 * kRestNodes <= kUfLdsWords, "LDS carve");
     __shared__ int s_wsum[kUfThreads / 64];
-    const bool vol = ((const Inst *)ws)[blockIdx.x].ndim == 3;
-    if (stage == 0 && blockIdx.y == 0) uf_run<false>(ws, n, s_lds, s_wsum, wide != 0);
-    else if ((stage == 0 && htop && vol) || (stage == 1 && !vol)) uf_run<true>(ws, n, s_lds, s_wsum, wide != 0);
+    __shared__ int s_any[2];
+    const int i = blockIdx.x;
+    const Inst I = ((const Inst *)ws)[i];           // one batch of loads, before any atomic
+    const bool is2d = I.ndim == 2, dual = stage == 1 || blockIdx.y == 1;
+    if (dual && (!htop || (is2d && (stage == 1) != (staged != 0)) || (stage == 1 && !is2d))) return;
+    int32_t *cnt = (int32_t *)(ws + off_cnt(n)) + i * CNT_WORDS;
+    const int mE = cnt[CNT_E], mF = cnt[CNT_F], m0 = cnt[CNT_M0], mT = cnt[CNT_MT];
+    if (block_failed(cnt)) return;
+    Forest f;
+    f.dual = dual;
+    f.m = !dual || is2d ? mE : mF;
+    f.M = dual ? mT : m0;
+    if (f.M < 1 || f.M > (dual ? I.MTcap : I.M0cap) || f.m > (dual && !is2d ? I.F : I.E)) {
+        if (threadIdx.x == 0) set_err(cnt, PH_EINTERNAL);
+        return;
+    }
+    f.ea = arr<int32_t>(ws, pick(dual, I.o_ea, I.o_fa, 0, 0));
+    f.eb = arr<int32_t>(ws, pick(dual, I.o_eb, I.o_fb, 0, 0));
+    f.rank = nullptr;
+    f.death0 = arr<int32_t>(ws, I.o_death0);
+    f.killer = arr<int32_t>(ws, I.o_killer);
+    f.neg0 = arr<int32_t>(ws, I.o_neg0);
+    const int64_t L = I.E > I.F ? I.E : I.F;
+    int32_t *live = arr<int32_t>(ws, pick(dual, I.o_live, I.o_live2, 0, 0));
+    int32_t *A = arr<int32_t>(ws, pick(dual, I.o_ra, I.o_scratch, 0, 0));
+    int32_t *B = arr<int32_t>(ws, pick(dual, I.o_rb, I.o_scratch + 4 * L, 0, 0));
+    if (wide && uf_is_wide(I, f.M, f.m)) {
+        uf_rest(ws, I, cnt, f, s_mem, s_wsum, s_any);
+        return;
+    }
+    if (f.M <= kUfLdsNodes && f.m <= 4 * kUfThreads) {
+        uf_lds<4, false>(f, f.m, f.M, cnt, s_mem, nullptr, nullptr, s_wsum, s_any, live, A, B);
+        return;
+    }
+    if (f.M <= kUfLdsNodes && f.m <= kUfLdsEdges) {
+        uf_lds<kUfK, false>(f, f.m, f.M, cnt, s_mem, nullptr, nullptr, s_wsum, s_any, live, A, B);
+        return;
+    }
+    uf_body(f, cnt, arr<int32_t>(ws, pick(dual, I.o_uf0, I.o_ufT, 0, 0)),
+            arr<int32_t>(ws, pick(dual, I.o_moe0, I.o_moeT, 0, 0)), live, A, B, s_wsum, false);
 }
 
 // ======================================================================= 3D H1 ====
@@ -2623,8 +3072,12 @@ __device__ __forceinline__ int64_t cell_index(const Inst &I, int64_t v, int code
 // kUfThreads list entries of each section into the live-edge array (free once the union-finds
 // are done), k_output_scan turns the counts into each chunk's first position and the section
 // totals (CNT_OSEC0, CNT_OSECT), and mode 2 (the same grid) writes every chunk's pairs there.
-// Mode 0 (grid n) writes the other instances' pairs as one workgroup and, for the wide ones,
-// only their count and status.
+// Mode 0 (grid (n, parts)) writes the other instances' pairs and, for the wide ones, only their
+// count and status.  Each of its workgroups writes a part of every section, at least kUfThreads
+// list entries, and finds its first positions by counting the pairs of the whole lists itself:
+// that is a few loads a thread, all in flight together, where one workgroup writing everything
+// waits for a chain of dependent loads and two barriers every kUfThreads entries (20k and 31k
+// entries, 316^2 noise: 159 -> 41 us).
 __device__ __forceinline__ bool out_is_wide(const Inst &I, uint32_t flags) {
     return (flags & PH_WIDE) && I.N >= kWideVoxels && !I.h1;
 }
@@ -2634,7 +3087,8 @@ __global__ __launch_bounds__(kUfThreads) void k_output(const void *__restrict__ 
                                                       ph_pairs out, int64_t *__restrict__ d_counts,
                                                       int32_t *__restrict__ d_status, int mode) {
     __shared__ int s_wsum[kUfThreads / 64];
-    const int i = mode == 0 ? blockIdx.x : blockIdx.y;
+    __shared__ int s_cnt[kUfThreads / 64][6];
+    const int i = mode == 0 ? blockIdx.x : blockIdx.y, part = mode == 0 ? blockIdx.y : 0;
     const Inst I = ((const Inst *)ws)[i];           // one batch of loads, before any atomic
     int32_t *cnt = (int32_t *)(ws + off_cnt(n)) + i * CNT_WORDS;
     const bool wide = out_is_wide(I, flags);
@@ -2646,7 +3100,6 @@ __global__ __launch_bounds__(kUfThreads) void k_output(const void *__restrict__ 
         if (flags & PH_IN_U16) return (float)((const uint16_t *)imgs)[q];
         return ((const float *)imgs)[q];
     };
-    const int32_t *par0 = arr<int32_t>(ws, I.o_par0);
     const int32_t *death0 = arr<int32_t>(ws, I.o_death0);
     const int32_t *killer = arr<int32_t>(ws, I.o_killer);
     const uint64_t *keyE = arr<uint64_t>(ws, I.o_keyE);
@@ -2657,14 +3110,20 @@ __global__ __launch_bounds__(kUfThreads) void k_output(const void *__restrict__ 
     const int M0 = cnt[CNT_M0], MT = cnt[CNT_MT], mE = cnt[CNT_E];
     const int mf = is2d ? cnt[CNT_E] : cnt[CNT_F];
     const int64_t cap = I.out_cap, o = I.out_off;
-    int64_t P = 0;
     if (block_failed(cnt)) {
-        if (threadIdx.x == 0 && mode == 0) { d_counts[i] = 0; d_status[i] = cnt[CNT_ERR]; }
+        if (threadIdx.x == 0 && mode == 0 && part == 0) { d_counts[i] = 0; d_status[i] = cnt[CNT_ERR]; }
         return;
     }
-    // chunks of kUfThreads entries: this block's first and step (mode 0: all, in order);
-    // wide: per-chunk counts, then first positions, H0 section first (ch0), then the top's (chT)
+    // chunks of kUfThreads entries: this block's first and step, and (mode 0) the number of each
+    // list's chunks a part takes; wide: per-chunk counts, then first positions, H0 section
+    // first (ch0), then the top's (chT)
     const int c_first = mode == 0 ? 0 : blockIdx.x, c_step = mode == 0 ? 1 : gridDim.x;
+    const int longest = M0 > mE ? (M0 > mf ? M0 : mf) : (mE > mf ? mE : mf), parts = mode == 0 ? gridDim.y : 1;
+    const int chunks = (longest + kUfThreads - 1) / kUfThreads, share = (chunks + parts - 1) / parts * kUfThreads;
+    const int e_first = mode == 0 ? part * share : 0;      // this part's entries of every list
+    const int e_end = mode == 0 ? e_first + share : 0x7FFFFFFF;
+    if (mode == 0 && !wide && part > 0 && e_first >= longest) return;
+    if (mode == 0 && wide && part > 0) return;
     int32_t *ch0 = arr<int32_t>(ws, I.o_live);
     int32_t *chT = ch0 + (M0 + kUfThreads - 1) / kUfThreads;
     // a pixel index and a cell code read back from a key must name a cell of this instance
@@ -2707,24 +3166,22 @@ __global__ __launch_bounds__(kUfThreads) void k_output(const void *__restrict__ 
     };
     const float kInf = __int_as_float(0x7f800000);
     // A section's k-th pair (in the order of its list) goes to start + k, or, with rev >= 0
-    // pairs in the section, to start + rev - 1 - k.  With write false the section only counts.
+    // pairs in the section, to start + rev - 1 - k; k0: its pairs before this part.
     auto place = [](int64_t start, int64_t rev, int64_t k) { return rev >= 0 ? start + rev - 1 - k : start + k; };
 
     // H0 pairs of the V complex, by birth key (under the T-filtration: its top pairs)
-    auto sec_h0 = [&](bool write, int64_t start, int64_t rev) -> int64_t {
-        int64_t Q = 0;
-        for (int base = c_first * blockDim.x; base < M0; base += c_step * blockDim.x) {
+    auto sec_h0 = [&](int64_t start, int64_t rev, int64_t k0) {
+        int64_t Q = k0;
+        for (int base = e_first + c_first * blockDim.x; base < M0 && base < e_end; base += c_step * blockDim.x) {
             const int j = base + threadIdx.x;
             int flag = 0;
             uint64_t nk = 0, ek = 0;
             int d = -1;
             if (j < M0) {
-                nk = n0s[j];
-                const int32_t pv = key_ok(nk, 0, 0) ? par0[key_pix(nk)] : 0;
-                const int id = -(pv + 1);
-                if (pv >= 0 || id >= M0) { set_err(cnt, PH_EINTERNAL); }
+                nk = n0s[j];                             // node j
+                if (!key_ok(nk, 0, 0)) { set_err(cnt, PH_EINTERNAL); }
                 else {
-                    d = death0[id];
+                    d = death0[j];
                     if (d < 0) flag = !tf;                    // essential (the frame's, under T)
                     else if (d >= mE || !key_ok(ek = keyE[d], 1, 6)) set_err(cnt, PH_EINTERNAL);
                     else flag = key_ord(ek) != key_ord(nk);
@@ -2737,7 +3194,7 @@ __global__ __launch_bounds__(kUfThreads) void k_output(const void *__restrict__ 
                 continue;
             }
             if (mode == 2) Q = ch0[base / blockDim.x];
-            if (flag && write) {
+            if (flag) {
                 const int32_t bp = (int32_t)key_pix(nk);
                 const int64_t at = place(start, rev, Q + pos);
                 if (d < 0) put(at, 0, img(bp), kInf, cell_index(I, bp, 0), bp, -1, -1);
@@ -2753,13 +3210,12 @@ __global__ __launch_bounds__(kUfThreads) void k_output(const void *__restrict__ 
             }
             Q += tot;
         }
-        return Q;
     };
     // top-dimension pairs of the V complex, by birth key (under the T-filtration: its H0
     // pairs; the one born on the frame is the essential class)
-    auto sec_top = [&](bool write, int64_t start, int64_t rev) -> int64_t {
-        int64_t Q = 0;
-        for (int base = c_first * blockDim.x; base < mf; base += c_step * blockDim.x) {
+    auto sec_top = [&](int64_t start, int64_t rev, int64_t k0) {
+        int64_t Q = k0;
+        for (int base = e_first + c_first * blockDim.x; base < mf && base < e_end; base += c_step * blockDim.x) {
             const int r = base + threadIdx.x;
             int flag = 0;
             uint64_t fk = 0, tk = 0;
@@ -2781,7 +3237,7 @@ __global__ __launch_bounds__(kUfThreads) void k_output(const void *__restrict__ 
                 continue;
             }
             if (mode == 2) Q = chT[base / blockDim.x];
-            if (flag && write) {
+            if (flag) {
                 const int32_t bp = (int32_t)key_pix(fk), dp = (int32_t)key_pix(tk);
                 const int64_t at = place(start, rev, Q + pos);
                 if (!tf) {
@@ -2801,16 +3257,15 @@ __global__ __launch_bounds__(kUfThreads) void k_output(const void *__restrict__ 
             }
             Q += tot;
         }
-        return Q;
     };
 
     // H1 pairs of a volume (KEEP edge r paired with column piv[r]), by birth key (under the
     // T-filtration: its H1 pairs, the dual of each, by death key)
     const bool h1 = I.h1 && vol;
     const int32_t *piv = h1 ? arr<int32_t>(ws, I.o_piv) : nullptr;
-    auto sec_h1 = [&](bool write, int64_t start, int64_t rev) -> int64_t {
-        int64_t Q = 0;
-        for (int base = 0; base < mE; base += blockDim.x) {
+    auto sec_h1 = [&](int64_t start, int64_t rev, int64_t k0) {
+        int64_t Q = k0;
+        for (int base = e_first; base < mE && base < e_end; base += blockDim.x) {
             const int r = base + threadIdx.x;
             int flag = 0;
             uint64_t ek = 0, sk = 0;
@@ -2826,7 +3281,7 @@ __global__ __launch_bounds__(kUfThreads) void k_output(const void *__restrict__ 
             }
             int tot;
             const int pos = block_flag_scan(flag, s_wsum, &tot);
-            if (flag && write) {
+            if (flag) {
                 const int32_t bp = (int32_t)key_pix(ek), dp = (int32_t)key_pix(sk);
                 const int64_t at = place(start, rev, Q + pos);
                 if (!tf) {
@@ -2840,54 +3295,96 @@ __global__ __launch_bounds__(kUfThreads) void k_output(const void *__restrict__ 
             }
             Q += tot;
         }
-        return Q;
     };
 
-    if (wide) {
-        // section sizes from k_output_scan (mode 1 counts; mode 0 only reports)
+    if (mode != 0) {
+        // wide: section sizes from k_output_scan (mode 1 only counts)
         const int64_t nh0 = cnt[CNT_OSEC0], ntop = cnt[CNT_OSECT];
-        if (mode == 1) {
-            if (flags & (tf ? PH_HTOP : PH_H0)) sec_h0(false, 0, -1);
-            if (flags & (tf ? PH_H0 : PH_HTOP)) sec_top(false, 0, -1);
-            return;
+        if (!tf) {
+            if (flags & PH_H0) sec_h0(0, -1, 0);
+            if (flags & PH_HTOP) sec_top((flags & PH_H0) ? nh0 : 0, -1, 0);
+        } else {
+            const int64_t c0 = (flags & PH_H0) ? ntop : 0;
+            if (flags & PH_H0) sec_top(0, c0, 0);
+            if (flags & PH_HTOP) sec_h0(c0, nh0, 0);
+        }
+        return;
+    }
+    // pairs of the H0 list, the top list and the H1 list: all, and those before this part
+    const bool use0 = (flags & (tf ? PH_HTOP : PH_H0)) != 0, useT = (flags & (tf ? PH_H0 : PH_HTOP)) != 0;
+    int64_t all[3] = {0, 0, 0}, pre[3] = {0, 0, 0};
+    if (wide) {
+        all[0] = use0 ? cnt[CNT_OSEC0] : 0;
+        all[1] = useT ? cnt[CNT_OSECT] : 0;
+    } else {
+        int c[3] = {0, 0, 0}, p[3] = {0, 0, 0};
+        // (an entry without a partner reads the partner list's first key; an empty one has none)
+        const uint64_t *kE = mE > 0 ? keyE : n0s, *kF = mf > 0 ? fkey : keyE;
+        if (use0) {
+#pragma unroll 4
+            for (int j = threadIdx.x; j < M0; j += kUfThreads) {
+                const int d = death0[j];
+                const uint32_t eo = key_ord(kE[d < 0 || d >= mE ? 0 : d]), no = key_ord(n0s[j]);
+                const int on = d < 0 ? (tf ? 0 : 1) : (eo != no ? 1 : 0);
+                c[0] += on;
+                p[0] += j < e_first ? on : 0;
+            }
+        }
+        if (useT) {
+#pragma unroll 4
+            for (int r = threadIdx.x; r < mf; r += kUfThreads) {
+                const int x = killer[r];
+                const uint32_t to = key_ord(nTkey[x < 1 || x >= MT ? 0 : x]), fo = key_ord(fkey[r]);
+                const int on = x > 0 && to != fo ? 1 : 0;
+                c[1] += on;
+                p[1] += r < e_first ? on : 0;
+            }
+        }
+        if (h1) {
+#pragma unroll 4
+            for (int r = threadIdx.x; r < mE; r += kUfThreads) {
+                const int j = piv[r];
+                const uint32_t so = key_ord(kF[j < 0 || j >= mf ? 0 : j]), eo = key_ord(keyE[r]);
+                const int on = j >= 0 && so != eo ? 1 : 0;
+                c[2] += on;
+                p[2] += r < e_first ? on : 0;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int cw = (int)wave_incl_sum((uint32_t)c[k]), pw = (int)wave_incl_sum((uint32_t)p[k]);
+            if (__lane_id() == 63) {
+                s_cnt[threadIdx.x >> 6][k] = cw;
+                s_cnt[threadIdx.x >> 6][3 + k] = pw;
+            }
+        }
+        __syncthreads();
+        for (int v = 0; v < kUfThreads / 64; ++v) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                all[k] += s_cnt[v][k];
+                pre[k] += s_cnt[v][3 + k];
+            }
         }
         if (!tf) {
-            const int64_t a0 = (flags & PH_H0) ? nh0 : 0;
-            if (mode == 2) {
-                if (flags & PH_H0) sec_h0(true, 0, -1);
-                if (flags & PH_HTOP) sec_top(true, a0, -1);
-                return;
-            }
-            P = a0 + ((flags & PH_HTOP) ? ntop : 0);
+            if (use0) sec_h0(0, -1, pre[0]);
+            if (h1) sec_h1(all[0], -1, pre[2]);
+            if (useT) sec_top(all[0] + all[2], -1, pre[1]);
         } else {
-            const int64_t c0 = (flags & PH_H0) ? ntop : 0, ct = (flags & PH_HTOP) ? nh0 : 0;
-            if (mode == 2) {
-                if (flags & PH_H0) sec_top(true, 0, c0);
-                if (flags & PH_HTOP) sec_h0(true, c0, ct);
-                return;
-            }
-            P = c0 + ct;
+            // T order: by dimension, then by death key, so each section is written backwards
+            if (useT) sec_top(0, all[1], pre[1]);
+            if (h1) sec_h1(all[1], all[2], pre[2]);
+            if (use0) sec_h0(all[1] + all[2], all[0], pre[0]);
         }
-    } else if (!tf) {
-        if (flags & PH_H0) P += sec_h0(true, P, -1);
-        if (h1) P += sec_h1(true, P, -1);
-        if (flags & PH_HTOP) P += sec_top(true, P, -1);
-    } else {
-        // T order: by dimension, then by death key, so each section is written backwards
-        const int64_t c0 = (flags & PH_H0) ? sec_top(false, 0, -1) : 0;
-        const int64_t c1 = h1 ? sec_h1(false, 0, -1) : 0;
-        const int64_t ct = (flags & PH_HTOP) ? sec_h0(false, 0, -1) : 0;
-        if (flags & PH_H0) sec_top(true, 0, c0);
-        if (h1) sec_h1(true, c0, c1);
-        if (flags & PH_HTOP) sec_h0(true, c0 + c1, ct);
-        P = c0 + c1 + ct;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        d_counts[i] = P;
-        int st = __hip_atomic_load(&cnt[CNT_ERR], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (st == 0 && P > cap) st = PH_ECAPACITY;
-        d_status[i] = st;
+        // (d_status is PH_OK from k_plan on; an error any part found outweighs the capacity)
+        const int64_t P = all[0] + all[1] + all[2];
+        if (part == 0) d_counts[i] = P;
+        const int st = __hip_atomic_load(&cnt[CNT_ERR], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (st != 0) __hip_atomic_store(&d_status[i], st, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else if (part == 0 && P > cap) atomicCAS(&d_status[i], 0, (int32_t)PH_ECAPACITY);
     }
 }
 
@@ -3017,8 +3514,7 @@ int check_kernels(int dev, char *report, size_t len) {
         {"k_resolve", (const void *)k_resolve, 256},
         {"k_unionfind", (const void *)k_unionfind, kUfThreads},
         {"k_uf_wide", (const void *)k_uf_wide, kWideThreads},
-        {"k_sort_runs", (const void *)k_sort_runs, kSortThreads},
-        {"k_sort_merge", (const void *)k_sort_merge, kSortThreads},
+        {"k_sort_merge", (const void *)k_sort_merge, kMergeThreads},
         {"k_output_scan", (const void *)k_output_scan, kUfThreads},
         {"k_output", (const void *)k_output, kUfThreads},
         {"k_zero", (const void *)k_zero, 256},
@@ -3204,12 +3700,12 @@ bool tuned_for(const ph_shape *h, int n, ph_tuning *t) {
 // stream is being captured into a graph).
 enum KernelId {
     K_PLAN, K_CLASSIFY2D, K_CLASSIFY3D, K_SORT, K_RESOLVE, K_UF, K_RESOLVE_2D, K_UF_2D, K_H1MORSE, K_H1MORSE2, K_H1REDUCE,
-    K_OUTPUT, K_ZERO, K_SCATTER, K_UFWIDE, K_UFWIDE_2D, K_SORTWIDE, K_OUTWIDE, K_COUNT
+    K_OUTPUT, K_ZERO, K_SCATTER, K_UFWIDE, K_UFWIDE_2D, K_SORTMERGE, K_OUTWIDE, K_COUNT
 };
 const char *const kKernelNames[K_COUNT] = {
     "k_plan", "k_classify2d", "k_classify3d", "k_sort", "k_resolve", "k_unionfind",
     "k_resolve(2d top)", "k_unionfind(2d top)", "k_h1_morse", "k_h1_morse(large)", "k_h1_reduce", "k_output", "k_zero", "k_scatter",
-    "k_uf_wide", "k_uf_wide(2d top)", "k_sort_wide", "k_output_wide"};
+    "k_uf_wide", "k_uf_wide(2d top)", "k_sort_merge", "k_output_wide"};
 
 struct ProfRec { int kid; hipEvent_t a, b; };
 std::mutex g_prof_mu;
@@ -3353,44 +3849,54 @@ int run(int n, const void *d_imgs, const int64_t *d_img_off, const ph_shape *d_s
         else if (tile3 == 2) FC_LAUNCH(K_CLASSIFY3D, launch3d<8, 8, 16>(t3, cimgs, ws, n, lut, st, d_grad));
         else FC_LAUNCH(K_CLASSIFY3D, launch3d<16, 8, 8>(t3, cimgs, ws, n, lut, st, d_grad));
     }
-    // resolve grid: the lists are a small share of the voxels for any field that is not noise,
-    // so 256 threads per 64Ki voxels of the largest instance; the loops stride over the rest
-    int64_t rb = (mv + 65535) / 65536;
-    if (rb > (ml + 255) / 256) rb = (ml + 255) / 256;
-    if ((flags & PH_WIDE) && mv >= kWideVoxels) rb = (mv + 4095) / 4096;   // noise: lists of a sixth of the pixels
-    const unsigned rblocks = (unsigned)(rb < 1 ? 1 : (rb > 1024 ? 1024 : rb));
+    // resolve grid: a thread an entry, up to 512 workgroups over the instances (for any field
+    // that is not noise the lists are a small share of their bound, so most return at once), or
+    // one per 64Ki voxels
+    const unsigned rblocks = (unsigned)std::min<int64_t>((ml + 255) / 256, std::max<int64_t>((mv + 65535) / 65536, 512 / n + 1));
     // PH_WIDE: the union-finds and the long lists of instances of kWideVoxels or more voxels
     // are spread over the whole GPU (each instance's kernels decide for themselves, from its
     // counts)
     const int wide = (flags & PH_WIDE) && mv >= kWideVoxels ? 1 : 0;
-    FC_LAUNCH(K_SORT, hipLaunchKernelGGL(k_sort_lists, dim3(n, 3), dim3(kSortThreads), 0, st, ws, n, wide));
-    if (wide) {
-        int64_t runs = (ml + kSortCap - 1) / kSortCap;
-        const unsigned sb = (unsigned)std::min<int64_t>(512, runs);   // workgroups per list: runs, then tiles
-        FC_LAUNCH(K_SORTWIDE, hipLaunchKernelGGL(k_sort_runs, dim3(sb, n, 3), dim3(kSortThreads), 0, st, ws, n));
-        int passes = 0;
-        while (((int64_t)kSortCap << passes) < ml) ++passes;
-        for (int p = 0; p <= passes; ++p)         // the last one only copies back
-            FC_LAUNCH(K_SORTWIDE, hipLaunchKernelGGL(k_sort_merge, dim3(sb, n, 3), dim3(kSortThreads), 0, st, ws, n, p));
+    // Long lists: a workgroup per run and one merge launch (two under PH_WIDE, for hundreds of
+    // runs).  A list of 8193 keys or more needs about 2^15 voxels even of noise (0.33 KEEP edges
+    // a pixel); below 2^16 voxels, and in batches that fill the chip with a workgroup a list,
+    // the one workgroup merges its two or three runs itself, which saves the launch.
+    const bool multi = mv >= kSortMultiVoxels && n <= kSortMultiInstances;
+    const int passes = !multi ? 0 : (wide ? 2 : 1);
+    const int rl = multi ? kSortRun : kSortCap;
+    const int64_t runs = (ml + rl - 1) / rl;
+    const unsigned sr = multi ? (unsigned)std::min<int64_t>(runs, std::max<int64_t>(1, 256 / n)) : 1u;
+    FC_LAUNCH(K_SORT, hipLaunchKernelGGL(k_sort_lists, dim3(sr, n, 4), dim3(kSortThreads), 0, st, ws, n, rl, passes));
+    for (int p = 0; p < passes; ++p) {
+        const unsigned mb = (unsigned)std::min<int64_t>((ml + kMergeThreads - 1) / kMergeThreads, std::max<int64_t>(16, 256 / n));
+        FC_LAUNCH(K_SORTMERGE, hipLaunchKernelGGL(k_sort_merge, dim3(mb, n, 4), dim3(kMergeThreads), 0, st, ws, n, rl, passes, p));
     }
     // volumes: the dual (resolve, union-find) beside H0; images: the dual after H0
     // T's H0 is the V top; 3D H1 needs the squares the dual union-find pairs
     const int htop = (tf || (flags & PH_HTOP) || (h1 && any3)) ? 1 : 0;
-    const unsigned side = htop && any3 ? 2 : 1;
-    FC_LAUNCH(K_RESOLVE, hipLaunchKernelGGL(k_resolve, dim3(rblocks, n, side), dim3(256), 0, st, ws, n, 0, htop));
+    // Few instances leave most of the chip idle: the images' dual then runs beside H0 as well, on
+    // all their KEEP edges, which saves two launches one after another; in larger batches it
+    // follows on the edges H0 left, a third of them.
+    const int staged = any2 && n > kSideBySideInstances ? 1 : 0;
+    const unsigned side = htop && (any3 || !staged) ? 2 : 1;
+    FC_LAUNCH(K_RESOLVE, hipLaunchKernelGGL(k_resolve, dim3(rblocks, n, side), dim3(256), 0, st, ws, n, 0, staged, htop, wide));
     auto wide_rounds = [&](int stage, unsigned sides, int kid) -> int {
-        for (int ph = -1, r = 0; r < kWideRounds; ph == 1 ? (ph = 0, ++r) : ++ph) {
-            FC_LAUNCH(kid, hipLaunchKernelGGL(k_uf_wide, dim3(kWideBlocks, n, sides), dim3(kWideThreads), 0, st, ws, n,
-                                              stage, htop, ph, r));
+        const unsigned wb = (unsigned)std::min<int64_t>((ml + kWideSeg - 1) / kWideSeg, std::max(1, kWideBlocks / n));
+        // the set-up, the rounds' two phases each, phase 0 once more (the last round's fired edges
+        // dropped, new roots), the nodes left numbered and the segments closed up
+        for (int k = -1; k <= 2 * kWideRounds + 2; ++k) {
+            const int ph = k < 0 ? -1 : (k > 2 * kWideRounds ? k - 2 * kWideRounds + 1 : k & 1);
+            FC_LAUNCH(kid, hipLaunchKernelGGL(k_uf_wide, dim3(wb, n, sides), dim3(kWideThreads), 0, st, ws, n, stage, staged,
+                                              htop, ph, k / 2));
         }
         return PH_OK;
     };
     if (wide && wide_rounds(0, side, K_UFWIDE) != PH_OK) return PH_EHIP;
-    FC_LAUNCH(K_UF, hipLaunchKernelGGL(k_unionfind, dim3(n, side), dim3(kUfThreads), 0, st, ws, n, 0, htop, wide));
-    if (htop && any2) {
-        FC_LAUNCH(K_RESOLVE_2D, hipLaunchKernelGGL(k_resolve, dim3(rblocks, n), dim3(256), 0, st, ws, n, 1, htop));
+    FC_LAUNCH(K_UF, hipLaunchKernelGGL(k_unionfind, dim3(n, side), dim3(kUfThreads), 0, st, ws, n, 0, staged, htop, wide));
+    if (htop && staged) {
+        FC_LAUNCH(K_RESOLVE_2D, hipLaunchKernelGGL(k_resolve, dim3(rblocks, n), dim3(256), 0, st, ws, n, 1, staged, htop, wide));
         if (wide && wide_rounds(1, 1, K_UFWIDE_2D) != PH_OK) return PH_EHIP;
-        FC_LAUNCH(K_UF_2D, hipLaunchKernelGGL(k_unionfind, dim3(n), dim3(kUfThreads), 0, st, ws, n, 1, htop, wide));
+        FC_LAUNCH(K_UF_2D, hipLaunchKernelGGL(k_unionfind, dim3(n), dim3(kUfThreads), 0, st, ws, n, 1, staged, htop, wide));
     }
     if (h1 && any3) {
         // one 64-thread workgroup per 512 voxels of the largest volume (at most 8192 per
@@ -3417,7 +3923,8 @@ int run(int n, const void *d_imgs, const int64_t *d_img_off, const ph_shape *d_s
         FC_LAUNCH(K_OUTWIDE, hipLaunchKernelGGL(k_output, dim3(kWideBlocks / 4, n), dim3(kUfThreads), 0, st, d_imgs, ws, n,
                                                 flags, out, d_counts, d_status, 2));
     }
-    FC_LAUNCH(K_OUTPUT, hipLaunchKernelGGL(k_output, dim3(n), dim3(kUfThreads), 0, st, d_imgs, ws, n, flags, out, d_counts,
+    const unsigned parts = (unsigned)std::max<int64_t>(1, std::min<int64_t>(kOutParts / n, (mv + 65535) / 65536 * 16));
+    FC_LAUNCH(K_OUTPUT, hipLaunchKernelGGL(k_output, dim3(n, parts), dim3(kUfThreads), 0, st, d_imgs, ws, n, flags, out, d_counts,
                                  d_status, 0));
     return PH_OK;
 }

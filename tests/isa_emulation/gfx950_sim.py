@@ -622,7 +622,7 @@ def _scc_nz(w, x):
 
 def _compile_salu(op, O, mods, nxt):
     if op.startswith("s_load_dword"):
-        n = {"s_load_dword": 1, "s_load_dwordx2": 2, "s_load_dwordx4": 4, "s_load_dwordx8": 8}[op]
+        n = {"s_load_dword": 1, "s_load_dwordx2": 2, "s_load_dwordx4": 4, "s_load_dwordx8": 8, "s_load_dwordx16": 16}[op]
         d, base = O[0], rs64(O[1])
         offr = rs(O[2]) if len(O) > 2 else (lambda w: 0)
         di = d.idx
@@ -735,11 +735,26 @@ def _compile_salu(op, O, mods, nxt):
                 return nxt
             return f
         return lambda w: (d(w, _scc_nz(w, bin(a(w)).count("1"))), nxt)[1]
+    if op in ("s_bitset0_b32", "s_bitset1_b32"):        # one bit of D cleared or set; SCC unchanged
+        set1, a, di = op == "s_bitset1_b32", rs(O[1]), O[0].idx
+
+        def f(w):
+            bit = 1 << (a(w) & 31)
+            d(w, (w.s[di] | bit) if set1 else (w.s[di] & ~bit & M32))
+            return nxt
+        return f
     if len(O) < 3:
         raise Unsupported(op)
     a, b = O[1], O[2]
-    if op in ("s_lshl_b64", "s_lshr_b64"):
+    if op in ("s_lshl_b64", "s_lshr_b64", "s_ashr_i64"):
         ra, rb = rs64(a), rs(b)
+        if op == "s_ashr_i64":
+            def f(w):
+                x = ra(w)
+                x = x - (1 << 64) if x >= 1 << 63 else x
+                d(w, _scc_nz(w, (x >> (rb(w) & 63)) & M64))
+                return nxt
+            return f
         if op == "s_lshl_b64":
             return lambda w: (d(w, _scc_nz(w, (ra(w) << (rb(w) & 63)) & M64)), nxt)[1]
         return lambda w: (d(w, _scc_nz(w, ra(w) >> (rb(w) & 63))), nxt)[1]
@@ -988,6 +1003,14 @@ def _compile_valu(op, O, mods, nxt):
         d, a, b, c = wv(O[0]), r32(O[1]), r32(O[2]), r32(O[3])
         fn = _bitop3(int(mods["bitop3"], 0))
         return lambda w: (d(w, fn(a(w), b(w), c(w))), nxt)[1]
+    if op == "v_fmamk_f32":                          # D = S0 * K + S1
+        d, a, k, b = wv(O[0]), r32(O[1]), r32(O[2]), r32(O[3])
+
+        def f(w):
+            x = f32(a(w)).astype(np.longdouble) * f32(k(w)).astype(np.longdouble) + f32(b(w)).astype(np.longdouble)
+            d(w, bits(x.astype(F32)))
+            return nxt
+        return f
     if op == "v_fmac_f32":
         d, a, b = wv(O[0]), r32(O[1]), r32(O[2])
         di = O[0].idx

@@ -1,0 +1,79 @@
+"""The list passes at the sizes where they change form: one sort run, several runs in one
+workgroup, runs merged by many workgroups (2^16 voxels and more, up to 32 instances), one and
+several union-find batches with and without the sequential finish, one and several output
+workgroups, the images' dual beside H0 or after it (more than 64 instances).  Bit for bit against
+the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import synthetic as S
+from gpu_util import diff_pairs
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+import paper_2606_04801_amd as fc  # noqa: E402
+
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+DEV = torch.device("cuda:0")
+
+
+def staircase(n):
+    """Every merge waits for the previous one: the rounds run out in every batch."""
+    a = np.zeros(2 * n + 1, np.float32)
+    a[0::2] = np.linspace(0.5, 0.1, n + 1).astype(np.float32)
+    a[1::2] = np.linspace(1.0, 2.0, n).astype(np.float32)
+    return a.reshape(1, -1)
+
+
+# noise keeps about 0.31 edges, 0.2 minima a pixel; 0.33 edges, 0.2 squares a voxel
+CASES = {
+    "one_run_2k": lambda: S.uniform((81, 81), 1),                # 2,048 edges a run of two keys a thread
+    "one_run_4k": lambda: S.uniform((114, 115), 2),              # about 4,096 edges
+    "two_runs_in_place": lambda: S.uniform((117, 118), 3),
+    "below_multi": lambda: S.uniform((255, 256), 4),             # 65,280 pixels: one workgroup a list
+    "multi": lambda: S.uniform((256, 256), 5),
+    "multi_ties": lambda: S.levels((256, 257), 7, 6),
+    "multi_volume": lambda: S.uniform((40, 41, 41), 7),
+    "strip": lambda: S.levels((1, 70000), 40, 8),
+    "staircase_two_batches": lambda: staircase(9000),
+    "seventeen_runs": lambda: S.uniform((340, 341), 9),          # 36k edges: five union-find batches
+}
+
+
+@pytest.mark.parametrize("filtration", ["V", "T"])
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_single(name, filtration):
+    img = CASES[name]()
+    print("case", name, img.shape, filtration, flush=True)
+    got = fc.ph_diagram(torch.from_numpy(img).to(DEV), filtration=filtration).numpy()
+    assert diff_pairs(got, oracle.diagram(img, filtration=filtration)) is None
+
+
+@pytest.mark.parametrize("n", [32, 33, 64, 65])
+def test_batches(n):
+    """A multi-run image beside small instances, at both sides of the batch limits."""
+    imgs = [S.uniform((256, 256), 20), S.uniform((24, 20, 22), 21)]
+    imgs += [S.levels((17 + k % 5, 23), 9, 30 + k) for k in range(n - 2)]
+    bt = fc.Batch([a.shape for a in imgs], device=DEV)
+    bt.set_images([torch.from_numpy(a) for a in imgs])
+    print("batch of", n, flush=True)
+    bt.ph_diagram_batch()
+    for a, got in zip(imgs, bt.results()):
+        assert diff_pairs(got, oracle.diagram(a)) is None, a.shape
+
+
+def test_multi_run_volume_with_h1():
+    """Each vertex's first KEEP edge is found across runs (3D H1 looks its edges up by it)."""
+    img = S.uniform((41, 40, 42), 40)
+    fl = fc.PH_H0 | fc.PH_HTOP | fc.PH_H1
+    print("h1", img.shape, flush=True)
+    got = fc.ph_diagram(torch.from_numpy(img).to(DEV), flags=fl).numpy()
+    want = oracle.diagram(img, dims=(0, 2))
+    assert diff_pairs(got[got["dim"] != 1], want) is None
+    small = S.levels((20, 60, 60), 6, 41)                        # 72,000 voxels, ties across runs
+    got = fc.ph_diagram(torch.from_numpy(small).to(DEV), flags=fl).numpy()
+    assert diff_pairs(got[got["dim"] != 1], oracle.diagram(small, dims=(0, 2))) is None
+    assert (got["dim"] == 1).any()
