@@ -162,7 +162,8 @@ enum {
     CNT_WLEFT0, CNT_WLEFTT,
     CNT_OSEC0 = 148, CNT_OSECT,          // wide output: pairs of the H0 and the top-dimension lists
     CNT_WNODES0, CNT_WNODEST,            // wide union-find: the nodes the rounds left
-    CNT_H1POOL = 160, CNT_WORDS = 192
+    CNT_H1POOL = 160, CNT_H1NEXT = 168, CNT_H1NEXT2,   // pool entries; columns taken in the two passes
+    CNT_WORDS = 192
 };
 // pool entries per KEEP-square slot of an H1 volume: room for the Morse boundaries of the
 // columns (a few entries each) and the reduced forms of the columns that need reduction

@@ -2477,8 +2477,12 @@ __global__ __launch_bounds__(kUfThreads) void k_unionfind(uint8_t *__restrict__ 
 //
 // One single-wave workgroup per column at a time, 64 queued entries per step; the column is an
 // F2 set of edge keys in an open-addressing table in LDS (toggling a key is adding the edge).
-constexpr int kH1Slots = 1024;             // table slots (and queue entries) of the first pass
+// Bound by instruction issue (vector and scalar alike, half each) and the steps' dependent reads:
+// more workgroups a compute unit (smaller tables) gain 4 %, several columns a workgroup lose 25 %.
+constexpr int kH1Slots = 1024;             // table slots of the first pass
 constexpr int kH1BigSlots = 4096;          // the same for the columns the first pass could not hold
+constexpr int kH1Groups = 4096;            // workgroups of the first pass, over all instances (18 a compute unit run)
+constexpr int kH1PerVolume = 512;          // ... and of one instance: about what one XCD runs at once
 constexpr int kH1MaxBoundary = 64;         // entries of one column's boundary in critical cells
 constexpr int kH1MaxChunks = 1 << 20;
 // A column holds edges by their id, pixel << 5 | code (the low 32 bits of the edge key: the
@@ -2495,45 +2499,48 @@ __device__ __forceinline__ uint32_t h1_hash(uint32_t id) {
     return (x * 2654435761u) >> (32 - BITS);
 }
 
-// The LDS state of one column: an open-addressing table of edge keys (a key's slot keeps its
-// state: present in the column, classified, known negative), and a FIFO of keys that turned
-// present while unclassified (each is looked at once it comes out).
+// The state of one column: in LDS an open-addressing table of edge keys (a key's slot keeps its
+// state: present in the column, classified, known negative) and a FIFO of the keys that turned
+// present while unclassified (each is looked at once it comes out).  The counts are the wave's
+// own (uniform) and advance by ballots, not by an atomic of up to 64 lanes on one word.
+constexpr uint32_t kH1Inserted = 1, kH1Queued = 2;
 template <int SLOTS>
 struct H1Col {
+    static constexpr int kQueue = SLOTS / 2;       // (a step leaves about 23 entries)
     uint32_t *tab;
     uint32_t *alt;                 // second table the big tables compact into (unused below 2048)
     uint32_t *queue;
     uint32_t *neg;                 // bit per slot: the key there is a negative edge
-    int *used, *tail, *over;
-    int head;                      // queue position of the chunk being processed (uniform)
+    int *over;                     // the table or the queue is outgrown
+    int used, tail, head;          // slots taken; queue: entries so far, position of the chunk being processed
 
     __device__ __forceinline__ bool is_neg(uint32_t h) const { return (neg[h >> 5] >> (h & 31)) & 1u; }
-    __device__ __forceinline__ void enqueue(uint32_t key) {
-        const int t = atomicAdd(tail, 1);
-        if (t - head >= SLOTS) atomicOr(over, 1);
-        else queue[t & (SLOTS - 1)] = key;
-    }
-    // add edge `key` to the column (toggle its presence); negative edges are left out for good
-    __device__ __forceinline__ void toggle(uint32_t key) {
+    // add edge `key` to the column (toggle its presence); negative edges are left out for good.
+    // Returns what to count (account)
+    __device__ __forceinline__ uint32_t toggle(uint32_t key) {
         uint32_t h = h1_hash<SLOTS>(key);
         for (int probe = 0; probe < SLOTS; ++probe, h = (h + 1) & (SLOTS - 1)) {
-            uint32_t v = __hip_atomic_load(&tab[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (v == kH1Empty) {
-                v = atomicCAS(&tab[h], kH1Empty, key | kH1Present);
-                if (v == kH1Empty) {
-                    atomicAdd(used, 1);
-                    enqueue(key);
-                    return;
-                }
-            }
+            const uint32_t v = atomicCAS(&tab[h], kH1Empty, key | kH1Present);
+            if (v == kH1Empty) return kH1Inserted | kH1Queued;
             if ((v & ~kH1Flags) == key) {
-                if ((v & kH1Final) && is_neg(h)) return;
+                if ((v & kH1Final) && is_neg(h)) return 0;
                 const uint32_t old = atomicXor(&tab[h], kH1Present);
-                if (!(old & kH1Present) && !(old & kH1Final)) enqueue(key);
-                return;
+                return !(old & kH1Present) && !(old & kH1Final) ? kH1Queued : 0u;
             }
         }
         atomicOr(over, 1);
+        return 0;
+    }
+    // queue the lanes' toggled keys and advance the counts; all lanes call it (what: 0 for none)
+    __device__ __forceinline__ void account(uint32_t what, uint32_t key) {
+        const uint64_t q = __ballot((what & kH1Queued) != 0);
+        if (what & kH1Queued) {
+            const int t = tail + __popcll(q & ((1ull << __lane_id()) - 1ull));
+            if (t - head >= kQueue) atomicOr(over, 1);
+            else queue[t & (kQueue - 1)] = key;
+        }
+        tail += __popcll(q);
+        used += __popcll(__ballot((what & kH1Inserted) != 0));
     }
     // slot of `key`, or -1
     __device__ __forceinline__ int find(uint32_t key) const {
@@ -2549,19 +2556,20 @@ struct H1Col {
         uint32_t h = h1_hash<SLOTS>(x & ~kH1Flags);
         for (int probe = 0; probe < SLOTS; ++probe, h = (h + 1) & (SLOTS - 1))
             if (atomicCAS(&t[h], kH1Empty, x) == kH1Empty) break;
-        atomicAdd(used, 1);
     }
-    // rebuild the table with its live entries (present, not negative); all lanes call it
-    __device__ __forceinline__ void compact() {
+    // rebuild the table with its live entries (present, not negative); all lanes call it.
+    // Returns their number
+    __device__ __forceinline__ int compact() {
         const int lane = threadIdx.x;
         if constexpr (SLOTS >= 2048) {              // through the second table
-            lds_barrier();                          // every lane has read *used
+            int live = 0;
             for (int k = lane; k < SLOTS; k += 64) alt[k] = kH1Empty;
-            if (lane == 0) *used = 0;
             lds_barrier();
             for (int k = lane; k < SLOTS; k += 64) {
                 const uint32_t x = tab[k];
-                if (x != kH1Empty && (x & kH1Present) && !((x & kH1Final) && is_neg(k))) reinsert(alt, x);
+                const bool keep = x != kH1Empty && (x & kH1Present) && !((x & kH1Final) && is_neg(k));
+                if (keep) reinsert(alt, x);
+                live += __popcll(__ballot(keep));
             }
             lds_barrier();
             for (int k = lane; k < SLOTS / 32; k += 64) neg[k] = 0;
@@ -2569,9 +2577,10 @@ struct H1Col {
             tab = alt;
             alt = t;
             lds_barrier();
-            return;
+            return live;
         }
         constexpr int PER = SLOTS / 64;
+        int live = 0;
         uint32_t keep[PER];
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
@@ -2583,12 +2592,14 @@ struct H1Col {
 #pragma unroll
         for (int j = 0; j < PER; ++j) tab[lane + 64 * j] = kH1Empty;
         for (int k = lane; k < SLOTS / 32; k += 64) neg[k] = 0;
-        if (lane == 0) *used = 0;
         lds_barrier();
 #pragma unroll
-        for (int j = 0; j < PER; ++j)
+        for (int j = 0; j < PER; ++j) {
             if (keep[j] != kH1Empty) reinsert(tab, keep[j]);
+            live += __popcll(__ballot(keep[j] != kH1Empty));
+        }
         lds_barrier();
+        return live;
     }
 };
 
@@ -2620,26 +2631,43 @@ __device__ __forceinline__ uint64_t edge_key_of(uint64_t ka, uint64_t kb, uint32
     return (k & 0xFFFFFFFF00000000ull) | ((k & 0xFFFFFFFFull) << kCodeBits) | (a_last ? code_ab : 7u - code_ab);
 }
 
-// Add the boundary of square slot q of L(w) to the column, every occurrence of edge `skip` left
-// out: its two edges at w (w is their last vertex) and the two opposite ones, whose last
-// vertices are looked up.
+// Square slot q of a lower star, as its two axes span it: the steps to the vertices across each,
+// and the codes of its two edges at the vertex (a word: first | second << 3).
+struct H1Square {
+    int d1, d2, codes;
+};
+__device__ __forceinline__ H1Square h1_square_of(int q, int W, int HW) {
+    const int code = 7 + q;
+    const int a1 = off_of(code, 0) ? 0 : 1;         // the two axes the square spans, slowest first
+    const int a2 = off_of(code, 2) ? 2 : 1;
+    const int s1 = off_of(code, a1), s2 = off_of(code, a2);
+    const int c1 = s1 < 0 ? 1 + a1 : 6 - a1, c2 = s2 < 0 ? 1 + a2 : 6 - a2;
+    return H1Square{s1 * (a1 == 0 ? HW : W), s2 * (a2 == 2 ? 1 : W), c1 | c2 << 3};
+}
+
+// Add the boundary of square sq of L(w) to the column (the lanes with `on`; all lanes call it),
+// every occurrence of edge `skip` left out: its two edges at w (w is their last vertex) and the
+// two opposite ones, whose last vertices are looked up.
 template <int SLOTS, typename T>
-__device__ __forceinline__ void h1_square(H1Col<SLOTS> &col, const VoxVals<T> &img, uint32_t w, int q, int W, int HW,
+__device__ __forceinline__ void h1_square(H1Col<SLOTS> &col, bool on, const VoxVals<T> &img, uint32_t w, const H1Square &sq,
                                           uint32_t skip) {
-    const int c = 7 + q;
-    const int a1 = off_of(c, 0) ? 0 : 1;            // the two axes the square spans, slowest first
-    const int a2 = off_of(c, 2) ? 2 : 1;
-    const int s1 = off_of(c, a1), s2 = off_of(c, a2);
-    const int st1 = a1 == 0 ? HW : W, st2 = a2 == 2 ? 1 : W;
-    const uint32_t c1 = s1 < 0 ? 1 + a1 : 6 - a1, c2 = s2 < 0 ? 1 + a2 : 6 - a2;
-    const uint32_t pa = (uint32_t)((int)w + s1 * st1), pb = (uint32_t)((int)w + s2 * st2);
-    const uint32_t pab = (uint32_t)((int)pa + s2 * st2);
-    const uint64_t ka = vox_key(img, pa), kb = vox_key(img, pb), kab = vox_key(img, pab);
-    const uint32_t w5 = w << kCodeBits;
-    const uint32_t e[4] = {w5 | c1, w5 | c2, (uint32_t)edge_key_of(ka, kab, c2), (uint32_t)edge_key_of(kb, kab, c1)};
+    uint32_t e[4] = {0, 0, 0, 0};
+    if (on) {
+        const uint32_t c1 = sq.codes & 7, c2 = sq.codes >> 3;
+        const uint32_t pa = (uint32_t)((int)w + sq.d1), pb = (uint32_t)((int)w + sq.d2);
+        const uint32_t pab = (uint32_t)((int)pa + sq.d2);
+        const uint64_t ka = vox_key(img, pa), kb = vox_key(img, pb), kab = vox_key(img, pab);
+        const uint32_t w5 = w << kCodeBits;
+        e[0] = w5 | c1;
+        e[1] = w5 | c2;
+        e[2] = (uint32_t)edge_key_of(ka, kab, c2);
+        e[3] = (uint32_t)edge_key_of(kb, kab, c1);
+    }
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-        if (e[k] != skip) col.toggle(e[k]);
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t what = on && e[k] != skip ? col.toggle(e[k]) : 0u;
+        col.account(what, e[k]);
+    }
 }
 
 // Class of the edge with id `key` (no state bits): 0 negative (paired with its vertex, or a KEEP
@@ -2667,21 +2695,27 @@ __device__ __forceinline__ int h1_class(uint32_t key, const uint16_t *cfg3, cons
     return cm ? 2 : -1;
 }
 
-// One workgroup of 64 threads per column at a time, blockIdx.y = instance.  Pass 0 takes every
-// KEEP square in turn (a square paired in H2 is no column: h1n = -1) with tables of kH1Slots;
-// a column whose live entries outgrow them is put on the instance's retry list, which pass 1
-// goes through with kH1BigSlots.  The column's boundary in critical cells (sorted descending)
+// One workgroup of 64 threads per column at a time.  Pass 0 takes every KEEP square (a square
+// paired in H2 is no column: h1n = -1) with tables of kH1Slots; a column whose live entries
+// outgrow them is put on the instance's retry list, which pass 1 goes through with kH1BigSlots.
+// The workgroups of an instance draw their columns from a counter, and all but the last n % 8
+// instances have theirs on one XCD, an instance after another, so that its pixels and
+// configurations stay in that XCD's L2 (2,270 -> 2,160 us on 32 volumes 96^3).  The column's boundary in critical cells (sorted descending)
 // goes to the pool, its start and length to h1b, h1n.
 template <typename T, int SLOTS>
 __global__ __launch_bounds__(64) void k_h1_morse(const T *__restrict__ imgs, uint8_t *__restrict__ ws, int n,
                                                  Luts lut, int pass) {
     __shared__ uint32_t s_tab[SLOTS];
     __shared__ uint32_t s_tab2[SLOTS >= 2048 ? SLOTS : 1];
-    __shared__ uint32_t s_queue[SLOTS];
+    __shared__ uint32_t s_queue[H1Col<SLOTS>::kQueue];
     __shared__ uint32_t s_neg[SLOTS / 32];
-    __shared__ int s_used, s_tail, s_over, s_nb;
+    __shared__ int s_over, s_nb;
     __shared__ int32_t s_bnd[kH1MaxBoundary];
-    const int i = blockIdx.y;
+    __shared__ uint16_t s_task[64 * 12];            // squares of a step: lane of the entry << 4 | square slot
+    __shared__ H1Square s_sq[12];
+    // gridDim.x / n workgroups an instance; workgroup b runs on XCD b % 8
+    const int per = gridDim.x / n, even = n / kXcds * kXcds, b = blockIdx.x;
+    const int i = b < even * per ? b / (kXcds * per) * kXcds + b % kXcds : even + (b - even * per) / per;
     const Inst I = ((const Inst *)ws)[i];           // one batch of loads, before any atomic
     int32_t *cnt = (int32_t *)(ws + off_cnt(n)) + i * CNT_WORDS;
     if (I.ndim != 3 || !I.h1) return;
@@ -2703,9 +2737,15 @@ __global__ __launch_bounds__(64) void k_h1_morse(const T *__restrict__ imgs, uin
     int32_t *pool = arr<int32_t>(ws, I.o_pool);
     int32_t *retry = arr<int32_t>(ws, I.o_retry);
     const int ncols = pass == 0 ? mF : cnt[CNT_H1RETRY];
-    H1Col<SLOTS> col{s_tab, s_tab2, s_queue, s_neg, &s_used, &s_tail, &s_over, 0};
+    int32_t *next = &cnt[pass == 0 ? CNT_H1NEXT : CNT_H1NEXT2];
+    H1Col<SLOTS> col{s_tab, s_tab2, s_queue, s_neg, &s_over, 0, 0, 0};
+    if (lane < 12) s_sq[lane] = h1_square_of(lane, W, HW);
     int cols = 0, max_chunks = 0;
-    for (int k = blockIdx.x; k < ncols; k += gridDim.x) {
+    for (;;) {
+        int k = 0;
+        if (lane == 0) k = atomicAdd(next, 1);
+        k = __shfl(k, 0, 64);
+        if (k >= ncols) break;
         const int r = pass == 0 ? k : retry[k];
         if (r < 0 || r >= mF) {
             if (lane == 0) set_err(cnt, PH_EINTERNAL);
@@ -2720,8 +2760,8 @@ __global__ __launch_bounds__(64) void k_h1_morse(const T *__restrict__ imgs, uin
         col.alt = s_tab2;
         for (int t = lane; t < SLOTS; t += 64) s_tab[t] = kH1Empty;
         for (int t = lane; t < SLOTS / 32; t += 64) s_neg[t] = 0;
-        if (lane == 0) { s_used = 0; s_tail = 0; s_over = 0; s_nb = 0; }
-        col.head = 0;
+        if (lane == 0) { s_over = 0; s_nb = 0; }
+        col.used = col.tail = col.head = 0;
         lds_barrier();
         // the column's own combination: the sum of its boundaries leaves L(v)
         const uint64_t ks = keyF[r];
@@ -2731,19 +2771,19 @@ __global__ __launch_bounds__(64) void k_h1_morse(const T *__restrict__ imgs, uin
         ok = ok && cfg < (uint32_t)kL3Configs;
         const uint32_t comb = ok ? lut.h1s[cfg * 16 + (cs - 7)] : 0u;
         ok = ok && ((comb >> (cs - 7)) & 1u);
-        if (ok && lane < 12 && ((comb >> lane) & 1u)) h1_square(col, img, v, lane, W, HW, kH1Empty);
-        lds_barrier();
         bool bad = __ballot(!ok) != 0;
+        h1_square(col, ok && lane < 12 && ((comb >> lane) & 1u), img, v, s_sq[lane < 12 ? lane : 0], kH1Empty);
+        lds_barrier();
         int chunk = 0;
         for (; !bad && chunk < kH1MaxChunks; ++chunk) {
             if (s_over) break;                       // uniform: read after a barrier
-            if (s_used > SLOTS * 3 / 4) {
-                col.compact();
-                if (s_used > SLOTS / 2) { if (lane == 0) s_over = 1; lds_barrier(); break; }
+            if (col.used > SLOTS * 3 / 4) {
+                col.used = col.compact();
+                if (col.used > SLOTS / 2) { if (lane == 0) s_over = 1; lds_barrier(); break; }
             }
-            const int tail = s_tail;
+            const int tail = col.tail;
             if (col.head >= tail) break;             // every key that turned present was looked at
-            const uint32_t key = col.head + lane < tail ? s_queue[(col.head + lane) & (SLOTS - 1)] : kH1Empty;
+            const uint32_t key = col.head + lane < tail ? s_queue[(col.head + lane) & (H1Col<SLOTS>::kQueue - 1)] : kH1Empty;
             lds_barrier();
             bool err = false;
             uint32_t tasks = 0;                          // squares of a claimed entry's partner
@@ -2756,10 +2796,9 @@ __global__ __launch_bounds__(64) void k_h1_morse(const T *__restrict__ imgs, uin
                     const int cl = h1_class(key, cfg3, kpos, neg0, I.N, mE, lut, &cm, &rr);
                     if (cl == 0) {
                         atomicOr(&s_neg[h >> 5], 1u << (h & 31));
-                        atomicOr(&col.tab[h], kH1Final);
-                        atomicAnd(&col.tab[h], ~kH1Present);
+                        col.tab[h] = key | kH1Final;     // (a second entry of the key stores the same)
                     } else if (cl == 1) {
-                        atomicOr(&col.tab[h], kH1Final);
+                        col.tab[h] = key | kH1Flags;
                     } else if (cl == 2) {
                         // claim the entry; its partner's reduced column (without it) is added
                         // below, one square per lane
@@ -2770,31 +2809,17 @@ __global__ __launch_bounds__(64) void k_h1_morse(const T *__restrict__ imgs, uin
                     }
                 }
             }
-            // the claimed entries' squares, spread over the lanes 64 at a time: square g of the
-            // wave's list belongs to the lane whose exclusive prefix is the largest one <= g
+            // the claimed entries' squares, listed in LDS and taken 64 at a time
             const int ntask = __popc(tasks);
-            int off = ntask;                             // inclusive prefix over the lanes
-            for (int d = 1; d < 64; d <<= 1) {
-                const int y = __shfl_up(off, d, 64);
-                if (lane >= d) off += y;
-            }
-            const int total = __shfl(off, 63, 64);
-            off -= ntask;
-            for (int r0 = 0; r0 < total; r0 += 64) {
-                const int g = r0 + lane;
-                int owner = 0;
-                for (int st = 32; st > 0; st >>= 1) {
-                    const int cand = owner + st < 64 ? owner + st : 63;
-                    const int co = __shfl(off, cand, 64);
-                    if (owner + st < 64 && co <= g) owner = cand;
-                }
-                uint32_t m = (uint32_t)__shfl((int)tasks, owner, 64);
-                const uint32_t okey = (uint32_t)__shfl((int)key, owner, 64);
-                const int kth = g - __shfl(off, owner, 64);
-                if (g < total) {
-                    for (int j = 0; j < kth; ++j) m &= m - 1;
-                    h1_square(col, img, okey >> kCodeBits, __builtin_ctz(m), W, HW, okey);
-                }
+            int at = (int)wave_incl_sum((uint32_t)ntask);
+            const int total = __shfl(at, 63, 64);
+            at -= ntask;
+            for (; tasks; tasks &= tasks - 1) s_task[at++] = (uint16_t)(lane << 4 | __builtin_ctz(tasks));
+            lds_barrier();
+            for (int g = lane; g - lane < total; g += 64) {
+                const int task = g < total ? s_task[g] : 0;
+                const uint32_t okey = (uint32_t)__shfl((int)key, task >> 4, 64);
+                h1_square(col, g < total, img, okey >> kCodeBits, s_sq[task & 15], okey);
             }
             col.head = col.head + 64 < tail ? col.head + 64 : tail;
             lds_barrier();
@@ -3899,20 +3924,19 @@ int run(int n, const void *d_imgs, const int64_t *d_img_off, const ph_shape *d_s
         FC_LAUNCH(K_UF_2D, hipLaunchKernelGGL(k_unionfind, dim3(n), dim3(kUfThreads), 0, st, ws, n, 1, staged, htop, wide));
     }
     if (h1 && any3) {
-        // one 64-thread workgroup per 512 voxels of the largest volume (at most 8192 per
-        // instance), each taking columns in turn: short-lived workgroups, so the hardware
-        // balances the columns' uneven costs (per 4096 voxels measured 13 % slower)
-        const unsigned hb = (unsigned)std::max<int64_t>(1, std::min<int64_t>(8192, (mv + 511) / 512));
+        // kH1Groups 64-thread workgroups over the instances, or kH1PerVolume for each; one per
+        // 512 voxels of the largest volume at most
+        const unsigned hb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((mv + 511) / 512, std::max<int64_t>((kH1Groups + n - 1) / n, kH1PerVolume)));
         // pass 1 (64 workgroups per instance) takes the columns pass 0 could not hold
         if (elem == 1) {
-            FC_LAUNCH(K_H1MORSE, hipLaunchKernelGGL((k_h1_morse<uint8_t, kH1Slots>), dim3(hb, n), dim3(64), 0, st, (const uint8_t *)cimgs, ws, n, lut, 0));
-            FC_LAUNCH(K_H1MORSE2, hipLaunchKernelGGL((k_h1_morse<uint8_t, kH1BigSlots>), dim3(64, n), dim3(64), 0, st, (const uint8_t *)cimgs, ws, n, lut, 1));
+            FC_LAUNCH(K_H1MORSE, hipLaunchKernelGGL((k_h1_morse<uint8_t, kH1Slots>), dim3(hb * n), dim3(64), 0, st, (const uint8_t *)cimgs, ws, n, lut, 0));
+            FC_LAUNCH(K_H1MORSE2, hipLaunchKernelGGL((k_h1_morse<uint8_t, kH1BigSlots>), dim3(64u * n), dim3(64), 0, st, (const uint8_t *)cimgs, ws, n, lut, 1));
         } else if (elem == 2) {
-            FC_LAUNCH(K_H1MORSE, hipLaunchKernelGGL((k_h1_morse<uint16_t, kH1Slots>), dim3(hb, n), dim3(64), 0, st, (const uint16_t *)cimgs, ws, n, lut, 0));
-            FC_LAUNCH(K_H1MORSE2, hipLaunchKernelGGL((k_h1_morse<uint16_t, kH1BigSlots>), dim3(64, n), dim3(64), 0, st, (const uint16_t *)cimgs, ws, n, lut, 1));
+            FC_LAUNCH(K_H1MORSE, hipLaunchKernelGGL((k_h1_morse<uint16_t, kH1Slots>), dim3(hb * n), dim3(64), 0, st, (const uint16_t *)cimgs, ws, n, lut, 0));
+            FC_LAUNCH(K_H1MORSE2, hipLaunchKernelGGL((k_h1_morse<uint16_t, kH1BigSlots>), dim3(64u * n), dim3(64), 0, st, (const uint16_t *)cimgs, ws, n, lut, 1));
         } else {
-            FC_LAUNCH(K_H1MORSE, hipLaunchKernelGGL((k_h1_morse<float, kH1Slots>), dim3(hb, n), dim3(64), 0, st, (const float *)cimgs, ws, n, lut, 0));
-            FC_LAUNCH(K_H1MORSE2, hipLaunchKernelGGL((k_h1_morse<float, kH1BigSlots>), dim3(64, n), dim3(64), 0, st, (const float *)cimgs, ws, n, lut, 1));
+            FC_LAUNCH(K_H1MORSE, hipLaunchKernelGGL((k_h1_morse<float, kH1Slots>), dim3(hb * n), dim3(64), 0, st, (const float *)cimgs, ws, n, lut, 0));
+            FC_LAUNCH(K_H1MORSE2, hipLaunchKernelGGL((k_h1_morse<float, kH1BigSlots>), dim3(64u * n), dim3(64), 0, st, (const float *)cimgs, ws, n, lut, 1));
         }
         FC_LAUNCH(K_H1REDUCE, hipLaunchKernelGGL(k_h1_reduce, dim3(n), dim3(kUfThreads), 0, st, ws, n));
     }
