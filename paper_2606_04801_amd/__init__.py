@@ -257,14 +257,21 @@ class PairBuffers:
 class Diagram:
     """Result of ph_diagram: device SoA buffers plus the device count and status."""
 
-    def __init__(self, bufs: PairBuffers, count, status, shape):
+    def __init__(self, bufs: PairBuffers, count, status, shape, words=None):
         self.bufs, self.count_t, self.status_t, self.shape = bufs, count, status, tuple(shape)
+        self._words = words          # int64 (0, count, status) that count_t and status_t are views of
 
     def check(self) -> int:
-        st = int(self.status_t.item())
+        # ph_diagram keeps the count and the status side by side: one copy brings both (each
+        # copy waits for the stream and costs about 25 us of host time)
+        if self._words is not None:
+            _, n, st = self._words.tolist()
+            st -= (st & 0x80000000) << 1              # the low half, signed
+        else:
+            n, st = int(self.count_t.item()), int(self.status_t.item())
         if st != PH_OK:
             raise PHError(st, "ph_diagram")
-        return int(self.count_t.item())
+        return n
 
     def numpy(self) -> np.ndarray:
         n = self.check()
@@ -304,15 +311,16 @@ def ph_diagram(img, flags: int = PH_H0 | PH_HTOP, capacity: int | None = None, w
     shp = make_shape(img.shape)
     cap = capacity_bound(img.shape, filtration, flags) if capacity is None else int(capacity)
     bufs = PairBuffers(cap, img.device)
-    count = torch.zeros(1, dtype=torch.int64, device=img.device)
-    status = torch.zeros(1, dtype=torch.int32, device=img.device)
+    # 0, count, status (the low half of the third word: the host is little-endian as the GPU is)
+    words = torch.zeros(3, dtype=torch.int64, device=img.device)
+    count, status = words[1:2], words.view(torch.int32)[4:5]
     nb = int(lib().ph_workspace_bytes(ctypes.byref(shp), 1, flags))
     w = (ws or _default_ws).get(nb, img.device)
     rc = lib().ph_diagram(_ptr(img), shp, flags, bufs.c(), cap, _ptr(count), _ptr(status), _ptr(w),
                           w.numel(), _stream_ptr(stream))
     if rc != PH_OK:
         raise PHError(rc, "ph_diagram")
-    return Diagram(bufs, count, status, img.shape)
+    return Diagram(bufs, count, status, img.shape, words)
 
 
 def ph_diagram_noalloc(img, bufs: PairBuffers, count, status, flags: int = PH_H0 | PH_HTOP,
@@ -503,9 +511,8 @@ def _autograd():
             d = ph_diagram(img.detach(), filtration=filtration)
             n = d.check()
             b = d.bufs
-            ctx.save_for_backward(b.birth_vertex[:n].clone(), b.death_vertex[:n].clone())
             ctx.shape = img.shape
-            ctx.bufs, ctx.n = b, n
+            ctx.bufs, ctx.n, ctx.words = b, n, d._words   # (buffers of this call's own)
             return b.birth[:n].clone(), b.death[:n].clone(), b.dim[:n].clone()
 
         @staticmethod
@@ -516,10 +523,10 @@ def _autograd():
             gb = g_birth.contiguous() if g_birth is not None else torch.zeros(n, device=dev)
             gd = g_death.contiguous() if g_death is not None else torch.zeros(n, device=dev)
             gimg = torch.empty(ctx.shape, dtype=torch.float32, device=dev)
-            counts = torch.tensor([n], dtype=torch.int64, device=dev)
-            out_off = torch.tensor([0, max(n, 1)], dtype=torch.int64, device=dev)
-            img_off = torch.zeros(1, dtype=torch.int64, device=dev)
-            ph_backward(ctx.bufs, counts, out_off, img_off, gb, gd, gimg)
+            # the words (0, count, status): the pair offsets (0, count), the count, the image's
+            # offset 0.  Made anew on the host they took three waiting copies a pass
+            w = ctx.words
+            ph_backward(ctx.bufs, w[1:2], w[:2], w[:1], gb, gd, gimg)
             return gimg, None
 
     class BatchDiagramFn(torch.autograd.Function):
