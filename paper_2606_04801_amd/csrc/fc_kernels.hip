@@ -51,7 +51,7 @@ constexpr int32_t kUnset = 0x7FFFFFFF;     // LDS cube slot not yet written
 constexpr int kMaxChase = 1 << 22;         // bound of every pointer walk
 constexpr int kUfThreads = 1024;
 constexpr int kUfLdsNodes = 40000;         // union-find nodes kept in LDS (a word each)
-constexpr int kUfK = 8;                    // edges a thread of a batch of the union-find
+constexpr int kUfK = 4;                    // edges a thread of a batch of the union-find
 constexpr int kUfLdsWords = 40600;         // the union-find's LDS, int32 (160 KiB less its other shared words)
 constexpr int kUfWideNodes = 20440;        // the wide rounds (PH_WIDE) take forests of more nodes
 constexpr int kSortThreads = 1024;
@@ -62,7 +62,7 @@ constexpr int kSortRun = 2048;             // keys of their runs
 constexpr int kSideBySideInstances = 64;   // batches of up to this many run the images' dual beside H0
 constexpr int kOutParts = 64;              // workgroups that write the pairs, over all instances
 constexpr int kMaxRounds = 48;             // parallel rounds before the sequential finish
-constexpr int kWideRounds = 4;             // union-find rounds over many workgroups (PH_WIDE)
+constexpr int kWideRounds = 6;             // union-find rounds over many workgroups (PH_WIDE)
 constexpr int64_t kWideVoxels = 1 << 20;   // ... for instances of this many voxels
 constexpr int kWideBlocks = 2048, kWideThreads = 256;
 constexpr int kWidePer = 2, kWideSeg = kWidePer * kWideThreads;   // edges a thread, a segment
@@ -1371,11 +1371,13 @@ __device__ __forceinline__ void sort_run(uint8_t *__restrict__ ws, const Inst &I
 }
 
 // Merge passes k_sort_merge makes over a list of m keys, of at most `passes` launched
-// (0: one workgroup sorts the list): one pass up to 16 runs, else as many as are launched.
-// A key's place in one pass takes one binary search in each other run of its group, so two
-// passes over sqrt(runs) runs each beat one over all once there are more than about 16.
+// (0: one workgroup sorts the list): one pass up to 16 runs, two up to 64, else as many as are
+// launched.  A key's place in one pass takes one binary search in each other run of its group,
+// so the searches, 12 instructions a step, bound a long list: noise 128^3 (690k edges in 338
+// runs, and the other lists) takes 319 us in two passes over 19 runs each, 202 us in three over 7.
 __device__ __forceinline__ int sort_passes(int runs, int passes) {
-    return runs <= 1 ? 0 : (runs <= 16 ? (passes < 1 ? passes : 1) : passes);
+    const int want = runs <= 1 ? 0 : (runs <= 16 ? 1 : (runs <= 64 ? 2 : 3));
+    return want < passes ? want : passes;
 }
 
 // The sorts of every instance in one launch: grid (R, n, 4), blockIdx.y = instance, z = list, so
@@ -1494,7 +1496,7 @@ __global__ __launch_bounds__(kSortThreads, 8) void k_sort_lists(uint8_t *__restr
 }
 
 // Merge pass of the lists longer than one run: grid (blocks, n, 4).  The runs are taken in
-// groups (all of them in one pass, or the square root of their number in each of two); a
+// groups (all of them in one pass, or a root of their number in each of two or three); a
 // key's place among its group is its own in its run plus the number of smaller keys in each
 // other run.  A workgroup places kMergeThreads consecutive keys of one run at a time: the part
 // of another run their searches can end in lies between the places of the first and the last of
@@ -1505,7 +1507,7 @@ __global__ __launch_bounds__(kSortThreads, 8) void k_sort_lists(uint8_t *__restr
 // of a 2048^2 8-bit field 40 us (274 us).  Passes alternate between the list's scratch and its place, and the last ends in place.
 constexpr int kMergeThreads = 256;
 constexpr int kMergeRuns = 32;             // runs searched together
-constexpr int kMergeWindow = 6144;         // keys of their windows held in LDS (48 KiB)
+constexpr int kMergeWindow = 3072;         // keys of their windows held in LDS (24 KiB: six workgroups a compute unit)
 
 // keys of a[0, n) below k
 __device__ __forceinline__ int keys_below(const uint64_t *a, int n, uint64_t k) {
@@ -1538,7 +1540,11 @@ __global__ __launch_bounds__(kMergeThreads) void k_sort_merge(uint8_t *__restric
     int fan = runs;                              // runs of a group: the smallest f with f^np >= runs
     if (np == 2)
         for (fan = 2; fan * fan < runs;) ++fan;
-    const int rl = pass == 0 ? run : fan * run, gl = pass == np - 1 ? m : rl * fan;   // keys of a run, a group
+    if (np == 3)
+        for (fan = 2; fan * fan * fan < runs;) ++fan;
+    int rl = run;                                // keys of a run, a group
+    for (int p = 0; p < pass; ++p) rl *= fan;
+    const int gl = pass == np - 1 ? m : rl * fan;
     const uint64_t *a = (np - pass) & 1 ? L.scr : L.dst;
     uint64_t *b = (np - pass) & 1 ? L.dst : L.scr;
     const int steps = (rl + kMergeThreads - 1) / kMergeThreads, all = (m + rl - 1) / rl * steps;
@@ -1584,13 +1590,23 @@ __global__ __launch_bounds__(kMergeThreads) void k_sort_merge(uint8_t *__restric
                     p = v0 - at > 0 ? v0 - at : 0;
                     e = v0 + kMergeWindow - at < len ? v0 + kMergeWindow - at : len;
                 };
-                // a wave loads every fourth window
-                for (int j = threadIdx.x >> 6; j < nr; j += kMergeThreads / 64) {
-                    int p, e;
-                    part(j, p, e);
-                    const uint64_t *src = a + q + j * rl + s_lo[j];
-                    const int at = s_at[j] - v0;
-                    for (int x = p + __lane_id(); x < e; x += 64) s_win[at + x] = src[x];
+                // one key after another of all windows' parts, eight loads a thread in flight (a
+                // wave a window waits for each of its loads: 690k keys 190 us a pass)
+                const int vend = v0 + kMergeWindow < total ? v0 + kMergeWindow : total;
+                for (int v = v0 + (int)threadIdx.x; v < vend; v += 8 * kMergeThreads) {
+                    uint64_t x[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const int y = v + u * kMergeThreads;
+                        int j = 0;               // the last run whose window starts at or before y
+#pragma unroll
+                        for (int st = kMergeRuns / 2; st > 0; st >>= 1) j = s_at[j + st] <= y ? j + st : j;
+                        const int z = y < vend ? q + j * rl + s_lo[j] + (y - s_at[j]) : t0;
+                        x[u] = a[z];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+                        if (v + u * kMergeThreads < vend) s_win[v + u * kMergeThreads - v0] = x[u];
                 }
                 __syncthreads();
                 if (t > tl) continue;
@@ -1964,22 +1980,22 @@ __device__ __forceinline__ void uf_body(const Forest &f, int32_t *cnt, int32_t *
 // ends).  The edges are taken kUfGroup at a time, so that the steps of their walks to the roots
 // are in flight together.  It is bound by the LDS reads of the walks: 31k edges and 20k nodes
 // (316^2 noise) 270 us with the edges in the workspace, 211 us with par and moe in words of
-// their own and batches of 32k edges, about 130 us so (batches of 4k to 16k edges: within 15 %).
+// their own and batches of 32k edges, 127 us so (8k edges a batch 133 us, 16k 149 us).
 // MAPPED: the forest is what the wide rounds left (uf_rest): edge e of m joins the two nodes
 // packed in f.ea[e], numbered anyhow below M (s_rank: their ranks), and has walk position pos[e].
 constexpr uint32_t kDone = ~0u;
 constexpr uint32_t kRoot = 1u << 31;
 constexpr int kUfGroup = 2;
-constexpr int kUfPlaceBits = 14;           // an edge's place in its batch
+constexpr int kUfPlaceBits = 12;           // an edge's place in its batch
 constexpr uint32_t kUfTags = (1u << (31 - kUfPlaceBits)) - 2;   // rounds of all batches
-constexpr int kUfLdsEdges = 1 << 24;       // edges of a forest: 48 rounds in each of 2048 batches
+constexpr int kUfLdsEdges = 1 << 24;       // edges of a forest: 48 rounds in each of 4096 batches
 
 template <int K, bool MAPPED>
 __device__ __forceinline__ void uf_lds(const Forest &f, int m, int M, int32_t *cnt, uint32_t *s_node, const uint32_t *s_rank,
                                        const int32_t *pos, int *s_wsum, int *s_any, int32_t *live, int32_t *A, int32_t *B) {
     const int tid = threadIdx.x;
     constexpr int kBatch = K * kUfThreads;
-    static_assert(kBatch <= 1 << kUfPlaceBits && (uint64_t)kUfLdsEdges / (8 * kUfThreads) * kMaxRounds < kUfTags, "places and tags");
+    static_assert(kBatch <= 1 << kUfPlaceBits && (uint64_t)kUfLdsEdges / kBatch * kMaxRounds < kUfTags, "places and tags");
     auto rank_of = [&](uint32_t x) { return MAPPED ? s_rank[x] : x; };
     auto place_of = [&](int e) { return f.edge_of(MAPPED ? pos[e] : e); };
     auto get = [&](uint32_t x) { return __hip_atomic_load(&s_node[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
@@ -2135,8 +2151,10 @@ __device__ __forceinline__ void uf_lds(const Forest &f, int m, int M, int32_t *c
 // few cache lines: in order of age each launch took twice as long) and are compared by rank;
 // the resolve passes leave them so.  The eldest node never dies and takes no atomics: its
 // component grows to hold most edges' ends, and one word taking an atomic per edge is a hot spot.
-// Noise of 2^20 pixels: after four rounds 13k of 210k nodes and 85k of 326k edges are left, which
-// one workgroup's LDS holds; more rounds here would end few nodes each.
+// Noise of 2^20 pixels: after six rounds 53k of 326k edges are left, between some 4k of 210k nodes,
+// which one workgroup's LDS holds.  A round here costs 30 us less by the round (80 us the first:
+// 1.3M atomics), and saves the workgroup 50 us by then (four rounds: 33 us more in all, 65 us on
+// 128^3 noise).
 // The arrays of a wide forest: par and moe (which holds the left nodes' new numbers in the end);
 // the segments' edges (walk position, roots) and sizes; the same of all segments closed up, both
 // ends packed in one word (ends, pos); the ranks, and those of the nodes left by new number; the
@@ -2203,25 +2221,35 @@ __global__ __launch_bounds__(kWideThreads) void k_uf_wide(uint8_t *__restrict__ 
         }
     }
     if (phase == 2) {
-        // one atomic a workgroup and pass; new numbers in any order
-        for (int x0 = blockIdx.x * kWideThreads; x0 < M; x0 += gridDim.x * kWideThreads) {
-            const int x = x0 + tid;
-            const bool mark = x < M && w.moe[x] == 0;
-            const uint64_t vote = __ballot(mark);
+        // one atomic a workgroup and pass of kNum nodes a thread (an atomic for every 256 nodes
+        // queued up at the one word: 50 us for 210k nodes, 8 us so); new numbers in any order
+        constexpr int kNum = 8;
+        for (int x0 = blockIdx.x * kWideThreads * kNum; x0 < M; x0 += gridDim.x * kWideThreads * kNum) {
+            uint32_t mark = 0;
+#pragma unroll
+            for (int j = 0; j < kNum; ++j) {
+                const int x = x0 + j * kWideThreads + tid;
+                if (x < M && w.moe[x] == 0) mark |= 1u << j;
+            }
+            const int mine = __popc(mark), upto = (int)wave_incl_sum((uint32_t)mine);
             __syncthreads();                         // the last pass's counts have been read
-            if (lane == 0) s_cnt[0][wid] = __popcll(vote);
+            if (lane == 63) s_cnt[0][wid] = upto;
             __syncthreads();
-            int sum = 0, before = 0;
+            int sum = 0, id = upto - mine;
             for (int v = 0; v < kWideThreads / 64; ++v) {
-                if (v < wid) before += s_cnt[0][v];
+                if (v < wid) id += s_cnt[0][v];
                 sum += s_cnt[0][v];
             }
             if (tid == 0) s_flag = sum ? atomicAdd(w.nodes, sum) : 0;
             __syncthreads();
-            if (mark) {
-                const int id = s_flag + before + __popcll(vote & ((1ull << lane) - 1ull));
+            id += s_flag;
+#pragma unroll
+            for (int j = 0; j < kNum; ++j) {
+                if (!((mark >> j) & 1u)) continue;
+                const int x = x0 + j * kWideThreads + tid;
                 w.moe[x] = (uint32_t)id;
                 if (id < kRestNodes) w.left[id] = w.rank[x];
+                ++id;
             }
         }
         return;
@@ -2426,8 +2454,8 @@ __device__ __forceinline__ void uf_rest(uint8_t *__restrict__ ws, const Inst &I,
 
 // Union-find passes, blockIdx.x = instance.  Stage 0: blockIdx.y = 0 H0 of every instance,
 // y = 1 (with the top dimension) the dual of the volumes, and of the images too unless a stage 1
-// follows for them (staged).  Forests that fit take uf_lds with the fewest registers that hold
-// their edges; larger ones use the workspace for everything.  H0 and the dual of one instance
+// follows for them (staged).  Forests that fit take uf_lds; larger ones use the workspace for
+// everything.  H0 and the dual of one instance
 // run side by side: the dual keeps its live edges in the free second live array and its roots
 // in the sort scratch (8 max(L, N) bytes).
 // wide: the call ran the wide rounds (k_uf_wide) before this launch.
@@ -2464,10 +2492,6 @@ __global__ __launch_bounds__(kUfThreads) void k_unionfind(uint8_t *__restrict__ 
     int32_t *B = arr<int32_t>(ws, pick(dual, I.o_rb, I.o_scratch + 4 * L, 0, 0));
     if (wide && uf_is_wide(I, f.M, f.m)) {
         uf_rest(ws, I, cnt, f, s_mem, s_wsum, s_any);
-        return;
-    }
-    if (f.M <= kUfLdsNodes && f.m <= 4 * kUfThreads) {
-        uf_lds<4, false>(f, f.m, f.M, cnt, s_mem, nullptr, nullptr, s_wsum, s_any, live, A, B);
         return;
     }
     if (f.M <= kUfLdsNodes && f.m <= kUfLdsEdges) {
@@ -3367,7 +3391,7 @@ __global__ __launch_bounds__(kUfThreads) void k_output(const void *__restrict__ 
         // (an entry without a partner reads the partner list's first key; an empty one has none)
         const uint64_t *kE = mE > 0 ? keyE : n0s, *kF = mf > 0 ? fkey : keyE;
         if (use0) {
-#pragma unroll 4
+#pragma unroll 8
             for (int j = threadIdx.x; j < M0; j += kUfThreads) {
                 const int d = death0[j];
                 const uint32_t eo = key_ord(kE[d < 0 || d >= mE ? 0 : d]), no = key_ord(n0s[j]);
@@ -3377,7 +3401,7 @@ __global__ __launch_bounds__(kUfThreads) void k_output(const void *__restrict__ 
             }
         }
         if (useT) {
-#pragma unroll 4
+#pragma unroll 8
             for (int r = threadIdx.x; r < mf; r += kUfThreads) {
                 const int x = killer[r];
                 const uint32_t to = key_ord(nTkey[x < 1 || x >= MT ? 0 : x]), fo = key_ord(fkey[r]);
@@ -3387,7 +3411,7 @@ __global__ __launch_bounds__(kUfThreads) void k_output(const void *__restrict__ 
             }
         }
         if (h1) {
-#pragma unroll 4
+#pragma unroll 8
             for (int r = threadIdx.x; r < mE; r += kUfThreads) {
                 const int j = piv[r];
                 const uint32_t so = key_ord(kF[j < 0 || j >= mf ? 0 : j]), eo = key_ord(keyE[r]);
@@ -3903,18 +3927,18 @@ int run(int n, const void *d_imgs, const int64_t *d_img_off, const ph_shape *d_s
     // are spread over the whole GPU (each instance's kernels decide for themselves, from its
     // counts)
     const int wide = (flags & PH_WIDE) && mv >= kWideVoxels ? 1 : 0;
-    // Long lists: a workgroup per run and one merge launch (two under PH_WIDE, for hundreds of
+    // Long lists: a workgroup per run and one merge launch (three under PH_WIDE, for hundreds of
     // runs).  A list of 8193 keys or more needs about 2^15 voxels even of noise (0.33 KEEP edges
     // a pixel); below 2^16 voxels, and in batches that fill the chip with a workgroup a list,
     // the one workgroup merges its two or three runs itself, which saves the launch.
     const bool multi = mv >= kSortMultiVoxels && n <= kSortMultiInstances;
-    const int passes = !multi ? 0 : (wide ? 2 : 1);
+    const int passes = !multi ? 0 : (wide ? 3 : 1);
     const int rl = multi ? kSortRun : kSortCap;
     const int64_t runs = (ml + rl - 1) / rl;
     const unsigned sr = multi ? (unsigned)std::min<int64_t>(runs, std::max<int64_t>(1, 256 / n)) : 1u;
     FC_LAUNCH(K_SORT, hipLaunchKernelGGL(k_sort_lists, dim3(sr, n, 4), dim3(kSortThreads), 0, st, ws, n, rl, passes));
     for (int p = 0; p < passes; ++p) {
-        const unsigned mb = (unsigned)std::min<int64_t>((ml + kMergeThreads - 1) / kMergeThreads, std::max<int64_t>(16, 256 / n));
+        const unsigned mb = (unsigned)std::min<int64_t>((ml + kMergeThreads - 1) / kMergeThreads, std::max<int64_t>(16, (wide ? 1024 : 256) / n));
         FC_LAUNCH(K_SORTMERGE, hipLaunchKernelGGL(k_sort_merge, dim3(mb, n, 4), dim3(kMergeThreads), 0, st, ws, n, rl, passes, p));
     }
     // volumes: the dual (resolve, union-find) beside H0; images: the dual after H0
