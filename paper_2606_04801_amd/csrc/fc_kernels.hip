@@ -2743,10 +2743,12 @@ __device__ __forceinline__ int h1_class(uint32_t key, const uint16_t *cfg3, cons
 // One workgroup of 64 threads per column at a time.  Pass 0 takes every KEEP square (a square
 // paired in H2 is no column: h1n = -1) with tables of kH1Slots; a column whose live entries
 // outgrow them is put on the instance's retry list, which pass 1 goes through with kH1BigSlots.
-// The workgroups of an instance draw their columns from a counter, and all but the last n % 8
-// instances have theirs on one XCD, an instance after another, so that its pixels and
-// configurations stay in that XCD's L2 (2,270 -> 2,160 us on 32 volumes 96^3).  The column's boundary in critical cells (sorted descending)
-// goes to the pool, its start and length to h1b, h1n.
+// The workgroups of an instance draw their columns from a counter, the latest squares first:
+// theirs are the long columns, which else end the launch on a few compute units (8 volumes 96^3
+// 825 -> 663 us, 32 volumes 2,000 -> 1,833 us).  All but the last n % 8 instances have theirs on
+// one XCD, an instance after another, so that its pixels and configurations stay in that XCD's
+// L2 (2,270 -> 2,160 us on 32 volumes 96^3).  The column's boundary in critical cells (sorted
+// descending) goes to the pool, its start and length to h1b, h1n.
 template <typename T, int SLOTS>
 __global__ __launch_bounds__(64) void k_h1_morse(const T *__restrict__ imgs, uint8_t *__restrict__ ws, int n,
                                                  Luts lut, int pass) {
@@ -2791,7 +2793,7 @@ __global__ __launch_bounds__(64) void k_h1_morse(const T *__restrict__ imgs, uin
         if (lane == 0) k = atomicAdd(next, 1);
         k = __shfl(k, 0, 64);
         if (k >= ncols) break;
-        const int r = pass == 0 ? k : retry[k];
+        const int r = pass == 0 ? ncols - 1 - k : retry[k];
         if (r < 0 || r >= mF) {
             if (lane == 0) set_err(cnt, PH_EINTERNAL);
             return;
