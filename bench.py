@@ -185,7 +185,7 @@ def algorithmic_bytes(name, wc, npairs, shapes, grad=False):
         return (4 * n + 4 * n + 4 * t + (4 * n if grad else 0)
                 + 8 * (int(wc[sel, 0].sum()) + int(wc[sel, 1].sum()) + int(wc[sel, 2].sum()) + int(wc[sel, 3].sum())))
     if name == "k_sort":
-        return 16 * (ke + kf + m0)
+        return 16 * (ke + kf + m0 + mt)
     f3 = int(wc[is3, 1].sum())                          # facets of the volumes (walked beside H0)
     if name == "k_resolve":
         return 16 * (ke + f3) + 4 * int(hops0.sum() + hopsT[is3].sum())
