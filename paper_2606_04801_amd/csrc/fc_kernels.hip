@@ -2551,7 +2551,11 @@ __device__ __forceinline__ uint32_t h1_hash(uint32_t id) {
 constexpr uint32_t kH1Inserted = 1, kH1Queued = 2;
 template <int SLOTS>
 struct H1Col {
-    static constexpr int kQueue = SLOTS / 2;       // (a step leaves about 23 entries)
+    // The first pass keeps half as many keys waiting as slots (a step leaves about 23; more
+    // workgroups then fit a compute unit): a column that outgrows them is only put off.  In the second
+    // pass it would be an error, and a column may leave more of them than it has live entries (keys
+    // queued twice, keys toggled off again): a queue of half the slots refused a circle of radius 250.
+    static constexpr int kQueue = SLOTS >= kH1BigSlots ? SLOTS : SLOTS / 2;
     uint32_t *tab;
     uint32_t *alt;                 // second table the big tables compact into (unused below 2048)
     uint32_t *queue;

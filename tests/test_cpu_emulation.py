@@ -413,3 +413,16 @@ def test_wide_union_find_rounds():
     imgs = [S.uniform((1024, 1024), 25), S.uniform((20, 21), 26)]
     for img, (got, st) in zip(imgs, run(exe, imgs, mode=1, flags=3 | 64)[0]):
         assert st == 0 and diff_pairs(got, oracle.diagram(img)) is None, img.shape
+
+
+def test_h1_column_with_a_long_queue():
+    """A valley along a circle of radius 250: the column of the square that ends it has over 2048
+    keys waiting to be looked at in the second pass, though fewer than 2048 entries."""
+    n = 512
+    y, x = np.mgrid[0:n, 0:n].astype(np.float64)
+    c = (n - 1) / 2
+    f = (np.hypot(y - c, x - c) - 250) ** 2
+    f += np.random.default_rng(1).random(f.shape) * 1e-3
+    a = (f / f.max()).astype(np.float32)[None]
+    (got, st), = run(emu_build.build("poison"), [a], flags=3 | 32)[0]
+    assert st == 0 and diff_pairs(got, h1_ref(a)) is None
