@@ -199,8 +199,11 @@ FC_HD int64_t layout(Inst &I, int64_t at) {
     I.o_par0 = take(4 * N);
     I.o_parT = take(4 * T);
     I.o_keyE = take(8 * E);
-    I.o_ea = take(4 * E);
-    I.o_eb = take(4 * E);
+    // ea and eb are one contiguous region: before the edges' ends are written there it is the
+    // scratch of a long list of dual nodes (8 bytes each; T <= E, under a list fraction too, so
+    // they are E at most)
+    I.o_ea = take(8 * E);
+    I.o_eb = I.o_ea + 4 * E;
     I.o_neg0 = take(4 * E);
     I.o_keyF = take(8 * F);
     I.o_fa = take(4 * FAC);

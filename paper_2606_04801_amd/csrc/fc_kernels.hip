@@ -1206,9 +1206,9 @@ __device__ __forceinline__ int block_flag_scan(int flag, int *s_wsum, int *total
 // takes a fifth of those of the bitonic network that stood here (78 compare-exchange stages of
 // 4096 keys; 16 workgroup waves on four SIMDs): 64 volumes 96^3 and 64 images 512^2 43 -> 26 us,
 // 512 images of 64^2 to 512^2 89 -> 44 us (with a fourth list, the dual nodes).
-// Longer lists are sorted in runs of kSortCap keys.  With one workgroup a list (R = 1) the runs
-// are merged pairwise through LDS tiles; with more, each run has a workgroup of its own and
-// k_sort_merge merges all of them at once.
+// Longer lists are sorted in runs.  With one workgroup a list (R = 1) the runs, of kSortCap keys,
+// are merged pairwise through LDS tiles; with more, each run, of up to kSortRun keys, has a
+// workgroup of its own and k_sort_merge merges them.
 // Keys are unique (the pixel and code are part of them), so every order is total, and no key
 // (and no complement of a dual node's) is ~0, the padding.
 
@@ -1383,8 +1383,7 @@ __device__ __forceinline__ int sort_passes(int runs, int passes) {
 // The sorts of every instance in one launch: grid (R, n, 4), blockIdx.y = instance, z = list, so
 // the lists of all instances are sorted side by side.  Each list has a scratch of its own: the
 // sort scratch (KEEP edges), the live-edge arrays (KEEP squares), the root arrays (H0 nodes) and
-// the edges' endpoint array (dual nodes: at most half as many as edges wherever a list outgrows
-// one run), all written only afterwards.
+// the edges' endpoint arrays (dual nodes), all written only afterwards.
 // rl: keys of a run, at most kSortCap (all of it where one workgroup sorts the list).
 // passes: k_sort_merge launches that follow (0: none; a long list is merged here).
 __global__ __launch_bounds__(kSortThreads, 8) void k_sort_lists(uint8_t *__restrict__ ws, int n, int rl, int passes) {

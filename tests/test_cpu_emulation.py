@@ -426,3 +426,15 @@ def test_h1_column_with_a_long_queue():
     a = (f / f.max()).astype(np.float32)[None]
     (got, st), = run(emu_build.build("poison"), [a], flags=3 | 32)[0]
     assert st == 0 and diff_pairs(got, h1_ref(a)) is None
+
+
+@pytest.mark.parametrize("variant", ["asan", "trace"])
+def test_dual_node_runs_under_a_list_fraction(variant):
+    """2,601 dual nodes in two sort runs beside edge lists of 4,096 entries, the least a list
+    fraction leaves (PH_LIST_FRACTION(1)): the runs' scratch holds 8 bytes a dual node."""
+    y, x = np.mgrid[0:256, 0:256]
+    a = (y * 256 + x).astype(np.float32)
+    a[2:254:5, 2:254:5] += 1e6                       # 51 x 51 peaks: one top pair each, one minimum in all
+    (got, st), = run(emu_build.build(variant), [a], flags=3 | 1 << 8)[0]
+    assert st == 0 and diff_pairs(got, oracle.diagram(a)) is None
+    assert (got["dim"] == 1).sum() == 51 * 51
