@@ -53,7 +53,12 @@ constexpr int kUfThreads = 1024;
 constexpr int kUfLdsNodes = 40000;         // union-find nodes kept in LDS (a word each)
 constexpr int kUfK = 4;                    // edges a thread of a batch of the union-find
 constexpr int kUfLdsWords = 40600;         // the union-find's LDS, int32 (160 KiB less its other shared words)
-constexpr int kUfWideNodes = 20440;        // the wide rounds (PH_WIDE) take forests of more nodes
+// The sizes of the wide passes.  The tests' host build lowers them by FC_WIDE_SHIFT powers of two, so
+// that small images take every path of large ones.
+#ifndef FC_WIDE_SHIFT
+#define FC_WIDE_SHIFT 0
+#endif
+constexpr int kUfWideNodes = 20440 >> FC_WIDE_SHIFT;   // the wide rounds (PH_WIDE) take forests of more nodes
 constexpr int kSortThreads = 1024;
 constexpr int kSortCap = 4096;             // keys sorted entirely in LDS (two buffers of 34 KiB)
 constexpr int64_t kSortMultiVoxels = 1 << 16;   // long lists sorted by several workgroups from this size on
@@ -62,12 +67,13 @@ constexpr int kSortRun = 2048;             // keys of their runs
 constexpr int kSideBySideInstances = 64;   // batches of up to this many run the images' dual beside H0
 constexpr int kOutParts = 64;              // workgroups that write the pairs, over all instances
 constexpr int kMaxRounds = 48;             // parallel rounds before the sequential finish
-constexpr int kWideRounds = 6;             // union-find rounds over many workgroups (PH_WIDE)
-constexpr int64_t kWideVoxels = 1 << 20;   // ... for instances of this many voxels
+constexpr int kWideRoundsMin = 6;          // union-find rounds over many workgroups (PH_WIDE), at least
+constexpr int64_t kWideVoxels = (1 << 20) >> FC_WIDE_SHIFT;   // ... for instances of this many voxels
 constexpr int kWideBlocks = 2048, kWideThreads = 256;
 constexpr int kWidePer = 2, kWideSeg = kWidePer * kWideThreads;   // edges a thread, a segment
-constexpr int kRestNodes = 20000;          // nodes the finish in one workgroup holds (two words of LDS each)
-constexpr int kWidePosBits = 28;           // walk positions of a wide forest (the round's tag above)
+constexpr int kRestNodes = 20000 >> FC_WIDE_SHIFT;   // nodes the finish in one workgroup holds (two words of LDS each)
+constexpr int kWidePosBits = 29;           // walk positions of a wide forest (the round's tag above)
+constexpr int kWideTags = 7;               // rounds between two clearings of moe
 constexpr int32_t kInf = 0x7FFFFFFF;
 constexpr int kMaxInstances = 65535;       // instances of one call: the y extent of a grid
 // Halo key of a pixel outside the image.  Pixel keys are capped one below it (only the NaN bit
@@ -1652,7 +1658,8 @@ __global__ __launch_bounds__(kMergeThreads) void k_sort_merge(uint8_t *__restric
 __device__ __forceinline__ bool uf_is_wide(const Inst &I, int M, int m) {
     const int64_t L = I.E > I.F ? I.E : I.F;
     // (the segments' sizes and the ranks of uf_rest follow the m positions in the live-edge array)
-    return I.N >= kWideVoxels && M > kUfWideNodes && M <= L && I.MTcap <= I.M0cap && m < 1 << kWidePosBits &&
+    static_assert(3ll << kPixBits <= 1ll << kWidePosBits && kWideTags < 1 << (32 - kWidePosBits), "positions and tags");
+    return I.N >= kWideVoxels && M > kUfWideNodes && M <= L && I.MTcap <= I.M0cap &&
            m + m / kWideSeg + 1 + kRestNodes <= L;
 }
 
@@ -1982,6 +1989,7 @@ __device__ __forceinline__ void uf_body(const Forest &f, int32_t *cnt, int32_t *
 // their own and batches of 32k edges, 127 us so (8k edges a batch 133 us, 16k 149 us).
 // MAPPED: the forest is what the wide rounds left (uf_rest): edge e of m joins the two nodes
 // packed in f.ea[e], numbered anyhow below M (s_rank: their ranks), and has walk position pos[e].
+// before: the rounds made already.
 constexpr uint32_t kDone = ~0u;
 constexpr uint32_t kRoot = 1u << 31;
 constexpr int kUfGroup = 2;
@@ -1991,7 +1999,8 @@ constexpr int kUfLdsEdges = 1 << 24;       // edges of a forest: 48 rounds in ea
 
 template <int K, bool MAPPED>
 __device__ __forceinline__ void uf_lds(const Forest &f, int m, int M, int32_t *cnt, uint32_t *s_node, const uint32_t *s_rank,
-                                       const int32_t *pos, int *s_wsum, int *s_any, int32_t *live, int32_t *A, int32_t *B) {
+                                       const int32_t *pos, int *s_wsum, int *s_any, int32_t *live, int32_t *A, int32_t *B,
+                                       int before) {
     const int tid = threadIdx.x;
     constexpr int kBatch = K * kUfThreads;
     static_assert(kBatch <= 1 << kUfPlaceBits && (uint64_t)kUfLdsEdges / kBatch * kMaxRounds < kUfTags, "places and tags");
@@ -2133,19 +2142,19 @@ __device__ __forceinline__ void uf_lds(const Forest &f, int m, int M, int32_t *c
         }
         __syncthreads();
     }
-    if (tid == 0) cnt[f.dual ? CNT_ROUNDST : CNT_ROUNDS0] = rounds + (MAPPED ? kWideRounds : 0);
+    if (tid == 0) cnt[f.dual ? CNT_ROUNDST : CNT_ROUNDS0] = before + rounds;
 }
 
 // ------------------------------------------------------------- wide union-find --
 // Under PH_WIDE a forest of more than kUfWideNodes nodes, of an instance of kWideVoxels or more
-// voxels, first takes kWideRounds of the rounds above spread over the whole GPU; k_unionfind then
-// finishes what is left in one workgroup (uf_rest).  Two launches a round: phase 0 finds each
+// voxels, first takes some of the rounds above (wide_rounds) spread over the whole GPU; k_unionfind
+// then finishes what is left in one workgroup (uf_rest).  Two launches a round: phase 0 finds each
 // live edge's roots and lowers their moe, phase 1 fires the roots whose least edge reaches an
 // elder root.  An edge takes part as (walk position, root, root) in the segment of kWideSeg
 // positions it comes from; phase 0 drops the edges that have fired or join one component and
 // closes the gaps, in order, inside each segment, so the work shrinks with the live edges and
-// no workgroup waits for another.  moe needs no clearing: an entry is an edge's walk position
-// below a tag that falls from round to round.
+// no workgroup waits for another.  moe is cleared every kWideTags rounds only: an entry is an
+// edge's walk position below a tag that falls from round to round.
 // Nodes keep the numbers the classify pass gave them (neighbours in space, so the walks stay in
 // few cache lines: in order of age each launch took twice as long) and are compared by rank;
 // the resolve passes leave them so.  The eldest node never dies and takes no atomics: its
@@ -2153,7 +2162,7 @@ __device__ __forceinline__ void uf_lds(const Forest &f, int m, int M, int32_t *c
 // Noise of 2^20 pixels: after six rounds 53k of 326k edges are left, between some 4k of 210k nodes,
 // which one workgroup's LDS holds.  A round here costs 30 us less by the round (80 us the first:
 // 1.3M atomics), and saves the workgroup 50 us by then (four rounds: 33 us more in all, 65 us on
-// 128^3 noise).
+// 128^3 noise).  Larger instances take more rounds (wide_rounds).
 // The arrays of a wide forest: par and moe (which holds the left nodes' new numbers in the end);
 // the segments' edges (walk position, roots) and sizes; the same of all segments closed up, both
 // ends packed in one word (ends, pos); the ranks, and those of the nodes left by new number; the
@@ -2182,12 +2191,13 @@ __device__ __forceinline__ WideForest wide_forest(uint8_t *__restrict__ ws, cons
     return w;
 }
 
-// phase -1: set up; 0, 1: the two phases of round `round` (in phase 0 of round kWideRounds, the
-// last, moe[x] = 0 marks the roots left); 2: the roots left numbered; 3: the segments closed up.
+// phase -1: set up; 0, 1: the two phases of round `round` of `rounds` (in phase 0 of round `rounds`,
+// the last, moe[x] = 0 marks the roots left); 2: the roots left numbered; 3: the segments closed
+// up; 4: moe cleared for the next rounds' tags.
 // Grid (blocks, n, side): blockIdx.y = instance; stage and blockIdx.z choose H0 or the dual as
 // in k_unionfind.
 __global__ __launch_bounds__(kWideThreads) void k_uf_wide(uint8_t *__restrict__ ws, int n, int stage, int staged, int htop,
-                                                          int phase, int round) {
+                                                          int phase, int round, int rounds) {
     __shared__ int s_cnt[kWidePer][kWideThreads / 64];
     __shared__ int s_flag;
     const int i = blockIdx.y, tid = threadIdx.x, lane = __lane_id(), wid = tid >> 6;
@@ -2198,7 +2208,7 @@ __global__ __launch_bounds__(kWideThreads) void k_uf_wide(uint8_t *__restrict__ 
     const int mE = cnt[CNT_E], mF = cnt[CNT_F], m0 = cnt[CNT_M0], mT = cnt[CNT_MT];
     const int M = dual ? mT : m0, m = !dual || is2d ? mE : mF;
     const int segs = (m + kWideSeg - 1) / kWideSeg;
-    if ((int)blockIdx.x >= segs && phase != -1 && phase != 2) return;
+    if ((int)blockIdx.x >= segs && phase != -1 && phase != 2 && phase != 4) return;
     if (tid == 0) s_flag = failed(cnt);
     lds_barrier();
     if (s_flag || !uf_is_wide(I, M, m)) return;
@@ -2218,6 +2228,10 @@ __global__ __launch_bounds__(kWideThreads) void k_uf_wide(uint8_t *__restrict__ 
             w.moe[x] = ~0u;
             if (!dual) death0[x] = -1;
         }
+    }
+    if (phase == 4) {
+        for (int x = blockIdx.x * kWideThreads + tid; x < M; x += gridDim.x * kWideThreads) w.moe[x] = ~0u;
+        return;
     }
     if (phase == 2) {
         // one atomic a workgroup and pass of kNum nodes a thread (an atomic for every 256 nodes
@@ -2253,7 +2267,7 @@ __global__ __launch_bounds__(kWideThreads) void k_uf_wide(uint8_t *__restrict__ 
         }
         return;
     }
-    const uint32_t tag = (uint32_t)(kWideRounds - round) << kWidePosBits;
+    const uint32_t tag = (uint32_t)(kWideTags - round % kWideTags) << kWidePosBits;   // (never 0: the mark)
     const int eldest = phase == 0 ? *w.eldest : 0;
     for (int sg = blockIdx.x; sg < segs; sg += gridDim.x) {
         const int at = sg * kWideSeg, all = m - at < kWideSeg ? m - at : kWideSeg;
@@ -2374,9 +2388,9 @@ __global__ __launch_bounds__(kWideThreads) void k_uf_wide(uint8_t *__restrict__ 
 #pragma unroll
             for (int j = 0; j < kWidePer; ++j) {
                 in[j] = in[j] && a[j] != b[j];
-                if (in[j] && round == kWideRounds) w.moe[a[j]] = w.moe[b[j]] = 0;
+                if (in[j] && round == rounds) w.moe[a[j]] = w.moe[b[j]] = 0;
             }
-            if (round < kWideRounds) {
+            if (round < rounds) {
                 uint32_t xa[kWidePer], xb[kWidePer];
 #pragma unroll
                 for (int j = 0; j < kWidePer; ++j) {
@@ -2418,7 +2432,7 @@ __global__ __launch_bounds__(kWideThreads) void k_uf_wide(uint8_t *__restrict__ 
         }
         if (tid == 0) {
             w.size[sg] = before;
-            if (before > 0 && phase == 0 && round < kWideRounds) cnt[dual ? CNT_ROUNDST : CNT_ROUNDS0] = round + 1;
+            if (before > 0 && phase == 0 && round < rounds) cnt[dual ? CNT_ROUNDST : CNT_ROUNDS0] = round + 1;
         }
     }
 }
@@ -2426,7 +2440,7 @@ __global__ __launch_bounds__(kWideThreads) void k_uf_wide(uint8_t *__restrict__ 
 // What the wide rounds left of a forest, by one workgroup: if the nodes fit in LDS with their
 // ranks (kRestNodes), uf_lds goes on; else uf_body.
 __device__ __forceinline__ void uf_rest(uint8_t *__restrict__ ws, const Inst &I, int32_t *cnt, Forest &f, uint32_t *s_mem,
-                                        int *s_wsum, int *s_any) {
+                                        int *s_wsum, int *s_any, int rounds) {
     const WideForest w = wide_forest(ws, I, cnt, f.dual, f.m);
     const int total = *w.total, nodes = *w.nodes;
     f.rank = w.rank;
@@ -2435,7 +2449,7 @@ __device__ __forceinline__ void uf_rest(uint8_t *__restrict__ ws, const Inst &I,
         for (int x = threadIdx.x; x < nodes; x += kUfThreads) s_mem[x] = (uint32_t)w.left[x];
         f.ea = w.ends;
         // (the sequential finish's lists: the segments' arrays, free now)
-        uf_lds<kUfK, true>(f, total, nodes, cnt, s_mem + kRestNodes, s_mem, w.pos, s_wsum, s_any, w.q, w.a, w.b);
+        uf_lds<kUfK, true>(f, total, nodes, cnt, s_mem + kRestNodes, s_mem, w.pos, s_wsum, s_any, w.q, w.a, w.b, rounds);
         return;
     }
     // each edge's roots to its walk position, and on in the workspace
@@ -2457,7 +2471,7 @@ __device__ __forceinline__ void uf_rest(uint8_t *__restrict__ ws, const Inst &I,
 // everything.  H0 and the dual of one instance
 // run side by side: the dual keeps its live edges in the free second live array and its roots
 // in the sort scratch (8 max(L, N) bytes).
-// wide: the call ran the wide rounds (k_uf_wide) before this launch.
+// wide: the wide rounds (k_uf_wide) the call ran before this launch, or 0.
 __global__ __launch_bounds__(kUfThreads) void k_unionfind(uint8_t *__restrict__ ws, int n, int stage, int staged, int htop,
                                                           int wide) {
     __shared__ uint32_t s_mem[kUfLdsWords];         // uf_lds's nodes; uf_rest: their ranks before
@@ -2490,11 +2504,11 @@ __global__ __launch_bounds__(kUfThreads) void k_unionfind(uint8_t *__restrict__ 
     int32_t *A = arr<int32_t>(ws, pick(dual, I.o_ra, I.o_scratch, 0, 0));
     int32_t *B = arr<int32_t>(ws, pick(dual, I.o_rb, I.o_scratch + 4 * L, 0, 0));
     if (wide && uf_is_wide(I, f.M, f.m)) {
-        uf_rest(ws, I, cnt, f, s_mem, s_wsum, s_any);
+        uf_rest(ws, I, cnt, f, s_mem, s_wsum, s_any, wide);
         return;
     }
     if (f.M <= kUfLdsNodes && f.m <= kUfLdsEdges) {
-        uf_lds<kUfK, false>(f, f.m, f.M, cnt, s_mem, nullptr, nullptr, s_wsum, s_any, live, A, B);
+        uf_lds<kUfK, false>(f, f.m, f.M, cnt, s_mem, nullptr, nullptr, s_wsum, s_any, live, A, B, 0);
         return;
     }
     uf_body(f, cnt, arr<int32_t>(ws, pick(dual, I.o_uf0, I.o_ufT, 0, 0)),
@@ -3747,6 +3761,19 @@ int64_t max_list(const ph_shape *h, int n) {
     return m;
 }
 
+// Wide union-find rounds of a call whose largest instance has mv voxels.  Of noise (the slowest of
+// the inputs tried: ramps, quantised and smoothed noise lose their nodes faster) a round leaves 0.6
+// of the nodes, 4k of 1024^2 pixels after six, and the finish holds kRestNodes: past 2200^2 pixels or
+// 200^3 voxels six leave more, and one workgroup then works out of the workspace (4096^2 99 ms, 256^3
+// 212 ms).  A doubling of the voxels takes 1.3 rounds more to the same nodes; two cost no more, since
+// each also saves the workgroup its share (256^3 with 8, 10, 12, 14, 20 rounds: 7.9, 7.7, 7.5, 7.5,
+// 7.4 ms; 2048^2 with 6, 8, 10, 14: 1.96, 1.90, 1.93, 2.04 ms; 1024^2 with 6, 8, 10: 0.80, 0.81, 0.84).
+int wide_rounds(int64_t mv) {
+    int r = kWideRoundsMin;
+    for (int64_t v = 4 * kWideVoxels; v <= mv; v *= 2) r += 2;
+    return r;
+}
+
 template <int A, int B, typename T = float>
 void launch2d(int64_t tiles, const void *imgs, uint8_t *ws, int n, Luts lut, hipStream_t st, float *grad) {
     hipLaunchKernelGGL((k_classify2d<A, B, T>), dim3((unsigned)tiles), dim3(256), 0, st, (const T *)imgs, ws, n, lut,
@@ -3957,7 +3984,7 @@ int run(int n, const void *d_imgs, const int64_t *d_img_off, const ph_shape *d_s
     // PH_WIDE: the union-finds and the long lists of instances of kWideVoxels or more voxels
     // are spread over the whole GPU (each instance's kernels decide for themselves, from its
     // counts)
-    const int wide = (flags & PH_WIDE) && mv >= kWideVoxels ? 1 : 0;
+    const int wide = (flags & PH_WIDE) && mv >= kWideVoxels ? wide_rounds(mv) : 0;
     // Long lists: a workgroup per run and one merge launch (three under PH_WIDE, for hundreds of
     // runs).  A list of 8193 keys or more needs about 2^15 voxels even of noise (0.33 KEEP edges
     // a pixel); below 2^16 voxels, and in batches that fill the chip with a workgroup a list,
@@ -3981,22 +4008,30 @@ int run(int n, const void *d_imgs, const int64_t *d_img_off, const ph_shape *d_s
     const int staged = any2 && n > kSideBySideInstances ? 1 : 0;
     const unsigned side = htop && (any3 || !staged) ? 2 : 1;
     FC_LAUNCH(K_RESOLVE, hipLaunchKernelGGL(k_resolve, dim3(rblocks, n, side), dim3(256), 0, st, ws, n, 0, staged, htop, wide));
-    auto wide_rounds = [&](int stage, unsigned sides, int kid) -> int {
+    auto run_wide = [&](int stage, unsigned sides, int kid) -> int {
         const unsigned wb = (unsigned)std::min<int64_t>((ml + kWideSeg - 1) / kWideSeg, std::max(1, kWideBlocks / n));
-        // the set-up, the rounds' two phases each, phase 0 once more (the last round's fired edges
-        // dropped, new roots), the nodes left numbered and the segments closed up
-        for (int k = -1; k <= 2 * kWideRounds + 2; ++k) {
-            const int ph = k < 0 ? -1 : (k > 2 * kWideRounds ? k - 2 * kWideRounds + 1 : k & 1);
+        auto pass = [&](int ph, int r) -> int {
             FC_LAUNCH(kid, hipLaunchKernelGGL(k_uf_wide, dim3(wb, n, sides), dim3(kWideThreads), 0, st, ws, n, stage, staged,
-                                              htop, ph, k / 2));
+                                              htop, ph, r, wide));
+            return PH_OK;
+        };
+        int rc = pass(-1, 0);
+        for (int r = 0; r < wide && rc == PH_OK; ++r) {
+            if (r > 0 && r % kWideTags == 0) rc = pass(4, r);
+            if (rc == PH_OK) rc = pass(0, r);
+            if (rc == PH_OK) rc = pass(1, r);
         }
-        return PH_OK;
+        // phase 0 once more (the last round's fired edges dropped, new roots), the nodes left
+        // numbered and the segments closed up
+        for (int ph : {0, 2, 3})
+            if (rc == PH_OK) rc = pass(ph, wide);
+        return rc;
     };
-    if (wide && wide_rounds(0, side, K_UFWIDE) != PH_OK) return PH_EHIP;
+    if (wide && run_wide(0, side, K_UFWIDE) != PH_OK) return PH_EHIP;
     FC_LAUNCH(K_UF, hipLaunchKernelGGL(k_unionfind, dim3(n, side), dim3(kUfThreads), 0, st, ws, n, 0, staged, htop, wide));
     if (htop && staged) {
         FC_LAUNCH(K_RESOLVE_2D, hipLaunchKernelGGL(k_resolve, dim3(rblocks, n), dim3(256), 0, st, ws, n, 1, staged, htop, wide));
-        if (wide && wide_rounds(1, 1, K_UFWIDE_2D) != PH_OK) return PH_EHIP;
+        if (wide && run_wide(1, 1, K_UFWIDE_2D) != PH_OK) return PH_EHIP;
         FC_LAUNCH(K_UF_2D, hipLaunchKernelGGL(k_unionfind, dim3(n), dim3(kUfThreads), 0, st, ws, n, 1, staged, htop, wide));
     }
     if (h1 && any3) {

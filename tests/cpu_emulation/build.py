@@ -4,6 +4,7 @@ The kernels of paper_2606_04801_amd/csrc are compiled as host C++ against the em
 runtime in this folder and linked with driver.cpp.  Variants:
   asan   g++, AddressSanitizer + UBSan (fatal), a redzone around every LDS array
   poison g++ -O2, LDS refilled with a poison byte before every block
+  small_wide  asan, with the sizes of the wide passes lowered by 2^8
   msan   clang++, MemorySanitizer (LDS, workspace and outputs start uninitialised)
   trace  clang++, every load and store of kernel code must hit device memory, LDS or the
          thread's own private memory; EMU_LOCKSTEP=1 switches threads after every access
@@ -34,6 +35,9 @@ VARIANTS = {
     "asan": ("g++", ["-O1", "-g", "-fno-omit-frame-pointer", "-fsanitize=address,undefined",
                      "-fno-sanitize-recover=undefined", "-DEMU_LDS_REDZONE"]),
     "poison": ("g++", ["-O2"]),
+    # PH_WIDE from 2^12 voxels on: an image takes the paths of one 256 times its size
+    "small_wide": ("g++", ["-O1", "-g", "-fno-omit-frame-pointer", "-fsanitize=address,undefined",
+                           "-fno-sanitize-recover=undefined", "-DEMU_LDS_REDZONE", "-DFC_WIDE_SHIFT=8"]),
     "msan": ("/opt/rocm/llvm/bin/clang++", ["-O1", "-g", "-fno-omit-frame-pointer", "-fsanitize=memory",
                                             "-fsanitize-memory-track-origins=2"]),
     # every load and store of kernel code checked against GPU-visible memory (runtime.cpp)

@@ -220,9 +220,10 @@ int main(int argc, char **argv) {
         for (int i = 0; i < n; ++i) {
             const int32_t *c = (const int32_t *)(ws + cn) + i * fc::CNT_WORDS;
             const fc::Inst &I = ((const fc::Inst *)ws)[i];
-            fprintf(stderr, "stats %d N %ld keepE %d keepF %d minima %d roots %d rounds0 %d roundsT %d seq %d\n", i,
+            fprintf(stderr, "stats %d N %ld keepE %d keepF %d minima %d roots %d rounds0 %d roundsT %d seq %d "
+                            "left0 %d leftT %d\n", i,
                     (long)I.N, c[fc::CNT_E], c[fc::CNT_F], c[fc::CNT_M0], c[fc::CNT_MT], c[fc::CNT_ROUNDS0],
-                    c[fc::CNT_ROUNDST], c[fc::CNT_SEQ]);
+                    c[fc::CNT_ROUNDST], c[fc::CNT_SEQ], c[fc::CNT_WNODES0], c[fc::CNT_WNODEST]);
         }
     }
 

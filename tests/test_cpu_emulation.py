@@ -438,3 +438,51 @@ def test_dual_node_runs_under_a_list_fraction(variant):
     (got, st), = run(emu_build.build(variant), [a], flags=3 | 1 << 8)[0]
     assert st == 0 and diff_pairs(got, oracle.diagram(a)) is None
     assert (got["dim"] == 1).sum() == 51 * 51
+
+
+def run_stats(monkeypatch, exe, imgs, **kw):
+    """run(), and per instance the driver's work counters as a dict."""
+    err = []
+    real = subprocess.run
+
+    def keep(*a, **k):
+        r = real(*a, **k)
+        err.append(r.stderr)
+        return r
+    monkeypatch.setenv("EMU_STATS", "1")
+    monkeypatch.setattr(subprocess, "run", keep)
+    out, _ = run(exe, imgs, **kw)
+    stats = []
+    for line in err[-1].splitlines():
+        if line.startswith("stats "):
+            w = line.split()[2:]
+            stats.append({w[k]: int(w[k + 1]) for k in range(0, len(w), 2)})
+    return out, stats
+
+
+@pytest.mark.parametrize("shape", [(256, 256), (40, 41, 42)])
+def test_wide_rounds_leave_what_the_finish_holds(monkeypatch, shape):
+    """Noise of 2^24 and more voxels under PH_WIDE (the build's limits are lowered 256 times): the
+    wide rounds leave no more nodes than the finish in one workgroup holds (20,000), whatever the
+    size, with the oracle's pairs under the sanitizers."""
+    img = S.uniform(shape, 31)
+    ((got, st),), (w,) = run_stats(monkeypatch, emu_build.build("small_wide"), [img], flags=3 | 64)
+    assert st == 0 and diff_pairs(got, oracle.diagram(img)) is None
+    assert w["minima"] > 20440 >> 8 and 0 < w["left0"] <= 20000 >> 8 and w["leftT"] <= 20000 >> 8, w
+
+
+def test_wide_rounds_with_nodes_left(monkeypatch):
+    """What the wide rounds leave where every merge waits for the one before it: more nodes than the
+    finish holds (the rounds go on in the workspace), and fewer, but more than its rounds merge
+    (the sequential finish on the packed edges).  The same pairs as without PH_WIDE and the oracle's."""
+    exe = emu_build.build("small_wide")
+    rows = np.full((16, 401), 9.0, np.float32)
+    rows[0::2] = staircase(200)
+    pits = np.full((50, 135), 3.0, np.float32)
+    pits[0, :], pits[2:48:4, 5:130:30] = staircase(67), 2.5      # (the pits die in the first round)
+    for img, more in ((rows, True), (pits, False)):
+        ((got, st),), (w,) = run_stats(monkeypatch, exe, [img], flags=3 | 64)
+        assert st == 0 and diff_pairs(got, oracle.diagram(img)) is None
+        assert w["minima"] > 20440 >> 8 and w["seq"] > 0, w
+        assert (w["left0"] > 20000 >> 8) == more and w["left0"] > 48, w
+        assert diff_pairs(got, run(exe, [img])[0][0][0]) is None

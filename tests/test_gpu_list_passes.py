@@ -77,3 +77,12 @@ def test_multi_run_volume_with_h1():
     got = fc.ph_diagram(torch.from_numpy(small).to(DEV), flags=fl).numpy()
     assert diff_pairs(got[got["dim"] != 1], oracle.diagram(small, dims=(0, 2))) is None
     assert (got["dim"] == 1).any()
+
+
+def test_wide_rounds_past_a_clearing():
+    """2^22 pixels of noise under PH_WIDE: eight wide rounds, with the nodes' words cleared after
+    seven, and a last sort pass over groups of many runs."""
+    img = S.uniform((2100, 2050), 50)
+    print("wide", img.shape, flush=True)
+    got = fc.ph_diagram(torch.from_numpy(img).to(DEV), flags=fc.PH_H0 | fc.PH_HTOP | fc.PH_WIDE).numpy()
+    assert diff_pairs(got, oracle.diagram(img)) is None
