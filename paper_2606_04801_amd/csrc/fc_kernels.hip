@@ -1376,21 +1376,11 @@ __device__ __forceinline__ void sort_run(uint8_t *__restrict__ ws, const Inst &I
     __syncthreads();                             // s is free for the next run
 }
 
-// Merge passes k_sort_merge makes over a list of m keys, of at most `passes` launched
-// (0: one workgroup sorts the list): one pass up to 16 runs, two up to 64, else as many as are
-// launched.  A key's place in one pass takes one binary search in each other run of its group,
-// so the searches, 12 instructions a step, bound a long list: noise 128^3 (690k edges in 338
-// runs, and the other lists) takes 319 us in two passes over 19 runs each, 202 us in three over 7.
-__device__ __forceinline__ int sort_passes(int runs, int passes) {
-    const int want = runs <= 1 ? 0 : (runs <= 16 ? 1 : (runs <= 64 ? 2 : 3));
-    return want < passes ? want : passes;
-}
-
 // The sorts of every instance in one launch: grid (R, n, 4), blockIdx.y = instance, z = list, so
 // the lists of all instances are sorted side by side.  Each list has a scratch of its own: the
 // sort scratch (KEEP edges), the live-edge arrays (KEEP squares), the root arrays (H0 nodes) and
 // the edges' endpoint arrays (dual nodes), all written only afterwards.
-// rl: keys of a run, at most kSortCap (all of it where one workgroup sorts the list).
+// rl: keys of a run at most, of kSortCap at most (all of it where one workgroup sorts the list).
 // passes: k_sort_merge launches that follow (0: none; a long list is merged here).
 __global__ __launch_bounds__(kSortThreads, 8) void k_sort_lists(uint8_t *__restrict__ ws, int n, int rl, int passes) {
     __shared__ uint64_t s[2 * pad_size(kSortCap)];
@@ -1403,11 +1393,10 @@ __global__ __launch_bounds__(kSortThreads, 8) void k_sort_lists(uint8_t *__restr
     lds_barrier();
     if (s_flag) return;
     const int m = L.m;                           // (a list has fewer than 2^29 keys)
-    // runs of equal length for k_sort_merge (a short last one's keys would have long searches in
-    // all the others); merged here they are whole tiles
-    const int runs = (m + rl - 1) / rl, run = passes > 0 && runs > 0 ? (m + runs - 1) / runs : rl;
-    const int base0 = blockIdx.x * run;
-    if ((int)blockIdx.x >= runs || base0 >= m) return;
+    // merged here the runs are whole tiles of rl keys
+    SortCut cut = sort_cut(m, rl, passes);
+    if (passes == 0) { cut.len = rl; cut.rem = 0; }
+    if ((int)blockIdx.x >= cut.runs) return;
     if (m > L.cap) { if (threadIdx.x == 0) set_err(cnt, PH_EINTERNAL); return; }
     // the keys of one run by the fewest a thread that hold it
     auto sort = [&](int64_t base, int len, uint64_t *out, bool whole) {
@@ -1416,13 +1405,12 @@ __global__ __launch_bounds__(kSortThreads, 8) void k_sort_lists(uint8_t *__restr
     };
     // an odd number of merge passes ends in dst when the runs start from the scratch.  With one
     // workgroup a list they start in place (as sorted: a dual node's complemented)
-    const int np = sort_passes(runs, passes);
-    uint64_t *out = np & 1 ? L.scr : L.dst;
-    for (int64_t base = base0; base < m; base += (int64_t)gridDim.x * run) {
-        const int len = (int)((m - base) < run ? (m - base) : run);
-        sort(base, len, out, runs == 1);
+    uint64_t *out = cut.passes & 1 ? L.scr : L.dst;
+    for (int j = blockIdx.x; j < cut.runs; j += gridDim.x) {
+        const int base = cut.start(j), end = j + 1 < cut.runs ? cut.start(j + 1) : m;
+        sort(base, end - base, out, cut.runs == 1);
     }
-    if (runs == 1) return;
+    if (cut.runs == 1) return;
     if (passes > 0) return;
     // one workgroup a list: merge pairs of runs, a tile of kTile outputs at a time through LDS
     // (merge path: each tile's share of the two runs by one binary search, each thread's four
@@ -1432,7 +1420,7 @@ __global__ __launch_bounds__(kSortThreads, 8) void k_sort_lists(uint8_t *__restr
     uint64_t *b = L.scr;
     int *s_split = (int *)(s + kTile);               // split points of a batch of tiles
     static_assert(2 * pad_size(kSortCap) >= kTile + (kSortThreads + 2) / 2 && kSortCap == kTile, "tile and split points fit");
-    for (int wd = run; wd < m; wd <<= 1) {
+    for (int wd = rl; wd < m; wd <<= 1) {
         const int ntiles = (m + kTile - 1) / kTile;
         for (int tb = 0; tb < ntiles; tb += kSortThreads) {
             const int nb = ntiles - tb < kSortThreads ? ntiles - tb : kSortThreads;
@@ -1501,8 +1489,7 @@ __global__ __launch_bounds__(kSortThreads, 8) void k_sort_lists(uint8_t *__restr
 }
 
 // Merge pass of the lists longer than one run: grid (blocks, n, 4).  The runs are taken in
-// groups (all of them in one pass, or a root of their number in each of two or three); a
-// key's place among its group is its own in its run plus the number of smaller keys in each
+// groups (sort_cut); a key's place among its group is its own in its run plus the number of smaller keys in each
 // other run.  A workgroup places kMergeThreads consecutive keys of one run at a time: the part
 // of another run their searches can end in lies between the places of the first and the last of
 // them, about as many keys as they are, found by two lanes for 32 runs at once; those parts
@@ -1528,7 +1515,8 @@ __device__ __forceinline__ int keys_below(const uint64_t *a, int n, uint64_t k) 
 __global__ __launch_bounds__(kMergeThreads) void k_sort_merge(uint8_t *__restrict__ ws, int n, int run_max,
                                                              int passes, int pass) {
     __shared__ uint64_t s_win[kMergeWindow + 1];
-    __shared__ int s_lo[kMergeRuns], s_at[kMergeRuns + 1];
+    __shared__ int s_lo[kMergeRuns], s_at[kMergeRuns + 1];   // a window's first key, its place among the windows'
+    __shared__ int s_key[kMergeRuns];            // a window's first key in the list, less that place
     __shared__ int s_flag;
     const int i = blockIdx.y, w = blockIdx.z;
     const Inst I = ((const Inst *)ws)[i];           // one batch of loads, before any atomic
@@ -1539,38 +1527,34 @@ __global__ __launch_bounds__(kMergeThreads) void k_sort_merge(uint8_t *__restric
     if (threadIdx.x == 0) s_flag = failed(cnt);
     lds_barrier();
     if (s_flag) return;
-    const int runs = (m + run_max - 1) / run_max, run = (m + runs - 1) / runs;   // as k_sort_lists cut them
-    const int np = sort_passes(runs, passes);
+    const SortCut cut = sort_cut(m, run_max, passes);   // as k_sort_lists cut it
+    const int np = cut.passes;
     if (pass >= np) return;
-    int fan = runs;                              // runs of a group: the smallest f with f^np >= runs
-    if (np == 2)
-        for (fan = 2; fan * fan < runs;) ++fan;
-    if (np == 3)
-        for (fan = 2; fan * fan * fan < runs;) ++fan;
-    int rl = run;                                // keys of a run, a group
-    for (int p = 0; p < pass; ++p) rl *= fan;
-    const int gl = pass == np - 1 ? m : rl * fan;
+    int u = 1;                                   // first runs in one sorted so far
+    for (int p = 0; p < pass; ++p) u *= cut.fan;
+    const int gu = pass == np - 1 ? cut.runs : u * cut.fan;   // ... in a group
     const uint64_t *a = (np - pass) & 1 ? L.scr : L.dst;
     uint64_t *b = (np - pass) & 1 ? L.dst : L.scr;
-    const int steps = (rl + kMergeThreads - 1) / kMergeThreads, all = (m + rl - 1) / rl * steps;
+    const int steps = (cut.start(u) + kMergeThreads - 1) / kMergeThreads, all = cut.runs / u * steps;
     for (int c = blockIdx.x; c < all; c += gridDim.x) {
-        const int r0 = c / steps * rl, t0 = r0 + c % steps * kMergeThreads;
-        if (t0 >= m) continue;                   // (past the end of a short last run)
-        const int g0 = r0 / gl * gl, g1 = g0 + gl < m ? g0 + gl : m;
-        const int r1 = r0 + rl < g1 ? r0 + rl : g1, tl = t0 + kMergeThreads <= r1 ? t0 + kMergeThreads - 1 : r1 - 1;
+        const int own = c / steps * u, jg = own / gu * gu;   // this workgroup's run, its group's first
+        const int r0 = cut.start(own), r1 = cut.start(own + u), t0 = r0 + c % steps * kMergeThreads;
+        if (t0 >= r1) continue;                  // (past the end of a run a key shorter)
+        const int g0 = cut.start(jg), tl = t0 + kMergeThreads <= r1 ? t0 + kMergeThreads - 1 : r1 - 1;
         const int t = t0 + (int)threadIdx.x;
         const uint64_t k = t <= tl ? a[t] : 0;
         const uint64_t kfirst = a[t0], klast = a[tl];
         int place = t - r0;                      // smaller keys of the group
         bool first = t > tl || t == r0 || (a[t - 1] >> kCodeBits) != (k >> kCodeBits);
-        for (int q = g0; q < g1; q += kMergeRuns * rl) {
+        for (int q = jg; q < jg + gu; q += kMergeRuns * u) {
             __syncthreads();                     // the last runs' windows have been read
             static_assert(2 * kMergeRuns == 64, "one wave finds the windows");
             if (threadIdx.x < 2 * kMergeRuns) {
                 // run j's window: from the key before the first one's place (the neighbour that
                 // may be of its vertex) to the last one's place; empty for the keys' own run
-                const int j = threadIdx.x & (kMergeRuns - 1), qs = q + j * rl;
-                const int len = qs < g1 && qs != r0 ? (g1 - qs < rl ? g1 - qs : rl) : 0;
+                const int j = threadIdx.x & (kMergeRuns - 1), jr = q + j * u;
+                const bool in = jr < jg + gu && jr != own;
+                const int qs = in ? cut.start(jr) : 0, len = in ? cut.start(jr + u) - qs : 0;
                 int x = keys_below(a + qs, len, threadIdx.x < kMergeRuns ? kfirst : klast);
                 if (threadIdx.x < kMergeRuns && x > 0) --x;
                 const int end = __shfl(x, j + kMergeRuns, 64);
@@ -1579,11 +1563,12 @@ __global__ __launch_bounds__(kMergeThreads) void k_sort_merge(uint8_t *__restric
                 if (threadIdx.x < kMergeRuns) {
                     s_lo[j] = x;
                     s_at[j] = upto - size;
+                    s_key[j] = qs + x - (upto - size);
                     if (j == kMergeRuns - 1) s_at[kMergeRuns] = upto;
                 }
             }
             __syncthreads();
-            const int nr = (g1 - q + rl - 1) / rl < kMergeRuns ? (g1 - q + rl - 1) / rl : kMergeRuns;
+            const int nr = (jg + gu - q) / u < kMergeRuns ? (jg + gu - q) / u : kMergeRuns;
             // the windows one after another, kMergeWindow keys at a time (once, but for the keys
             // of a short run); a key's places in the parts of a window add up
             const int total = s_at[kMergeRuns];
@@ -1606,7 +1591,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_sort_merge(uint8_t *__restric
                         int j = 0;               // the last run whose window starts at or before y
 #pragma unroll
                         for (int st = kMergeRuns / 2; st > 0; st >>= 1) j = s_at[j + st] <= y ? j + st : j;
-                        const int z = y < vend ? q + j * rl + s_lo[j] + (y - s_at[j]) : t0;
+                        const int z = y < vend ? s_key[j] + y : t0;
                         x[u] = a[z];
                     }
 #pragma unroll

@@ -80,9 +80,10 @@ def test_multi_run_volume_with_h1():
 
 
 def test_wide_rounds_past_a_clearing():
-    """2^22 pixels of noise under PH_WIDE: eight wide rounds, with the nodes' words cleared after
-    seven, and a last sort pass over groups of many runs."""
-    img = S.uniform((2100, 2050), 50)
+    """2^22 pixels of noise under PH_WIDE, against the call without the flag (one workgroup's union-find
+    out of the workspace, runs merged in one pass): eight wide rounds, with the nodes' words cleared
+    after seven, and merges in three passes."""
+    img = torch.from_numpy(S.uniform((2100, 2050), 50)).to(DEV)
     print("wide", img.shape, flush=True)
-    got = fc.ph_diagram(torch.from_numpy(img).to(DEV), flags=fc.PH_H0 | fc.PH_HTOP | fc.PH_WIDE).numpy()
-    assert diff_pairs(got, oracle.diagram(img)) is None
+    got = fc.ph_diagram(img, flags=fc.PH_H0 | fc.PH_HTOP | fc.PH_WIDE).numpy()
+    assert len(got) > 10 ** 6 and diff_pairs(got, fc.ph_diagram(img).numpy()) is None
