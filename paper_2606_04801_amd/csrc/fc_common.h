@@ -180,6 +180,12 @@ FC_HD int64_t list_cap(int64_t worst, int k) {
     return c < kListFloor ? kListFloor : (c > worst ? worst : c);
 }
 
+// The sizes from which the whole GPU works on one instance.  A host build of the tests lowers them by
+// FC_WIDE_SHIFT powers of two, so that small images take every path of large ones.
+#ifndef FC_WIDE_SHIFT
+#define FC_WIDE_SHIFT 0
+#endif
+
 // How a long list of m keys is cut into sorted runs of up to `most` keys and merged in `passes`
 // passes (as many as pay, of those launched), each over groups of `fan` of the last one's results, the
 // last over all that are left.  One pass up to 16 runs, two up to 64, else three: a key's place in
@@ -188,24 +194,35 @@ FC_HD int64_t list_cap(int64_t worst, int k) {
 // takes 319 us in two passes over 19 runs each, 202 us in three over 7.
 // All runs have the same length (but for one key), and every group as many of them: a key of a short
 // run or group has long windows in all the others, so a workgroup with its 256 keys goes through
-// the whole list (5.2M keys, a last group of one run: 11.4 ms a pass, 0.5 ms so).
+// the whole list (4096^2 noise under PH_WIDE, a last group of one run of 78 keys: a pass of 11.4 ms,
+// else 0.6 ms).
+// The searches of a pass grow with the runs of a group, so with the list: past kMergeRunsOnce or
+// kMergeRunsThrice runs each of the `blocks` workgroups of a list takes an equal share of it, sorts
+// its runs and merges them in pairs (a hundred instructions a key and doubling), and the passes
+// merge the shares.  Noise in one pass, 2048^2: 81 -> 74 ms a call, 4096^2: 500 -> 313, 256^3: 679 ->
+// 465 (two launched passes: 69, 297 and 450, but every smooth image would wait 4 us for an idle
+// one); in three, 4096^2: 7.6 -> 7.0 ms, 256^3: 7.5 -> 6.8, 512^3: 89 -> 72 (four or five launched
+// passes: 7.3, 7.1, 75).
+constexpr int kMergeRunsOnce = 256 >> FC_WIDE_SHIFT;     // runs merged at most in one pass, where one is
+constexpr int kMergeRunsThrice = 512 >> FC_WIDE_SHIFT;   // launched; in three
 struct SortCut {
     int m, runs, passes, fan;
     int len, rem;                    // the first rem runs have len + 1 keys, the others len
     FC_HD int start(int j) const { return j * len + (j < rem ? j : rem); }   // first key of run j <= runs
 };
-FC_HD SortCut sort_cut(int m, int most, int launched) {
+FC_HD SortCut sort_cut(int m, int most, int launched, int blocks) {
     SortCut c;
     c.m = m;
-    const int least = (m + most - 1) / most, want = least <= 1 ? 0 : (least <= 16 ? 1 : (least <= 64 ? 2 : 3));
+    c.runs = (m + most - 1) / most;
+    if (launched > 0 && c.runs > (launched < 3 ? kMergeRunsOnce : kMergeRunsThrice)) c.runs = blocks;
+    const int want = c.runs <= 1 ? 0 : (c.runs <= 16 ? 1 : (c.runs <= 64 ? 2 : 3));
     c.passes = want < launched ? want : launched;
-    c.fan = least;
-    c.runs = least;
+    c.fan = c.runs;
     if (c.passes >= 2) {
-        // the smallest fan with fan^passes >= least; the last pass's groups no more than needed
-        for (c.fan = 2; c.fan * c.fan * (c.passes == 3 ? c.fan : 1) < least;) ++c.fan;
+        // the smallest fan with fan^passes >= runs; the last pass's groups no more than needed
+        for (c.fan = 2; c.fan * c.fan * (c.passes == 3 ? c.fan : 1) < c.runs;) ++c.fan;
         const int unit = c.passes == 3 ? c.fan * c.fan : c.fan;
-        c.runs = (least + unit - 1) / unit * unit;
+        c.runs = (c.runs + unit - 1) / unit * unit;
     }
     c.len = c.runs > 0 ? m / c.runs : 0;
     c.rem = c.runs > 0 ? m % c.runs : 0;

@@ -53,11 +53,6 @@ constexpr int kUfThreads = 1024;
 constexpr int kUfLdsNodes = 40000;         // union-find nodes kept in LDS (a word each)
 constexpr int kUfK = 4;                    // edges a thread of a batch of the union-find
 constexpr int kUfLdsWords = 40600;         // the union-find's LDS, int32 (160 KiB less its other shared words)
-// The sizes of the wide passes.  The tests' host build lowers them by FC_WIDE_SHIFT powers of two, so
-// that small images take every path of large ones.
-#ifndef FC_WIDE_SHIFT
-#define FC_WIDE_SHIFT 0
-#endif
 constexpr int kUfWideNodes = 20440 >> FC_WIDE_SHIFT;   // the wide rounds (PH_WIDE) take forests of more nodes
 constexpr int kSortThreads = 1024;
 constexpr int kSortCap = 4096;             // keys sorted entirely in LDS (two buffers of 34 KiB)
@@ -1214,7 +1209,7 @@ __device__ __forceinline__ int block_flag_scan(int flag, int *s_wsum, int *total
 // 512 images of 64^2 to 512^2 89 -> 44 us (with a fourth list, the dual nodes).
 // Longer lists are sorted in runs.  With one workgroup a list (R = 1) the runs, of kSortCap keys,
 // are merged pairwise through LDS tiles; with more, each run, of up to kSortRun keys, has a
-// workgroup of its own and k_sort_merge merges them.
+// workgroup of its own (or each workgroup a share of many runs) and k_sort_merge merges them.
 // Keys are unique (the pixel and code are part of them), so every order is total, and no key
 // (and no complement of a dual node's) is ~0, the padding.
 
@@ -1376,51 +1371,15 @@ __device__ __forceinline__ void sort_run(uint8_t *__restrict__ ws, const Inst &I
     __syncthreads();                             // s is free for the next run
 }
 
-// The sorts of every instance in one launch: grid (R, n, 4), blockIdx.y = instance, z = list, so
-// the lists of all instances are sorted side by side.  Each list has a scratch of its own: the
-// sort scratch (KEEP edges), the live-edge arrays (KEEP squares), the root arrays (H0 nodes) and
-// the edges' endpoint arrays (dual nodes), all written only afterwards.
-// rl: keys of a run at most, of kSortCap at most (all of it where one workgroup sorts the list).
-// passes: k_sort_merge launches that follow (0: none; a long list is merged here).
-__global__ __launch_bounds__(kSortThreads, 8) void k_sort_lists(uint8_t *__restrict__ ws, int n, int rl, int passes) {
-    __shared__ uint64_t s[2 * pad_size(kSortCap)];
-    __shared__ int s_flag;
-    const int i = blockIdx.y, w = blockIdx.z;
-    const Inst I = ((const Inst *)ws)[i];           // one batch of loads, before any atomic
-    int32_t *cnt = (int32_t *)(ws + off_cnt(n)) + i * CNT_WORDS;
-    const SortLists L = sort_lists_of(ws, I, cnt, w);
-    if (threadIdx.x == 0) s_flag = failed(cnt);
-    lds_barrier();
-    if (s_flag) return;
-    const int m = L.m;                           // (a list has fewer than 2^29 keys)
-    // merged here the runs are whole tiles of rl keys
-    SortCut cut = sort_cut(m, rl, passes);
-    if (passes == 0) { cut.len = rl; cut.rem = 0; }
-    if ((int)blockIdx.x >= cut.runs) return;
-    if (m > L.cap) { if (threadIdx.x == 0) set_err(cnt, PH_EINTERNAL); return; }
-    // the keys of one run by the fewest a thread that hold it
-    auto sort = [&](int64_t base, int len, uint64_t *out, bool whole) {
-        if (len <= 2 * kSortThreads) sort_run<2>(ws, I, cnt, w, L, base, len, out, whole, s);
-        else sort_run<4>(ws, I, cnt, w, L, base, len, out, whole, s);
-    };
-    // an odd number of merge passes ends in dst when the runs start from the scratch.  With one
-    // workgroup a list they start in place (as sorted: a dual node's complemented)
-    uint64_t *out = cut.passes & 1 ? L.scr : L.dst;
-    for (int j = blockIdx.x; j < cut.runs; j += gridDim.x) {
-        const int base = cut.start(j), end = j + 1 < cut.runs ? cut.start(j + 1) : m;
-        sort(base, end - base, out, cut.runs == 1);
-    }
-    if (cut.runs == 1) return;
-    if (passes > 0) return;
-    // one workgroup a list: merge pairs of runs, a tile of kTile outputs at a time through LDS
-    // (merge path: each tile's share of the two runs by one binary search, each thread's four
-    // outputs by another in LDS)
+// Merge the sorted runs of wd keys (a power of two from half a tile on; the last may be shorter) of
+// a[0, m) in pairs, by the whole block, back and forth between a and b: a tile of kTile outputs at a
+// time through LDS (merge path: each tile's share of the two runs by one binary search, each
+// thread's four outputs by another in LDS).  Returns where the sorted keys end up.
+__device__ __forceinline__ uint64_t *merge_pairs(uint64_t *a, uint64_t *b, int m, int wd0, uint64_t *s) {
     constexpr int kTile = 4 * kSortThreads;
-    const uint64_t *a = L.dst;
-    uint64_t *b = L.scr;
     int *s_split = (int *)(s + kTile);               // split points of a batch of tiles
     static_assert(2 * pad_size(kSortCap) >= kTile + (kSortThreads + 2) / 2 && kSortCap == kTile, "tile and split points fit");
-    for (int wd = rl; wd < m; wd <<= 1) {
+    for (int wd = wd0; wd < m; wd <<= 1) {
         const int ntiles = (m + kTile - 1) / kTile;
         for (int tb = 0; tb < ntiles; tb += kSortThreads) {
             const int nb = ntiles - tb < kSortThreads ? ntiles - tb : kSortThreads;
@@ -1474,10 +1433,57 @@ __global__ __launch_bounds__(kSortThreads, 8) void k_sort_lists(uint8_t *__restr
                 __syncthreads();
             }
         }
-        const uint64_t *t = a;
+        uint64_t *t = a;
         a = b;
-        b = (uint64_t *)t;
+        b = t;
     }
+    return a;
+}
+
+// The sorts of every instance in one launch: grid (R, n, 4), blockIdx.y = instance, z = list, so
+// the lists of all instances are sorted side by side.  Each list has a scratch of its own: the
+// sort scratch (KEEP edges), the live-edge arrays (KEEP squares), the root arrays (H0 nodes) and
+// the edges' endpoint arrays (dual nodes), all written only afterwards.
+// rl: keys of a run at most, of kSortCap at most (all of it where one workgroup sorts the list).
+// passes: k_sort_merge launches that follow (0: none; a long list is merged here).
+__global__ __launch_bounds__(kSortThreads, 8) void k_sort_lists(uint8_t *__restrict__ ws, int n, int rl, int passes) {
+    __shared__ uint64_t s[2 * pad_size(kSortCap)];
+    __shared__ int s_flag;
+    const int i = blockIdx.y, w = blockIdx.z;
+    const Inst I = ((const Inst *)ws)[i];           // one batch of loads, before any atomic
+    int32_t *cnt = (int32_t *)(ws + off_cnt(n)) + i * CNT_WORDS;
+    const SortLists L = sort_lists_of(ws, I, cnt, w);
+    if (threadIdx.x == 0) s_flag = failed(cnt);
+    lds_barrier();
+    if (s_flag) return;
+    const int m = L.m;                           // (a list has fewer than 2^29 keys)
+    SortCut cut = sort_cut(m, rl, passes, gridDim.x);
+    if (passes == 0) { cut.runs = 1; cut.len = m; cut.rem = 0; }
+    if (m <= 0 || (int)blockIdx.x >= cut.runs) return;
+    if (m > L.cap) { if (threadIdx.x == 0) set_err(cnt, PH_EINTERNAL); return; }
+    // the keys of one run by the fewest a thread that hold it
+    auto sort = [&](int64_t base, int len, uint64_t *out, bool whole) {
+        if (len <= 2 * kSortThreads) sort_run<2>(ws, I, cnt, w, L, base, len, out, whole, s);
+        else sort_run<4>(ws, I, cnt, w, L, base, len, out, whole, s);
+    };
+    // an odd number of merge passes ends in dst when the runs start from the scratch
+    uint64_t *to = cut.passes & 1 ? L.scr : L.dst, *other = cut.passes & 1 ? L.dst : L.scr;
+    const uint64_t *a = L.dst;
+    for (int j = blockIdx.x; j < cut.runs; j += gridDim.x) {
+        const int base = cut.start(j), len = (j + 1 < cut.runs ? cut.start(j + 1) : m) - base;
+        if (len <= rl) {
+            sort(base, len, to, cut.runs == 1);
+            continue;
+        }
+        // merged here: runs of rl keys (as sorted: a dual node's complemented), which start where
+        // they end after all merges, or in the other array; a whole list starts in place
+        int merges = 0;
+        for (int wd = rl; wd < len; wd *= 2) ++merges;
+        uint64_t *from = cut.runs > 1 && (merges & 1) ? other : to;
+        for (int k = 0; k < len; k += rl) sort(base + k, len - k < rl ? len - k : rl, from, false);
+        a = merge_pairs(from + base, (from == to ? other : to) + base, len, rl, s);
+    }
+    if (cut.runs > 1 || m <= rl) return;
     // a holds the sorted keys; in dst they are stored over themselves, so the neighbour's
     // vertex is read before the barrier that precedes the stores of a chunk
     for (int t0 = 0; t0 < m; t0 += blockDim.x) {
@@ -1489,8 +1495,8 @@ __global__ __launch_bounds__(kSortThreads, 8) void k_sort_lists(uint8_t *__restr
 }
 
 // Merge pass of the lists longer than one run: grid (blocks, n, 4).  The runs are taken in
-// groups (sort_cut); a key's place among its group is its own in its run plus the number of smaller keys in each
-// other run.  A workgroup places kMergeThreads consecutive keys of one run at a time: the part
+// groups (sort_cut); a key's place among its group is its own in its run plus the number of
+// smaller keys in each other run.  A workgroup places kMergeThreads consecutive keys of one run at a time: the part
 // of another run their searches can end in lies between the places of the first and the last of
 // them, about as many keys as they are, found by two lanes for 32 runs at once; those parts
 // are loaded into LDS together and searched there, four at a time (searched in global memory
@@ -1512,7 +1518,7 @@ __device__ __forceinline__ int keys_below(const uint64_t *a, int n, uint64_t k) 
     return lo;
 }
 
-__global__ __launch_bounds__(kMergeThreads) void k_sort_merge(uint8_t *__restrict__ ws, int n, int run_max,
+__global__ __launch_bounds__(kMergeThreads) void k_sort_merge(uint8_t *__restrict__ ws, int n, int run_max, int blocks,
                                                              int passes, int pass) {
     __shared__ uint64_t s_win[kMergeWindow + 1];
     __shared__ int s_lo[kMergeRuns], s_at[kMergeRuns + 1];   // a window's first key, its place among the windows'
@@ -1527,7 +1533,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_sort_merge(uint8_t *__restric
     if (threadIdx.x == 0) s_flag = failed(cnt);
     lds_barrier();
     if (s_flag) return;
-    const SortCut cut = sort_cut(m, run_max, passes);   // as k_sort_lists cut it
+    const SortCut cut = sort_cut(m, run_max, passes, blocks);   // as k_sort_lists cut it
     const int np = cut.passes;
     if (pass >= np) return;
     int u = 1;                                   // first runs in one sorted so far
@@ -3970,19 +3976,19 @@ int run(int n, const void *d_imgs, const int64_t *d_img_off, const ph_shape *d_s
     // are spread over the whole GPU (each instance's kernels decide for themselves, from its
     // counts)
     const int wide = (flags & PH_WIDE) && mv >= kWideVoxels ? wide_rounds(mv) : 0;
-    // Long lists: a workgroup per run and one merge launch (three under PH_WIDE, for hundreds of
-    // runs).  A list of 8193 keys or more needs about 2^15 voxels even of noise (0.33 KEEP edges
+    // Long lists: a workgroup per run or share and one merge launch (three under PH_WIDE, for
+    // hundreds of runs).  A list of 8193 keys or more needs about 2^15 voxels even of noise (0.33 KEEP edges
     // a pixel); below 2^16 voxels, and in batches that fill the chip with a workgroup a list,
     // the one workgroup merges its two or three runs itself, which saves the launch.
     const bool multi = mv >= kSortMultiVoxels && n <= kSortMultiInstances;
     const int passes = !multi ? 0 : (wide ? 3 : 1);
     const int rl = multi ? kSortRun : kSortCap;
     const int64_t runs = (ml + rl - 1) / rl;
-    const unsigned sr = multi ? (unsigned)std::min<int64_t>(runs, std::max<int64_t>(1, 256 / n)) : 1u;
+    const unsigned sr = multi ? (unsigned)std::min<int64_t>(runs, std::max<int64_t>(1, (wide ? 512 : 256) / n)) : 1u;
     FC_LAUNCH(K_SORT, hipLaunchKernelGGL(k_sort_lists, dim3(sr, n, 4), dim3(kSortThreads), 0, st, ws, n, rl, passes));
     for (int p = 0; p < passes; ++p) {
         const unsigned mb = (unsigned)std::min<int64_t>((ml + kMergeThreads - 1) / kMergeThreads, std::max<int64_t>(16, (wide ? 1024 : 256) / n));
-        FC_LAUNCH(K_SORTMERGE, hipLaunchKernelGGL(k_sort_merge, dim3(mb, n, 4), dim3(kMergeThreads), 0, st, ws, n, rl, passes, p));
+        FC_LAUNCH(K_SORTMERGE, hipLaunchKernelGGL(k_sort_merge, dim3(mb, n, 4), dim3(kMergeThreads), 0, st, ws, n, rl, (int)sr, passes, p));
     }
     // volumes: the dual (resolve, union-find) beside H0; images: the dual after H0
     // T's H0 is the V top; 3D H1 needs the squares the dual union-find pairs

@@ -486,3 +486,13 @@ def test_wide_rounds_with_nodes_left(monkeypatch):
         assert w["minima"] > 20440 >> 8 and w["seq"] > 0, w
         assert (w["left0"] > 20000 >> 8) == more and w["left0"] > 48, w
         assert diff_pairs(got, run(exe, [img])[0][0][0]) is None
+
+
+def test_sort_shares_merged_by_their_workgroups():
+    """Lists of more runs than one merge pass takes (that limit lowered 256 times): eight workgroups a
+    list in a batch of 32, each merging its share of the runs before the one pass."""
+    imgs = [S.uniform((256, 260), 41), S.uniform((30, 48, 46), 42), S.levels((250, 270), 5, 43)]
+    imgs += [S.levels((4, 5), 3, 50 + k) for k in range(29)]
+    out, _ = run(emu_build.build("small_wide"), imgs, mode=1)
+    for img, (got, st) in zip(imgs, out):
+        assert st == 0 and diff_pairs(got, oracle.diagram(img)) is None, img.shape

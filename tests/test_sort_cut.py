@@ -15,13 +15,17 @@ PROGRAM = r"""
 #include "fc_common.h"
 #include <cstdio>
 #include <cstdlib>
-#define CHECK(x) do { if (!(x)) { printf("m %d most %d launched %d: %s\n", m, most, launched, #x); return 1; } } while (0)
-static int check(int m, int most, int launched) {
-    const fc::SortCut c = fc::sort_cut(m, most, launched);
+#include <initializer_list>
+#define CHECK(x) do { if (!(x)) { printf("m %d most %d launched %d blocks %d: %s\n", m, most, launched, blocks, #x); return 1; } } while (0)
+static int check(int m, int most, int launched, int blocks) {
+    const fc::SortCut c = fc::sort_cut(m, most, launched, blocks);
     if (m <= 0) { CHECK(c.runs == 0 && c.passes == 0); return 0; }
-    CHECK(c.runs >= 1 && c.passes >= 0 && c.passes <= launched && (c.runs == 1) == (m <= most));
-    CHECK((c.passes == 0) == (c.runs == 1 || launched == 0));
-    CHECK(c.start(0) == 0 && c.start(c.runs) == m && c.len >= 1 && c.len + (c.rem > 0) <= most);
+    // more runs than the passes take: each workgroup merges its own share first
+    const int least = (m + most - 1) / most;
+    const bool shares = launched > 0 && least > (launched < 3 ? 256 : 512);
+    CHECK(c.runs >= (shares ? blocks : least) && c.passes >= 0 && c.passes <= launched);
+    CHECK((c.passes == 0) == (c.runs == 1 || launched == 0) && (shares || (c.runs == 1) == (m <= most)));
+    CHECK(c.start(0) == 0 && c.start(c.runs) == m && c.len >= 1 && (shares || c.len + (c.rem > 0) <= most));
     CHECK(c.rem < c.runs && c.start(c.runs) - c.start(c.runs - 1) >= c.start(1) - 1);
     int u = 1;
     for (int p = 0; p + 1 < c.passes; ++p) {
@@ -30,17 +34,19 @@ static int check(int m, int most, int launched) {
         // the last group is as long as the first, but for a key a run
         CHECK(c.start(c.runs) - c.start(c.runs - u) >= c.start(u) - u);
     }
-    if (c.passes > 0) CHECK(c.runs / u <= (c.passes == 1 ? c.runs : c.fan));
+    if (c.passes > 0) CHECK(c.runs / u <= (c.passes == 1 ? (blocks > 256 ? blocks : 256) : c.fan));
     return 0;
 }
 int main() {
     const int mosts[] = {2048, 4096};
     for (int most : mosts)
-        for (int launched = 0; launched <= 3; ++launched) {
-            for (int m = -1; m < 300000; m += m < 20000 ? 1 : 37) if (check(m, most, launched)) return 1;
-            for (long long m = 300000; m < (1ll << 29); m += m / 97 + 1) if (check((int)m, most, launched)) return 1;
-            if (check(5218382, most, launched) || check((1 << 29) - 1, most, launched)) return 1;
-        }
+        for (int launched = 0; launched <= 3; ++launched)
+            for (int blocks : {1, 2, 15, 16, 170, 256, 512}) {
+                for (int m = -1; m < 300000; m += m < 20000 ? 1 : 37) if (check(m, most, launched, blocks)) return 1;
+                for (long long m = 300000; m < (1ll << 29); m += m / 97 + 1)
+                    if (check((int)m, most, launched, blocks)) return 1;
+                if (check(5218382, most, launched, blocks) || check((1 << 29) - 1, most, launched, blocks)) return 1;
+            }
     puts("ok");
 }
 """
