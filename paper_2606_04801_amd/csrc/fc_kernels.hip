@@ -58,6 +58,7 @@ constexpr int kSortThreads = 1024;
 constexpr int kSortCap = 4096;             // keys sorted entirely in LDS (two buffers of 34 KiB)
 constexpr int64_t kSortMultiVoxels = 1 << 16;   // long lists sorted by several workgroups from this size on
 constexpr int kSortMultiInstances = 32;    // ... in batches of up to this many instances
+constexpr int kSortWideInstances = 48;     // ... under PH_WIDE with up to this many of kWideVoxels voxels
 constexpr int kSortRun = 2048;             // keys of their runs
 constexpr int kSideBySideInstances = 64;   // batches of up to this many run the images' dual beside H0
 constexpr int kOutParts = 64;              // workgroups that write the pairs, over all instances
@@ -3741,6 +3742,13 @@ int64_t max_voxels(const ph_shape *h, int n) {
     return m;
 }
 
+// instances of kWideVoxels voxels or more
+int wide_instances(const ph_shape *h, int n) {
+    int k = 0;
+    for (int i = 0; i < n; ++i) k += max_voxels(h + i, 1) >= kWideVoxels ? 1 : 0;
+    return k;
+}
+
 int64_t max_list(const ph_shape *h, int n) {
     int64_t m = 1;
     for (int i = 0; i < n; ++i) {
@@ -3979,12 +3987,16 @@ int run(int n, const void *d_imgs, const int64_t *d_img_off, const ph_shape *d_s
     // Long lists: a workgroup per run or share and one merge launch (three under PH_WIDE, for
     // hundreds of runs).  A list of 8193 keys or more needs about 2^15 voxels even of noise (0.33 KEEP edges
     // a pixel); below 2^16 voxels, and in batches that fill the chip with a workgroup a list,
-    // the one workgroup merges its two or three runs itself, which saves the launch.
-    const bool multi = mv >= kSortMultiVoxels && n <= kSortMultiInstances;
+    // the one workgroup merges its two or three runs itself, which saves the launch.  Under PH_WIDE
+    // the lists may be hundreds of runs long, in a batch of any size, and a workgroup a list pays
+    // only when the large instances alone fill the chip (noise of 1024^2 pixels a call, by many
+    // workgroups and by one: 33 images 11.9 and 13.3 ms, 64 images 24.7 and 23.7).
+    const bool multi = wide ? wide_instances(hs, n) <= kSortWideInstances
+                            : mv >= kSortMultiVoxels && n <= kSortMultiInstances;
     const int passes = !multi ? 0 : (wide ? 3 : 1);
     const int rl = multi ? kSortRun : kSortCap;
     const int64_t runs = (ml + rl - 1) / rl;
-    const unsigned sr = multi ? (unsigned)std::min<int64_t>(runs, std::max<int64_t>(1, (wide ? 512 : 256) / n)) : 1u;
+    const unsigned sr = multi ? (unsigned)std::min<int64_t>(runs, std::max<int64_t>(wide ? 16 : 1, (wide ? 512 : 256) / n)) : 1u;
     FC_LAUNCH(K_SORT, hipLaunchKernelGGL(k_sort_lists, dim3(sr, n, 4), dim3(kSortThreads), 0, st, ws, n, rl, passes));
     for (int p = 0; p < passes; ++p) {
         const unsigned mb = (unsigned)std::min<int64_t>((ml + kMergeThreads - 1) / kMergeThreads, std::max<int64_t>(16, (wide ? 1024 : 256) / n));

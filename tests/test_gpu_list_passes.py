@@ -87,3 +87,26 @@ def test_wide_rounds_past_a_clearing():
     print("wide", img.shape, flush=True)
     got = fc.ph_diagram(img, flags=fc.PH_H0 | fc.PH_HTOP | fc.PH_WIDE).numpy()
     assert len(got) > 10 ** 6 and diff_pairs(got, fc.ph_diagram(img).numpy()) is None
+
+
+@pytest.mark.parametrize("n", [32, 33])
+def test_wide_sort_in_batches(n):
+    """Under PH_WIDE a large instance's lists are sorted by many workgroups beside any number of others:
+    the three merge passes are launched, and the pairs are those of the call without the flag."""
+    imgs = [S.uniform((1024, 1024), 60), S.uniform((24, 20, 22), 61)]
+    imgs += [S.levels((17 + k % 5, 23), 9, 62 + k) for k in range(n - 2)]
+    res = []
+    for flags in (fc.PH_H0 | fc.PH_HTOP, fc.PH_H0 | fc.PH_HTOP | fc.PH_WIDE):
+        bt = fc.Batch([a.shape for a in imgs], flags=flags, device=DEV)
+        bt.set_images([torch.from_numpy(a) for a in imgs])
+        print("batch of", n, "flags", flags, flush=True)
+        fc.profile(True)
+        bt.ph_diagram_batch()
+        torch.cuda.synchronize()
+        launches = fc.profile_read()
+        fc.profile(False)
+        res.append(bt.results())
+        if flags & fc.PH_WIDE:
+            assert launches["k_sort_merge"][0] == 3, launches
+    for a, b in zip(*res):
+        assert diff_pairs(a, b) is None
