@@ -1649,10 +1649,11 @@ __global__ __launch_bounds__(kMergeThreads) void k_sort_merge(uint8_t *__restric
 // A forest of M nodes and m edges that takes the wide rounds (k_uf_wide) under PH_WIDE
 __device__ __forceinline__ bool uf_is_wide(const Inst &I, int M, int m) {
     const int64_t L = I.E > I.F ? I.E : I.F;
-    // (the segments' sizes and the ranks of uf_rest follow the m positions in the live-edge array)
+    // (the segments' sizes follow the m positions in the live-edge array: under a list fraction that
+    // the edges fill to the last 0.2 % the rounds stay in one workgroup)
     static_assert(3ll << kPixBits <= 1ll << kWidePosBits && kWideTags < 1 << (32 - kWidePosBits), "positions and tags");
     return I.N >= kWideVoxels && M > kUfWideNodes && M <= L && I.MTcap <= I.M0cap &&
-           m + m / kWideSeg + 1 + kRestNodes <= L;
+           m + m / kWideSeg + 1 <= L;
 }
 
 // ===================================================================== resolve ====
@@ -2155,12 +2156,12 @@ __device__ __forceinline__ void uf_lds(const Forest &f, int m, int M, int32_t *c
 // which one workgroup's LDS holds.  A round here costs 30 us less by the round (80 us the first:
 // 1.3M atomics), and saves the workgroup 50 us by then (four rounds: 33 us more in all, 65 us on
 // 128^3 noise).  Larger instances take more rounds (wide_rounds).
-// The arrays of a wide forest: par and moe (which holds the left nodes' new numbers in the end);
-// the segments' edges (walk position, roots) and sizes; the same of all segments closed up, both
-// ends packed in one word (ends, pos); the ranks, and those of the nodes left by new number; the
-// eldest node, and the numbers of edges and nodes left.
+// The arrays of a wide forest: par and moe (in the end, if the finish holds them, the ranks of the
+// nodes left by new number, and the left nodes' new numbers); the segments' edges (walk position,
+// roots) and sizes; the same of all segments closed up, both ends packed in one word (ends, pos);
+// the ranks; the eldest node, and the numbers of edges and nodes left.
 struct WideForest {
-    int32_t *par, *q, *a, *b, *size, *ends, *pos, *rank, *left, *eldest, *total, *nodes;
+    int32_t *par, *q, *a, *b, *size, *ends, *pos, *rank, *eldest, *total, *nodes;
     uint32_t *moe;
 };
 __device__ __forceinline__ WideForest wide_forest(uint8_t *__restrict__ ws, const Inst &I, int32_t *cnt, bool dual, int m) {
@@ -2173,7 +2174,6 @@ __device__ __forceinline__ WideForest wide_forest(uint8_t *__restrict__ ws, cons
     w.size = w.q + m;
     w.a = arr<int32_t>(ws, pick(d, I.o_ra, I.o_scratch, 0, 0));
     w.b = arr<int32_t>(ws, pick(d, I.o_rb, I.o_scratch + 4 * L, 0, 0));
-    w.left = w.size + m / kWideSeg + 1;
     w.ends = arr<int32_t>(ws, pick(d, I.o_ea, I.o_fa, 0, 0));    // (the edges' ends, read only by the set-up)
     w.pos = arr<int32_t>(ws, pick(d, I.o_eb, I.o_fb, 0, 0));
     w.rank = arr<int32_t>(ws, I.o_n0key + pick(d, 0, 4 * I.M0cap, 0, 0));   // (the unsorted node keys are not needed)
@@ -2252,15 +2252,21 @@ __global__ __launch_bounds__(kWideThreads) void k_uf_wide(uint8_t *__restrict__ 
             for (int j = 0; j < kNum; ++j) {
                 if (!((mark >> j) & 1u)) continue;
                 const int x = x0 + j * kWideThreads + tid;
-                w.moe[x] = (uint32_t)id;
-                if (id < kRestNodes) w.left[id] = w.rank[x];
-                ++id;
+                w.moe[x] = (uint32_t)id++;
             }
         }
         return;
     }
     const uint32_t tag = (uint32_t)(kWideTags - round % kWideTags) << kWidePosBits;   // (never 0: the mark)
     const int eldest = phase == 0 ? *w.eldest : 0;
+    if (phase == 3 && *w.nodes <= kRestNodes) {
+        // the left nodes' ranks by new number (any other node's moe is a tagged position or ~0)
+        const int blocks = (int)gridDim.x < segs ? (int)gridDim.x : segs;
+        for (int x = blockIdx.x * kWideThreads + tid; x < M; x += blocks * kWideThreads) {
+            const uint32_t id = w.moe[x];
+            if (id < (uint32_t)kRestNodes) w.par[id] = w.rank[x];
+        }
+    }
     for (int sg = blockIdx.x; sg < segs; sg += gridDim.x) {
         const int at = sg * kWideSeg, all = m - at < kWideSeg ? m - at : kWideSeg;
         const int size = phase < 0 ? all : w.size[sg];
@@ -2438,7 +2444,7 @@ __device__ __forceinline__ void uf_rest(uint8_t *__restrict__ ws, const Inst &I,
     f.rank = w.rank;
     if (total == 0) return;
     if (nodes <= kRestNodes) {
-        for (int x = threadIdx.x; x < nodes; x += kUfThreads) s_mem[x] = (uint32_t)w.left[x];
+        for (int x = threadIdx.x; x < nodes; x += kUfThreads) s_mem[x] = (uint32_t)w.par[x];
         f.ea = w.ends;
         // (the sequential finish's lists: the segments' arrays, free now)
         uf_lds<kUfK, true>(f, total, nodes, cnt, s_mem + kRestNodes, s_mem, w.pos, s_wsum, s_any, w.q, w.a, w.b, rounds);

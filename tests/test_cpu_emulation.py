@@ -496,3 +496,12 @@ def test_sort_shares_merged_by_their_workgroups():
     out, _ = run(emu_build.build("small_wide"), imgs, mode=1)
     for img, (got, st) in zip(imgs, out):
         assert st == 0 and diff_pairs(got, oracle.diagram(img)) is None, img.shape
+
+
+def test_wide_rounds_under_a_tight_list_fraction(monkeypatch):
+    """Noise that fills its edge list but for 69 of 4,096 entries: the wide rounds need no more room in
+    it than the segments' sizes (and not the finish's nodes as well, 78 here)."""
+    img = S.uniform((113, 114), 64)
+    ((got, st),), (w,) = run_stats(monkeypatch, emu_build.build("small_wide"), [img], flags=3 | 64 | 1 << 8)
+    assert st == 0 and diff_pairs(got, oracle.diagram(img)) is None
+    assert w["keepE"] == 4096 - 69 and w["left0"] > 0, w
