@@ -2259,35 +2259,40 @@ __global__ __launch_bounds__(kWideThreads) void k_uf_wide(uint8_t *__restrict__ 
     }
     const uint32_t tag = (uint32_t)(kWideTags - round % kWideTags) << kWidePosBits;   // (never 0: the mark)
     const int eldest = phase == 0 ? *w.eldest : 0;
-    if (phase == 3 && *w.nodes <= kRestNodes) {
-        // the left nodes' ranks by new number (any other node's moe is a tagged position or ~0)
+    if (phase == 3) {
         const int blocks = (int)gridDim.x < segs ? (int)gridDim.x : segs;
-        for (int x = blockIdx.x * kWideThreads + tid; x < M; x += blocks * kWideThreads) {
-            const uint32_t id = w.moe[x];
-            if (id < (uint32_t)kRestNodes) w.par[id] = w.rank[x];
+        // the left nodes' ranks by new number (any other node's moe is a tagged position or ~0)
+        if (*w.nodes <= kRestNodes)
+            for (int x = blockIdx.x * kWideThreads + tid; x < M; x += blocks * kWideThreads) {
+                const uint32_t id = w.moe[x];
+                if (id < (uint32_t)kRestNodes) w.par[id] = w.rank[x];
+            }
+        // a run of segments each workgroup, from its first place on: the sizes before it, summed once
+        // (before every segment they are half as many as the segments: 512^3 noise, 87k segments,
+        // 1,776 us, so 249 us)
+        const int per = (segs + blocks - 1) / blocks, s0 = blockIdx.x * per, s1 = s0 + per < segs ? s0 + per : segs;
+        int before = 0;
+        for (int k = tid; k < s0 && k < segs; k += kWideThreads) before += w.size[k];
+        const int upto = (int)wave_incl_sum((uint32_t)before);
+        if (lane == 63) s_cnt[0][wid] = upto;
+        __syncthreads();
+        int first = 0;
+        for (int v = 0; v < kWideThreads / 64; ++v) first += s_cnt[0][v];
+        for (int sg = s0; sg < s1; ++sg) {
+            const int at = sg * kWideSeg, size = w.size[sg];
+            for (int e = tid; e < size; e += kWideThreads) {
+                w.pos[first + e] = w.q[at + e];
+                w.ends[first + e] = (int32_t)(w.moe[w.a[at + e]] | w.moe[w.b[at + e]] << 16);
+            }
+            first += size;
+            if (sg == segs - 1 && tid == 0) *w.total = first;
         }
+        return;
     }
     for (int sg = blockIdx.x; sg < segs; sg += gridDim.x) {
         const int at = sg * kWideSeg, all = m - at < kWideSeg ? m - at : kWideSeg;
         const int size = phase < 0 ? all : w.size[sg];
         int q[kWidePer], a[kWidePer], b[kWidePer];
-        if (phase == 3) {
-            // the segment's first place: the sizes before it
-            int before = 0;
-            for (int k = tid; k < sg; k += kWideThreads) before += w.size[k];
-            const int upto = (int)wave_incl_sum((uint32_t)before);
-            __syncthreads();                         // the last segment's sums have been read
-            if (lane == 63) s_cnt[0][wid] = upto;
-            __syncthreads();
-            int first = 0;
-            for (int v = 0; v < kWideThreads / 64; ++v) first += s_cnt[0][v];
-            for (int e = tid; e < size; e += kWideThreads) {
-                w.pos[first + e] = w.q[at + e];
-                w.ends[first + e] = (int32_t)(w.moe[w.a[at + e]] | w.moe[w.b[at + e]] << 16);
-            }
-            if (sg == segs - 1 && tid == 0) *w.total = first + size;
-            continue;
-        }
         if (phase == 1) {
 #pragma unroll
             for (int j = 0; j < kWidePer; ++j) {
