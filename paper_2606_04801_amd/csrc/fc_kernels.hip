@@ -1458,8 +1458,8 @@ __global__ __launch_bounds__(kSortThreads, 8) void k_sort_lists(uint8_t *__restr
     lds_barrier();
     if (s_flag) return;
     const int m = L.m;                           // (a list has fewer than 2^29 keys)
-    SortCut cut = sort_cut(m, rl, passes, gridDim.x);
-    if (passes == 0) { cut.runs = 1; cut.len = m; cut.rem = 0; }
+    SortCut cut{m, 1, 0, 1, m, 0};               // one run, or one workgroup's list
+    if (passes > 0 && m > rl) cut = sort_cut(m, rl, passes, gridDim.x);
     if (m <= 0 || (int)blockIdx.x >= cut.runs) return;
     if (m > L.cap) { if (threadIdx.x == 0) set_err(cnt, PH_EINTERNAL); return; }
     // the keys of one run by the fewest a thread that hold it
@@ -1472,17 +1472,13 @@ __global__ __launch_bounds__(kSortThreads, 8) void k_sort_lists(uint8_t *__restr
     const uint64_t *a = L.dst;
     for (int j = blockIdx.x; j < cut.runs; j += gridDim.x) {
         const int base = cut.start(j), len = (j + 1 < cut.runs ? cut.start(j + 1) : m) - base;
-        if (len <= rl) {
-            sort(base, len, to, cut.runs == 1);
-            continue;
-        }
-        // merged here: runs of rl keys (as sorted: a dual node's complemented), which start where
-        // they end after all merges, or in the other array; a whole list starts in place
-        int merges = 0;
-        for (int wd = rl; wd < len; wd *= 2) ++merges;
-        uint64_t *from = cut.runs > 1 && (merges & 1) ? other : to;
-        for (int k = 0; k < len; k += rl) sort(base + k, len - k < rl ? len - k : rl, from, false);
-        a = merge_pairs(from + base, (from == to ? other : to) + base, len, rl, s);
+        // more than rl keys are merged here: runs of rl keys (as sorted: a dual node's complemented),
+        // which start where they end after all merges, or in the other array; a whole list in place
+        uint64_t *from = to;
+        if (cut.runs > 1)
+            for (int wd = rl; wd < len; wd *= 2) from = from == to ? other : to;
+        for (int k = 0; k < len; k += rl) sort(base + k, len - k < rl ? len - k : rl, from, m <= rl);
+        if (len > rl) a = merge_pairs(from + base, (from == to ? other : to) + base, len, rl, s);
     }
     if (cut.runs > 1 || m <= rl) return;
     // a holds the sorted keys; in dst they are stored over themselves, so the neighbour's
