@@ -2539,6 +2539,9 @@ __global__ __launch_bounds__(kUfThreads) void k_unionfind(uint8_t *__restrict__ 
 constexpr int kH1Slots = 1024;             // table slots of the first pass
 constexpr int kH1BigSlots = 4096;          // the same for the columns the first pass could not hold
 constexpr int kH1Groups = 4096;            // workgroups of the first pass, over all instances (18 a compute unit run)
+// ... in all, where each volume may have kH1Groups (128^3 with seven, fifteen of 64^3, 1024, 2048 and 4096
+// each: 968, 838, 965 us and 996, 955, 1,275: those that find no column left are not free)
+constexpr int kH1AllGroups = 24 << 10;
 constexpr int kH1PerVolume = 512;          // ... and of one instance: about what one XCD runs at once
 constexpr int kH1MaxBoundary = 64;         // entries of one column's boundary in critical cells
 constexpr int kH1MaxChunks = 1 << 20;
@@ -2761,13 +2764,13 @@ __device__ __forceinline__ int h1_class(uint32_t key, const uint16_t *cfg3, cons
 // outgrow them is put on the instance's retry list, which pass 1 goes through with kH1BigSlots.
 // The workgroups of an instance draw their columns from a counter, the latest squares first:
 // theirs are the long columns, which else end the launch on a few compute units (8 volumes 96^3
-// 825 -> 663 us, 32 volumes 2,000 -> 1,833 us).  All but the last n % 8 instances have theirs on
-// one XCD, an instance after another, so that its pixels and configurations stay in that XCD's
-// L2 (2,270 -> 2,160 us on 32 volumes 96^3).  The column's boundary in critical cells (sorted
-// descending) goes to the pool, its start and length to h1b, h1n.
+// 825 -> 663 us, 32 volumes 2,000 -> 1,833 us).  even: the first `even` instances (a multiple of 8) have
+// theirs on one XCD each, an instance after another, so that an instance's pixels and configurations
+// stay in that XCD's L2 (2,270 -> 2,160 us on 32 volumes 96^3); see h1_even.  The column's boundary
+// in critical cells (sorted descending) goes to the pool, its start and length to h1b, h1n.
 template <typename T, int SLOTS>
 __global__ __launch_bounds__(64) void k_h1_morse(const T *__restrict__ imgs, uint8_t *__restrict__ ws, int n,
-                                                 Luts lut, int pass) {
+                                                 Luts lut, int pass, int even) {
     __shared__ uint32_t s_tab[SLOTS];
     __shared__ uint32_t s_tab2[SLOTS >= 2048 ? SLOTS : 1];
     __shared__ uint32_t s_queue[H1Col<SLOTS>::kQueue];
@@ -2777,7 +2780,7 @@ __global__ __launch_bounds__(64) void k_h1_morse(const T *__restrict__ imgs, uin
     __shared__ uint16_t s_task[64 * 12];            // squares of a step: lane of the entry << 4 | square slot
     __shared__ H1Square s_sq[12];
     // gridDim.x / n workgroups an instance; workgroup b runs on XCD b % 8
-    const int per = gridDim.x / n, even = n / kXcds * kXcds, b = blockIdx.x;
+    const int per = gridDim.x / n, b = blockIdx.x;
     const int i = b < even * per ? b / (kXcds * per) * kXcds + b % kXcds : even + (b - even * per) / per;
     const Inst I = ((const Inst *)ws)[i];           // one batch of loads, before any atomic
     int32_t *cnt = (int32_t *)(ws + off_cnt(n)) + i * CNT_WORDS;
@@ -3780,6 +3783,23 @@ int wide_rounds(int64_t mv) {
     return r;
 }
 
+// Instances whose H1 columns run on one XCD each (k_h1_morse): all but the last n % 8, if no XCD gets
+// more than twice its share of their voxels, else none.  On one XCD and over all: eight of 64^3 494 and
+// 525 us; sixteen of 64^3 to 96^3 (1.7 times the share) 865 and 1,041; two of 128^3 with 22 of 64^3
+// (2.1 times) 1,507 and 1,040; 96^3 with seven of 64^3 (2.6 times) 505 to 577 and 569 to 586; 128^3
+// with seven (4.3 times) 1,290 and 885.
+int h1_even(const ph_shape *h, int n) {
+    const int even = n / kXcds * kXcds;
+    int64_t load[kXcds] = {0}, all = 0, most = 0;
+    for (int i = 0; i < even; ++i)
+        if (h[i].ndim == 3) load[i % kXcds] += (int64_t)h[i].ext[0] * h[i].ext[1] * h[i].ext[2];
+    for (int x = 0; x < kXcds; ++x) {
+        all += load[x];
+        most = std::max(most, load[x]);
+    }
+    return kXcds * most <= 2 * all ? even : 0;
+}
+
 template <int A, int B, typename T = float>
 void launch2d(int64_t tiles, const void *imgs, uint8_t *ws, int n, Luts lut, hipStream_t st, float *grad) {
     hipLaunchKernelGGL((k_classify2d<A, B, T>), dim3((unsigned)tiles), dim3(256), 0, st, (const T *)imgs, ws, n, lut,
@@ -4045,19 +4065,22 @@ int run(int n, const void *d_imgs, const int64_t *d_img_off, const ph_shape *d_s
         FC_LAUNCH(K_UF_2D, hipLaunchKernelGGL(k_unionfind, dim3(n), dim3(kUfThreads), 0, st, ws, n, 1, staged, htop, wide));
     }
     if (h1 && any3) {
-        // kH1Groups 64-thread workgroups over the instances, or kH1PerVolume for each; one per
-        // 512 voxels of the largest volume at most
-        const unsigned hb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((mv + 511) / 512, std::max<int64_t>((kH1Groups + n - 1) / n, kH1PerVolume)));
+        // kH1Groups 64-thread workgroups over the instances, or kH1PerVolume for each (volumes of
+        // uneven sizes: kH1Groups for each, as far as kH1AllGroups goes); one per 512 voxels of the
+        // largest volume at most
+        const int even = h1_even(hs, n);
+        const int64_t most = even || n < kXcds ? (kH1Groups + n - 1) / n : std::min<int64_t>(kH1Groups, kH1AllGroups / n);
+        const unsigned hb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((mv + 511) / 512, std::max<int64_t>(most, kH1PerVolume)));
         // pass 1 (64 workgroups per instance) takes the columns pass 0 could not hold
         if (elem == 1) {
-            FC_LAUNCH(K_H1MORSE, hipLaunchKernelGGL((k_h1_morse<uint8_t, kH1Slots>), dim3(hb * n), dim3(64), 0, st, (const uint8_t *)cimgs, ws, n, lut, 0));
-            FC_LAUNCH(K_H1MORSE2, hipLaunchKernelGGL((k_h1_morse<uint8_t, kH1BigSlots>), dim3(64u * n), dim3(64), 0, st, (const uint8_t *)cimgs, ws, n, lut, 1));
+            FC_LAUNCH(K_H1MORSE, hipLaunchKernelGGL((k_h1_morse<uint8_t, kH1Slots>), dim3(hb * n), dim3(64), 0, st, (const uint8_t *)cimgs, ws, n, lut, 0, even));
+            FC_LAUNCH(K_H1MORSE2, hipLaunchKernelGGL((k_h1_morse<uint8_t, kH1BigSlots>), dim3(64u * n), dim3(64), 0, st, (const uint8_t *)cimgs, ws, n, lut, 1, even));
         } else if (elem == 2) {
-            FC_LAUNCH(K_H1MORSE, hipLaunchKernelGGL((k_h1_morse<uint16_t, kH1Slots>), dim3(hb * n), dim3(64), 0, st, (const uint16_t *)cimgs, ws, n, lut, 0));
-            FC_LAUNCH(K_H1MORSE2, hipLaunchKernelGGL((k_h1_morse<uint16_t, kH1BigSlots>), dim3(64u * n), dim3(64), 0, st, (const uint16_t *)cimgs, ws, n, lut, 1));
+            FC_LAUNCH(K_H1MORSE, hipLaunchKernelGGL((k_h1_morse<uint16_t, kH1Slots>), dim3(hb * n), dim3(64), 0, st, (const uint16_t *)cimgs, ws, n, lut, 0, even));
+            FC_LAUNCH(K_H1MORSE2, hipLaunchKernelGGL((k_h1_morse<uint16_t, kH1BigSlots>), dim3(64u * n), dim3(64), 0, st, (const uint16_t *)cimgs, ws, n, lut, 1, even));
         } else {
-            FC_LAUNCH(K_H1MORSE, hipLaunchKernelGGL((k_h1_morse<float, kH1Slots>), dim3(hb * n), dim3(64), 0, st, (const float *)cimgs, ws, n, lut, 0));
-            FC_LAUNCH(K_H1MORSE2, hipLaunchKernelGGL((k_h1_morse<float, kH1BigSlots>), dim3(64u * n), dim3(64), 0, st, (const float *)cimgs, ws, n, lut, 1));
+            FC_LAUNCH(K_H1MORSE, hipLaunchKernelGGL((k_h1_morse<float, kH1Slots>), dim3(hb * n), dim3(64), 0, st, (const float *)cimgs, ws, n, lut, 0, even));
+            FC_LAUNCH(K_H1MORSE2, hipLaunchKernelGGL((k_h1_morse<float, kH1BigSlots>), dim3(64u * n), dim3(64), 0, st, (const float *)cimgs, ws, n, lut, 1, even));
         }
         FC_LAUNCH(K_H1REDUCE, hipLaunchKernelGGL(k_h1_reduce, dim3(n), dim3(kUfThreads), 0, st, ws, n));
     }

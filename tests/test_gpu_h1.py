@@ -193,3 +193,18 @@ def test_large_column_takes_the_second_pass():
     (got,) = bt.results()
     assert bt.work_counters()[0, 12] > 0
     assert diff_pairs(got, ref(a)) is None
+
+
+@pytest.mark.parametrize("large", [0, 7, None])
+def test_volumes_of_uneven_sizes(large):
+    """Nine volumes, the columns of eight of them on one XCD each, or (a large one among them) all
+    volumes' columns over the whole GPU: every pair of the volumes as the oracle has it."""
+    imgs = [S.levels((6, 7, 5 + k % 3), 5, 80 + k) for k in range(9)]
+    if large is not None:
+        imgs[large] = S.grf((24, 26, 22), 2.0, 89)
+    bt = fc.Batch([a.shape for a in imgs], flags=ALL, device=DEV)
+    bt.set_images([torch.from_numpy(a) for a in imgs])
+    print("uneven volumes", large, flush=True)
+    bt.ph_diagram_batch()
+    for a, got in zip(imgs, bt.results()):
+        assert diff_pairs(got, ref(a)) is None, a.shape
