@@ -180,8 +180,9 @@ FC_HD int64_t list_cap(int64_t worst, int k) {
     return c < kListFloor ? kListFloor : (c > worst ? worst : c);
 }
 
-// The sizes from which the whole GPU works on one instance.  A host build of the tests lowers them by
-// FC_WIDE_SHIFT powers of two, so that small images take every path of large ones.
+// The sizes from which the whole GPU works on one instance, or a union-find out of the workspace.  A host
+// build of the tests lowers them by FC_WIDE_SHIFT powers of two, so that small images take every
+// path of large ones.
 #ifndef FC_WIDE_SHIFT
 #define FC_WIDE_SHIFT 0
 #endif

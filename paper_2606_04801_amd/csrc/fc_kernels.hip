@@ -50,7 +50,7 @@ constexpr int32_t kLocal = 0x40000000;     // LDS link to an entry of the same t
 constexpr int32_t kUnset = 0x7FFFFFFF;     // LDS cube slot not yet written
 constexpr int kMaxChase = 1 << 22;         // bound of every pointer walk
 constexpr int kUfThreads = 1024;
-constexpr int kUfLdsNodes = 40000;         // union-find nodes kept in LDS (a word each)
+constexpr int kUfLdsNodes = 40000 >> FC_WIDE_SHIFT;   // union-find nodes kept in LDS (a word each)
 constexpr int kUfK = 4;                    // edges a thread of a batch of the union-find
 constexpr int kUfLdsWords = 40600;         // the union-find's LDS, int32 (160 KiB less its other shared words)
 constexpr int kUfWideNodes = 20440 >> FC_WIDE_SHIFT;   // the wide rounds (PH_WIDE) take forests of more nodes

@@ -505,3 +505,14 @@ def test_wide_rounds_under_a_tight_list_fraction(monkeypatch):
     ((got, st),), (w,) = run_stats(monkeypatch, emu_build.build("small_wide"), [img], flags=3 | 64 | 1 << 8)
     assert st == 0 and diff_pairs(got, oracle.diagram(img)) is None
     assert w["keepE"] == 4096 - 69 and w["left0"] > 0, w
+
+
+def test_wide_passes_random_interleavings(monkeypatch):
+    """The union-find out of the workspace (its node limit lowered 256 times), and under PH_WIDE the sort's
+    merge passes, the wide rounds and their finish, with the threads resumed in random order."""
+    monkeypatch.setenv("EMU_SHUFFLE", "5")
+    exe = emu_build.build("small_wide")
+    img = S.uniform((130, 131), 81)
+    for flags in (3, 3 | 64):
+        (got, st), = run(exe, [img], flags=flags)[0]
+        assert st == 0 and diff_pairs(got, oracle.diagram(img)) is None, flags

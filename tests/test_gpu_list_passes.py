@@ -110,3 +110,32 @@ def test_wide_sort_in_batches(n):
             assert launches["k_sort_merge"][0] == 3, launches
     for a, b in zip(*res):
         assert diff_pairs(a, b) is None
+
+
+@pytest.mark.parametrize("filtration", ["V", "T"])
+@pytest.mark.parametrize("kind", ["field", "ties"])
+def test_h1_pairs_of_multi_run_volumes(kind, filtration):
+    """The H1 pairs, too, where each vertex's first KEEP edge is found across runs: two runs and
+    more of edges, against the oracle's reduction of every dimension."""
+    img = S.grf((41, 40, 42), 0.7, 40) if kind == "field" else S.levels((41, 40, 42), 6, 41)
+    bt = fc.Batch([img.shape], flags=fc.PH_H0 | fc.PH_HTOP | fc.PH_H1, filtration=filtration, device=DEV)
+    bt.set_images([torch.from_numpy(img)])
+    print("h1", kind, filtration, flush=True)
+    bt.ph_diagram_batch()
+    (got,) = bt.results()
+    assert diff_pairs(got, oracle.diagram(img, dims=(0, 1, 2), filtration=filtration)) is None
+    assert bt.work_counters()[0, 0] > 2048
+
+
+@pytest.mark.parametrize("side, h0, top", [(440, False, False), (456, True, False), (610, True, True)])
+def test_forests_at_the_lds_limit(side, h0, top):
+    """The two union-finds of noise at both sides of 40,000 nodes, where they leave LDS for the workspace."""
+    img = S.uniform((side, side + 1), 70)
+    bt = fc.Batch([img.shape], device=DEV)
+    bt.set_images([torch.from_numpy(img)])
+    print("forests", img.shape, flush=True)
+    bt.ph_diagram_batch()
+    (got,) = bt.results()
+    wc = bt.work_counters()
+    assert (wc[0, 2] > 40000) == h0 and (wc[0, 3] > 40000) == top and 36000 < wc[0, 2 + top] < 44000, wc[0]
+    assert diff_pairs(got, oracle.diagram(img)) is None
