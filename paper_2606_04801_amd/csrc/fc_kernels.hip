@@ -57,11 +57,22 @@ constexpr int kUfWideNodes = 20440 >> FC_WIDE_SHIFT;   // the wide rounds (PH_WI
 constexpr int kSortThreads = 1024;
 constexpr int kSortCap = 4096;             // keys sorted entirely in LDS (two buffers of 34 KiB)
 constexpr int64_t kSortMultiVoxels = 1 << 16;   // long lists sorted by several workgroups from this size on
-constexpr int kSortMultiInstances = 32;    // ... in batches of up to this many instances
+// ... in batches of up to this many instances.  A call with its lists sorted by many workgroups and by
+// one each, in us: 256^2 noise, 8, 32, 48, 64 images 262 and 351, 405 and 452, 522 and 557, 614 and 607;
+// 1024^2 8-bit fields, 8, 32, 64 images 235 and 247, 496 and 496, 819 and 797; 512^2 noise, 8, 16, 32
+// images 4,530 and 4,806, 5,214 and 5,097, 5,896 and 5,617 (long lists fill the chip sooner).
+constexpr int kSortMultiInstances = 32;
 constexpr int kSortWideInstances = 48;     // ... under PH_WIDE with up to this many of kWideVoxels voxels
 constexpr int kSortRun = 2048;             // keys of their runs
-constexpr int kSideBySideInstances = 64;   // batches of up to this many run the images' dual beside H0
-constexpr int kOutParts = 64;              // workgroups that write the pairs, over all instances
+// Batches of up to this many run the images' dual beside H0.  A call with it beside and after, in us:
+// 512^2 fields, 8, 64, 128, 256 images 171 and 209, 367 and 396, 575 and 605, 1,047 and 991; 512^2 noise,
+// whose unpruned dual walks three times the edges, 8, 64, 128 images 4,534 and 4,734, 6,800 and 6,873,
+// 10,736 and 10,581: up to 64 it is better for both.
+constexpr int kSideBySideInstances = 64;
+// Workgroups that write the pairs, over all instances: more of them write less each but count the
+// same.  316^2 noise with 16, 32, 64, 128, 256: one image 263, 250, 249, 249, 251 us a call, eight
+// images 425, 380, 353, 339, 342.
+constexpr int kOutParts = 64;
 constexpr int kMaxRounds = 48;             // parallel rounds before the sequential finish
 constexpr int kWideRoundsMin = 6;          // union-find rounds over many workgroups (PH_WIDE), at least
 constexpr int64_t kWideVoxels = (1 << 20) >> FC_WIDE_SHIFT;   // ... for instances of this many voxels
