@@ -1386,8 +1386,8 @@ __device__ __forceinline__ void sort_run(uint8_t *__restrict__ ws, const Inst &I
 // Merge the sorted runs of wd keys (a power of two from half a tile on; the last may be shorter) of
 // a[0, m) in pairs, by the whole block, back and forth between a and b: a tile of kTile outputs at a
 // time through LDS (merge path: each tile's share of the two runs by one binary search, each
-// thread's four outputs by another in LDS).  Returns where the sorted keys end up.
-__device__ __forceinline__ uint64_t *merge_pairs(uint64_t *a, uint64_t *b, int m, int wd0, uint64_t *s) {
+// thread's four outputs by another in LDS).
+__device__ __forceinline__ void merge_pairs(uint64_t *a, uint64_t *b, int m, int wd0, uint64_t *s) {
     constexpr int kTile = 4 * kSortThreads;
     int *s_split = (int *)(s + kTile);               // split points of a batch of tiles
     static_assert(2 * pad_size(kSortCap) >= kTile + (kSortThreads + 2) / 2 && kSortCap == kTile, "tile and split points fit");
@@ -1398,7 +1398,7 @@ __device__ __forceinline__ uint64_t *merge_pairs(uint64_t *a, uint64_t *b, int m
             // tile k starts at output o = (tb + k) T of its pair [ps, ps + 2w): the number of
             // left-run keys among the pair's first o - ps outputs (merge path); k = nb too, the
             // batch's end (used only when the batch's last tile ends inside its pair)
-            for (int k = threadIdx.x; k <= nb; k += blockDim.x) {
+            for (int k = threadIdx.x; k <= nb; k += kSortThreads) {
                 const int o = (tb + k) * kTile, ps = o / (2 * wd) * (2 * wd);
                 if (o >= m) { s_split[k] = 0; continue; }   // past the list: never read
                 const int la = (m - ps) < wd ? (m - ps) : wd;
@@ -1423,7 +1423,7 @@ __device__ __forceinline__ uint64_t *merge_pairs(uint64_t *a, uint64_t *b, int m
                 // the tile's end: the next tile's split inside the same pair, else the pair's end
                 const int i1 = o1 == pend ? la : s_split[k + 1];
                 const int na = (int)(i1 - i0), nt = (int)(o1 - o0), nb2 = nt - na;
-                for (int t = threadIdx.x; t < nt; t += blockDim.x)
+                for (int t = threadIdx.x; t < nt; t += kSortThreads)
                     s[t] = t < na ? a[ps + i0 + t] : a[ps + wd + j0 + (t - na)];
                 __syncthreads();
                 // thread t writes outputs 4t .. 4t + 3 of the tile: its split in LDS, then a
@@ -1449,7 +1449,6 @@ __device__ __forceinline__ uint64_t *merge_pairs(uint64_t *a, uint64_t *b, int m
         a = b;
         b = t;
     }
-    return a;
 }
 
 // The sorts of every instance in one launch: grid (R, n, 4), blockIdx.y = instance, z = list, so
@@ -1479,22 +1478,23 @@ __global__ __launch_bounds__(kSortThreads, 8) void k_sort_lists(uint8_t *__restr
         else sort_run<4>(ws, I, cnt, w, L, base, len, out, whole, s);
     };
     // an odd number of merge passes ends in dst when the runs start from the scratch
-    uint64_t *to = cut.passes & 1 ? L.scr : L.dst, *other = cut.passes & 1 ? L.dst : L.scr;
-    const uint64_t *a = L.dst;
     for (int j = blockIdx.x; j < cut.runs; j += gridDim.x) {
         const int base = cut.start(j), len = (j + 1 < cut.runs ? cut.start(j + 1) : m) - base;
         // more than rl keys are merged here: runs of rl keys (as sorted: a dual node's complemented),
         // which start where they end after all merges, or in the other array; a whole list in place
-        uint64_t *from = to;
+        bool scr = cut.passes & 1;
         if (cut.runs > 1)
-            for (int wd = rl; wd < len; wd *= 2) from = from == to ? other : to;
-        for (int k = 0; k < len; k += rl) sort(base + k, len - k < rl ? len - k : rl, from, m <= rl);
-        if (len > rl) a = merge_pairs(from + base, (from == to ? other : to) + base, len, rl, s);
+            for (int wd = rl; wd < len; wd *= 2) scr = !scr;
+        for (int k = 0; k < len; k += rl)
+            sort(base + k, len - k < rl ? len - k : rl, scr ? L.scr : L.dst, m <= rl);
+        if (len > rl) merge_pairs((scr ? L.scr : L.dst) + base, (scr ? L.dst : L.scr) + base, len, rl, s);
     }
     if (cut.runs > 1 || m <= rl) return;
+    const uint64_t *a = L.dst;                   // in place after an even number of merges
+    for (int wd = rl; wd < m; wd *= 2) a = a == L.dst ? L.scr : L.dst;
     // a holds the sorted keys; in dst they are stored over themselves, so the neighbour's
     // vertex is read before the barrier that precedes the stores of a chunk
-    for (int t0 = 0; t0 < m; t0 += blockDim.x) {
+    for (int t0 = 0; t0 < m; t0 += kSortThreads) {
         const int t = t0 + threadIdx.x;
         const uint64_t k = t < m ? a[t] : 0, prev = t > 0 && t < m ? a[t - 1] : 0;
         __syncthreads();
