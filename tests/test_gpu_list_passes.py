@@ -139,3 +139,19 @@ def test_forests_at_the_lds_limit(side, h0, top):
     wc = bt.work_counters()
     assert (wc[0, 2] > 40000) == h0 and (wc[0, 3] > 40000) == top and 36000 < wc[0, 2 + top] < 44000, wc[0]
     assert diff_pairs(got, oracle.diagram(img)) is None
+
+
+def ramp_noise(n, slope, seed):
+    """Noise on a ramp: the lists' order follows the image, so sorted runs hold bands of it."""
+    return S.uniform((n, n), seed) + slope * np.arange(n, dtype=np.float32)[:, None]
+
+
+@pytest.mark.parametrize("flags", [0, fc.PH_WIDE])
+@pytest.mark.parametrize("kind", ["ramp", "checkerboard"])
+def test_lists_ordered_like_the_image(kind, flags):
+    """Merges whose windows in the other runs are far larger than the keys placed, in one pass and
+    (PH_WIDE) in three."""
+    img = ramp_noise(1024, 0.05, 71) if kind == "ramp" else (np.indices((1024, 1024)).sum(axis=0) % 2).astype(np.float32)
+    print("ordered", kind, flags, flush=True)
+    got = fc.ph_diagram(torch.from_numpy(img).to(DEV), flags=fc.PH_H0 | fc.PH_HTOP | flags).numpy()
+    assert diff_pairs(got, oracle.diagram(img)) is None
