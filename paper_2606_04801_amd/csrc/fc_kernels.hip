@@ -3813,16 +3813,18 @@ int64_t max_list(const ph_shape *h, int n) {
     return m;
 }
 
-// Wide union-find rounds of a call whose largest instance has mv voxels.  Of noise (the slowest of
-// the inputs tried: ramps, quantised and smoothed noise lose their nodes faster) a round leaves 0.6
-// of the nodes, 4k of 1024^2 pixels after six, and the finish holds kRestNodes: past 2200^2 pixels or
-// 200^3 voxels six leave more, and one workgroup then works out of the workspace (4096^2 99 ms, 256^3
-// 212 ms).  A doubling of the voxels takes 1.3 rounds more to the same nodes; two cost no more, since
-// each also saves the workgroup its share (256^3 with 8, 10, 12, 14, 20 rounds: 7.9, 7.7, 7.5, 7.5,
-// 7.4 ms; 2048^2 with 6, 8, 10, 14: 1.96, 1.90, 1.93, 2.04 ms; 1024^2 with 6, 8, 10: 0.80, 0.81, 0.84).
+// Wide union-find rounds of a call whose largest instance has mv voxels: six at 2^20, two more for each
+// doubling.  A round leaves 0.6 of the nodes in the inputs that lose them slowest (white noise 0.58;
+// noise on a checkerboard, with a node for every other pixel the most there can be, 0.6; ramps, quantised
+// and smoothed noise lose them faster): 4k and 8k of 1024^2 pixels after six, and the finish holds
+// kRestNodes.  If more are left one workgroup works out of the workspace (six rounds at 4096^2
+// noise 99 ms, 256^3 212 ms; seven at 1448^2 noise on a checkerboard 14.4 ms, ten 1.7).  A doubling
+// of the voxels takes 1.4 rounds more to the same nodes; two cost no more, since each also saves the
+// workgroup its share (256^3 with 8, 10, 12, 14, 20 rounds: 7.9, 7.7, 7.5, 7.5, 7.4 ms; 2048^2 with 6,
+// 8, 10, 14: 1.96, 1.90, 1.93, 2.04 ms; 1024^2 with 6, 8, 10: 0.80, 0.81, 0.84).
 int wide_rounds(int64_t mv) {
     int r = kWideRoundsMin;
-    for (int64_t v = 4 * kWideVoxels; v <= mv; v *= 2) r += 2;
+    for (int64_t v = kWideVoxels; v < mv; v = v * 182 / 128) ++r;   // (a factor of the square root of 2 each)
     return r;
 }
 

@@ -460,15 +460,18 @@ def run_stats(monkeypatch, exe, imgs, **kw):
     return out, stats
 
 
-@pytest.mark.parametrize("shape", [(256, 256), (40, 41, 42)])
+@pytest.mark.parametrize("shape", [(256, 256), (40, 41, 42), "checkerboard"])
 def test_wide_rounds_leave_what_the_finish_holds(monkeypatch, shape):
     """Noise of 2^24 and more voxels under PH_WIDE (the build's limits are lowered 256 times): the
     wide rounds leave no more nodes than the finish in one workgroup holds (20,000), whatever the
     size, with the oracle's pairs under the sanitizers."""
-    img = S.uniform(shape, 31)
+    if shape == "checkerboard":                      # a node for every other pixel
+        img = np.indices((128, 128)).sum(axis=0) % 2 + np.float32(0.3) * S.uniform((128, 128), 31)
+    else:
+        img = S.uniform(shape, 31)
     ((got, st),), (w,) = run_stats(monkeypatch, emu_build.build("small_wide"), [img], flags=3 | 64)
     assert st == 0 and diff_pairs(got, oracle.diagram(img)) is None
-    assert w["minima"] > 20440 >> 8 and 0 < w["left0"] <= 20000 >> 8 and w["leftT"] <= 20000 >> 8, w
+    assert w["minima"] > 20440 >> 8 and w["rounds0"] > 6 and max(w["left0"], w["leftT"]) <= 20000 >> 8, w
 
 
 def test_wide_rounds_with_nodes_left(monkeypatch):
