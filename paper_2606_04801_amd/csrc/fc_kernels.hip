@@ -69,6 +69,7 @@ constexpr int kSortRun = 2048;             // keys of their runs
 // whose unpruned dual walks three times the edges, 8, 64, 128 images 4,534 and 4,734, 6,800 and 6,873,
 // 10,736 and 10,581: up to 64 it is better for both.
 constexpr int kSideBySideInstances = 64;
+constexpr int64_t kSideBySideWide = (3 << 19) >> FC_WIDE_SHIFT;   // ... under PH_WIDE below this many voxels
 // Workgroups that write the pairs, over all instances: more of them write less each but count the
 // same.  316^2 noise with 16, 32, 64, 128, 256: one image 263, 250, 249, 249, 251 us a call, eight
 // images 425, 380, 353, 339, 342.
@@ -4079,8 +4080,13 @@ int run(int n, const void *d_imgs, const int64_t *d_img_off, const ph_shape *d_s
     const int htop = (tf || (flags & PH_HTOP) || (h1 && any3)) ? 1 : 0;
     // Few instances leave most of the chip idle: the images' dual then runs beside H0 as well, on
     // all their KEEP edges, which saves two launches one after another; in larger batches it
-    // follows on the edges H0 left, a third of them.
-    const int staged = any2 && n > kSideBySideInstances ? 1 : 0;
+    // follows on the edges H0 left, a third of them.  Under PH_WIDE a large image alone fills the chip, and
+    // where its edges' sides are far from their roots (plateaus, checkerboards, dithered images) the
+    // walks for the edges that H0 will use outweigh all else.  Beside and after, in us: noise 1024^2
+    // 778 and 750, 1448^2 1,123 and 1,101, 2048^2 1,907 and 1,782, 4096^2 7,015 and 6,163; a dithered image
+    // 1448^2 2,129 and 1,272, 2048^2 5,243 and 2,214; a binary one, with few edges, 1024^2 452 and 523,
+    // 1448^2 630 and 652, 2048^2 974 and 964.
+    const int staged = any2 && (n > kSideBySideInstances || (wide && mv >= kSideBySideWide)) ? 1 : 0;
     const unsigned side = htop && (any3 || !staged) ? 2 : 1;
     FC_LAUNCH(K_RESOLVE, hipLaunchKernelGGL(k_resolve, dim3(rblocks, n, side), dim3(256), 0, st, ws, n, 0, staged, htop, wide));
     auto run_wide = [&](int stage, unsigned sides, int kid) -> int {
