@@ -107,8 +107,8 @@ enum { PH_H0 = 1, PH_HTOP = 2, PH_IN_U8 = 4, PH_IN_U16 = 8, PH_TFILT = 16, PH_H1
 
 /* PH_WIDE (not in the paper, a scheduling choice): the union-finds (H0 and the top dimension)
  * of an instance of 2^20 or more voxels with more than 20,440 nodes start with some of their
- * parallel rounds (6 at 2^20 voxels and two more for each doubling) spread over the whole GPU (two
- * launches a round), then finish in one workgroup;
+ * parallel rounds (6 at 2^20 voxels, one more for every factor of 1.55; two launches a round) spread
+ * over the whole GPU, then finish in one workgroup;
  * the merges of its lists and its output take the whole GPU as well.  The pairs are the same.
  * It pays for inputs with many critical cells (noise: about a sixth of the pixels are H0 nodes); a
  * smooth field rarely has that many nodes, and then the extra launches (a few microseconds

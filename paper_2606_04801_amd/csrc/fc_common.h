@@ -187,16 +187,18 @@ FC_HD int64_t list_cap(int64_t worst, int k) {
 #define FC_WIDE_SHIFT 0
 #endif
 
-// How a long list of m keys is cut into sorted runs of up to `most` keys and merged in `passes`
-// passes (as many as pay, of those launched), each over groups of `fan` of the last one's results, the
-// last over all that are left.  One pass up to 16 runs, two up to 64, else three: a key's place in
+// How a long list of m keys is cut into sorted runs of up to `most` (a power of two) keys and merged in `passes`
+// passes (as many as pay, of those launched), each over groups of `fan` of the last one's results (fan2
+// in the second of three), the last over all that are left.  One pass up to 16 runs, two up to 64, else three: a key's place in
 // one pass takes one binary search in each other run of its group, so the searches, 12
 // instructions a step, bound a long list: noise 128^3 (690k edges in 338 runs, and the other lists)
 // takes 319 us in two passes over 19 runs each, 202 us in three over 7.
 // All runs have the same length (but for one key), and every group as many of them: a key of a short
 // run or group has long windows in all the others, so a workgroup with its 256 keys goes through
 // the whole list (4096^2 noise under PH_WIDE, a last group of one run of 78 keys: a pass of 11.4 ms,
-// else 0.6 ms).
+// else 0.6 ms).  So the runs are a multiple of a group's: a little more than asked, since in two or
+// three lists a workgroup more than the chip holds at once takes another wave (a cube root rounded
+// up to itself makes 245 of 218 runs and 180 of 147: 110^3 noise 45 us, 33 us with 224 and 147).
 // The searches of a pass grow with the runs of a group, so with the list: past kMergeRunsOnce or
 // kMergeRunsThrice runs each of the `blocks` workgroups of a list takes an equal share of it, sorts
 // its runs and merges them in pairs (a hundred instructions a key and doubling), and the passes
@@ -207,23 +209,36 @@ FC_HD int64_t list_cap(int64_t worst, int k) {
 constexpr int kMergeRunsOnce = 256 >> FC_WIDE_SHIFT;     // runs merged at most in one pass, where one is
 constexpr int kMergeRunsThrice = 512 >> FC_WIDE_SHIFT;   // launched; in three
 struct SortCut {
-    int m, runs, passes, fan;
+    int m, runs, passes, fan, fan2;
     int len, rem;                    // the first rem runs have len + 1 keys, the others len
     FC_HD int start(int j) const { return j * len + (j < rem ? j : rem); }   // first key of run j <= runs
 };
 FC_HD SortCut sort_cut(int m, int most, int launched, int blocks) {
     SortCut c;
     c.m = m;
-    c.runs = (m + most - 1) / most;
+    c.runs = (m + most - 1) >> __builtin_ctz((unsigned)most);
     if (launched > 0 && c.runs > (launched < 3 ? kMergeRunsOnce : kMergeRunsThrice)) c.runs = blocks;
     const int want = c.runs <= 1 ? 0 : (c.runs <= 16 ? 1 : (c.runs <= 64 ? 2 : 3));
     c.passes = want < launched ? want : launched;
     c.fan = c.runs;
+    c.fan2 = 1;
     if (c.passes >= 2) {
-        // the smallest fan with fan^passes >= runs; the last pass's groups no more than needed
-        for (c.fan = 2; c.fan * c.fan * (c.passes == 3 ? c.fan : 1) < c.runs;) ++c.fan;
-        const int unit = c.passes == 3 ? c.fan * c.fan : c.fan;
-        c.runs = (c.runs + unit - 1) / unit * unit;
+        // the smallest fan with fan^passes >= runs, or one next to it, whatever makes the fewest runs
+        // (at most kMergeRunsThrice or `blocks`: 16 bits make the divisions short)
+        int f = 2, best = 0;
+        while (f * f * (c.passes == 3 ? f : 1) < c.runs) ++f;
+        for (int d = 0; d <= 1; ++d)
+            for (int d2 = c.passes == 3 ? d - 1 : 0; d2 <= (c.passes == 3 ? d : 0); ++d2) {
+                const int fan = f + d, fan2 = c.passes == 3 ? f + d2 : 1;
+                if (fan < 2 || (c.passes == 3 && fan2 < 2)) continue;
+                const int unit = fan * fan2, all = ((c.runs + unit - 1) & 0xFFFF) / (unit & 0xFFFF) * unit;
+                if (best == 0 || all < best) {
+                    best = all;
+                    c.fan = fan;
+                    c.fan2 = fan2;
+                }
+            }
+        c.runs = best;
     }
     c.len = c.runs > 0 ? m / c.runs : 0;
     c.rem = c.runs > 0 ? m % c.runs : 0;

@@ -1469,7 +1469,7 @@ __global__ __launch_bounds__(kSortThreads, 8) void k_sort_lists(uint8_t *__restr
     lds_barrier();
     if (s_flag) return;
     const int m = L.m;                           // (a list has fewer than 2^29 keys)
-    SortCut cut{m, 1, 0, 1, m, 0};               // one run, or one workgroup's list
+    SortCut cut{m, 1, 0, 1, 1, m, 0};               // one run, or one workgroup's list
     if (passes > 0 && m > rl) cut = sort_cut(m, rl, passes, gridDim.x);
     if (m <= 0 || (int)blockIdx.x >= cut.runs) return;
     if (m > L.cap) { if (threadIdx.x == 0) set_err(cnt, PH_EINTERNAL); return; }
@@ -1546,9 +1546,9 @@ __global__ __launch_bounds__(kMergeThreads) void k_sort_merge(uint8_t *__restric
     const SortCut cut = sort_cut(m, run_max, passes, blocks);   // as k_sort_lists cut it
     const int np = cut.passes;
     if (pass >= np) return;
-    int u = 1;                                   // first runs in one sorted so far
-    for (int p = 0; p < pass; ++p) u *= cut.fan;
-    const int gu = pass == np - 1 ? cut.runs : u * cut.fan;   // ... in a group
+    // first runs in one sorted so far, and in a group
+    const int u = pass == 0 ? 1 : (pass == 1 ? cut.fan : cut.fan * cut.fan2);
+    const int gu = pass == np - 1 ? cut.runs : (pass == 0 ? cut.fan : cut.fan * cut.fan2);
     const uint64_t *a = (np - pass) & 1 ? L.scr : L.dst;
     uint64_t *b = (np - pass) & 1 ? L.dst : L.scr;
     const int steps = (cut.start(u) + kMergeThreads - 1) / kMergeThreads, all = cut.runs / u * steps;
@@ -2223,6 +2223,17 @@ __device__ __forceinline__ WideForest wide_forest(uint8_t *__restrict__ ws, cons
     return w;
 }
 
+// Wide rounds a forest of M nodes takes, of those launched (wide_rounds): six up to kWideNodesSix
+// nodes, of which they leave 0.035 or 0.04 at most (noise on a checkerboard; white noise 0.017 to
+// 0.02), two more for each doubling.  (A round less than launched is two idle launches, 7 us; a round
+// not needed takes 25 us at 1.6M voxels.)
+constexpr int64_t kWideNodesSix = 450000 >> FC_WIDE_SHIFT;
+__device__ __forceinline__ int rounds_for(int M) {
+    int r = kWideRoundsMin;
+    for (int64_t k = kWideNodesSix; k < M; k = k * 182 / 128) ++r;   // (the square root of 2)
+    return r;
+}
+
 // phase -1: set up; 0, 1: the two phases of round `round` of `rounds` (in phase 0 of round `rounds`,
 // the last, moe[x] = 0 marks the roots left); 2: the roots left numbered; 3: the segments closed
 // up; 4: moe cleared for the next rounds' tags.
@@ -2233,12 +2244,15 @@ __global__ __launch_bounds__(kWideThreads) void k_uf_wide(uint8_t *__restrict__ 
     __shared__ int s_cnt[kWidePer][kWideThreads / 64];
     __shared__ int s_flag;
     const int i = blockIdx.y, tid = threadIdx.x, lane = __lane_id(), wid = tid >> 6;
-    const Inst I = ((const Inst *)ws)[i];           // one batch of loads, before any atomic
-    const bool is2d = I.ndim == 2, dual = stage == 1 || blockIdx.z == 1;
-    if (dual && (!htop || (is2d && (stage == 1) != (staged != 0)) || (stage == 1 && !is2d))) return;
+    const bool dual = stage == 1 || blockIdx.z == 1;
     int32_t *cnt = (int32_t *)(ws + off_cnt(n)) + i * CNT_WORDS;
-    const int mE = cnt[CNT_E], mF = cnt[CNT_F], m0 = cnt[CNT_M0], mT = cnt[CNT_MT];
-    const int M = dual ? mT : m0, m = !dual || is2d ? mE : mF;
+    const int m0 = cnt[CNT_M0], mT = cnt[CNT_MT], M = dual ? mT : m0;
+    // (before the record is loaded: nothing else is done in a round the forest does not need)
+    if ((phase == 0 || phase == 1) && round < rounds && round >= rounds_for(M)) return;
+    const Inst I = ((const Inst *)ws)[i];           // one batch of loads, before any atomic
+    const bool is2d = I.ndim == 2;
+    if (dual && (!htop || (is2d && (stage == 1) != (staged != 0)) || (stage == 1 && !is2d))) return;
+    const int mE = cnt[CNT_E], mF = cnt[CNT_F], m = !dual || is2d ? mE : mF;
     const int segs = (m + kWideSeg - 1) / kWideSeg;
     if ((int)blockIdx.x >= segs && phase != -1 && phase != 2 && phase != 4) return;
     if (tid == 0) s_flag = failed(cnt);
@@ -3814,18 +3828,18 @@ int64_t max_list(const ph_shape *h, int n) {
     return m;
 }
 
-// Wide union-find rounds of a call whose largest instance has mv voxels: six at 2^20, two more for each
-// doubling.  A round leaves 0.6 of the nodes in the inputs that lose them slowest (white noise 0.58;
-// noise on a checkerboard, with a node for every other pixel the most there can be, 0.6; ramps, quantised
-// and smoothed noise lose them faster): 4k and 8k of 1024^2 pixels after six, and the finish holds
-// kRestNodes.  If more are left one workgroup works out of the workspace (six rounds at 4096^2
-// noise 99 ms, 256^3 212 ms; seven at 1448^2 noise on a checkerboard 14.4 ms, ten 1.7).  A doubling
-// of the voxels takes 1.4 rounds more to the same nodes; two cost no more, since each also saves the
-// workgroup its share (256^3 with 8, 10, 12, 14, 20 rounds: 7.9, 7.7, 7.5, 7.5, 7.4 ms; 2048^2 with 6,
-// 8, 10, 14: 1.96, 1.90, 1.93, 2.04 ms; 1024^2 with 6, 8, 10: 0.80, 0.81, 0.84).
+// Wide union-find rounds launched by a call whose largest instance has mv voxels; a forest takes as many
+// of them as its nodes need (rounds_for).  A round leaves 0.6 of the nodes in the inputs that lose them
+// slowest (white noise 0.58; noise on a checkerboard, with a node for every other pixel the most there
+// can be, 0.62; ramps, quantised and smoothed noise lose them faster), and the finish holds kRestNodes:
+// six rounds at 2^20 voxels, and one more for every factor of 1.55.  If more nodes are left one
+// workgroup works out of the workspace (six rounds at 4096^2 noise 99 ms, 256^3 212 ms; seven at 1448^2
+// noise on a checkerboard 14.4 ms, ten 1.7).  Rounds past what is needed cost little, since each also
+// saves the workgroup its share (256^3 with 8, 10, 12, 14, 20 rounds: 7.9, 7.7, 7.5, 7.5, 7.4 ms;
+// 2048^2 with 6, 8, 10, 14: 1.96, 1.90, 1.93, 2.04 ms; 1024^2 with 6, 8, 10: 0.80, 0.81, 0.84).
 int wide_rounds(int64_t mv) {
     int r = kWideRoundsMin;
-    for (int64_t v = kWideVoxels; v < mv; v = v * 182 / 128) ++r;   // (a factor of the square root of 2 each)
+    for (int64_t v = kWideVoxels; v < mv; v = v * 198 / 128) ++r;
     return r;
 }
 
@@ -4069,7 +4083,10 @@ int run(int n, const void *d_imgs, const int64_t *d_img_off, const ph_shape *d_s
     const int passes = !multi ? 0 : (wide ? 3 : 1);
     const int rl = multi ? kSortRun : kSortCap;
     const int64_t runs = (ml + rl - 1) / rl;
-    const unsigned sr = multi ? (unsigned)std::min<int64_t>(runs, std::max<int64_t>(wide ? 16 : 1, (wide ? 512 : 256) / n)) : 1u;
+    // (two workgroups a compute unit where shares are likely, one else: those without a run take a
+    // slot of its LDS all the same, 110^3 noise 48 us of k_sort_lists with 512 a list, 34 with 256)
+    const int all = wide && mv >= 4 * kWideVoxels ? 512 : 256;
+    const unsigned sr = multi ? (unsigned)std::min<int64_t>(runs, std::max<int64_t>(wide ? 16 : 1, all / n)) : 1u;
     FC_LAUNCH(K_SORT, hipLaunchKernelGGL(k_sort_lists, dim3(sr, n, 4), dim3(kSortThreads), 0, st, ws, n, rl, passes));
     for (int p = 0; p < passes; ++p) {
         const unsigned mb = (unsigned)std::min<int64_t>((ml + kMergeThreads - 1) / kMergeThreads, std::max<int64_t>(16, (wide ? 1024 : 256) / n));
@@ -4092,7 +4109,10 @@ int run(int n, const void *d_imgs, const int64_t *d_img_off, const ph_shape *d_s
     auto run_wide = [&](int stage, unsigned sides, int kid) -> int {
         const unsigned wb = (unsigned)std::min<int64_t>((ml + kWideSeg - 1) / kWideSeg, std::max(1, kWideBlocks / n));
         auto pass = [&](int ph, int r) -> int {
-            FC_LAUNCH(kid, hipLaunchKernelGGL(k_uf_wide, dim3(wb, n, sides), dim3(kWideThreads), 0, st, ws, n, stage, staged,
+            // (below 2^22 voxels few forests take more than six rounds, and those that do have few edges
+            // left by then: a quarter of the workgroups, which cost less to launch for nothing)
+            const bool more = mv < 4 * kWideVoxels && r >= kWideRoundsMin && r < wide;
+            FC_LAUNCH(kid, hipLaunchKernelGGL(k_uf_wide, dim3(more ? wb / 4 + 1 : wb, n, sides), dim3(kWideThreads), 0, st, ws, n, stage, staged,
                                               htop, ph, r, wide));
             return PH_OK;
         };

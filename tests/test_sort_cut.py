@@ -29,12 +29,15 @@ static int check(int m, int most, int launched, int blocks) {
     CHECK(c.rem < c.runs && c.start(c.runs) - c.start(c.runs - 1) >= c.start(1) - 1);
     int u = 1;
     for (int p = 0; p + 1 < c.passes; ++p) {
-        CHECK(c.fan >= 2 && c.runs % (u * c.fan) == 0);      // whole groups
-        u *= c.fan;
+        const int fan = p == 0 ? c.fan : c.fan2;
+        CHECK(fan >= 2 && c.runs % (u * fan) == 0);          // whole groups
+        u *= fan;
         // the last group is as long as the first, but for a key a run
         CHECK(c.start(c.runs) - c.start(c.runs - u) >= c.start(u) - u);
     }
-    if (c.passes > 0) CHECK(c.runs / u <= (c.passes == 1 ? (blocks > 256 ? blocks : 256) : c.fan));
+    // groups of nearly the least size for these passes, and few more runs than asked
+    if (c.passes >= 2 && !shares) CHECK(c.runs / u <= c.fan + 1 && c.runs <= least + least / 6 + 1);
+    if (c.passes == 1) CHECK(c.runs <= (blocks > 256 ? blocks : 256));
     return 0;
 }
 int main() {
