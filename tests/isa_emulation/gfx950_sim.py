@@ -1011,6 +1011,14 @@ def _compile_valu(op, O, mods, nxt):
             d(w, bits(x.astype(F32)))
             return nxt
         return f
+    if op == "v_fma_f32":                            # D = S0 * S1 + S2
+        d, a, b, c = wv(O[0]), r32(O[1]), r32(O[2]), r32(O[3])
+
+        def f(w):
+            x = f32(a(w)).astype(np.longdouble) * f32(b(w)).astype(np.longdouble) + f32(c(w)).astype(np.longdouble)
+            d(w, bits(x.astype(F32)))
+            return nxt
+        return f
     if op == "v_fmac_f32":
         d, a, b = wv(O[0]), r32(O[1]), r32(O[2])
         di = O[0].idx
