@@ -198,7 +198,8 @@ FC_HD int64_t list_cap(int64_t worst, int k) {
 // the whole list (4096^2 noise under PH_WIDE, a last group of one run of 78 keys: a pass of 11.4 ms,
 // else 0.6 ms).  So the runs are a multiple of a group's: a little more than asked, since in two or
 // three lists a workgroup more than the chip holds at once takes another wave (a cube root rounded
-// up to itself makes 245 of 218 runs and 180 of 147: 110^3 noise 45 us, 33 us with 224 and 147).
+// up to itself makes 245 of 218 runs and 180 of 147, where 224 and 147 will do: 110^3 noise 45 us of
+// k_sort_lists, so 42).
 // The searches of a pass grow with the runs of a group, so with the list: past kMergeRunsOnce or
 // kMergeRunsThrice runs each of the `blocks` workgroups of a list takes an equal share of it, sorts
 // its runs and merges them in pairs (a hundred instructions a key and doubling), and the passes

@@ -2225,8 +2225,8 @@ __device__ __forceinline__ WideForest wide_forest(uint8_t *__restrict__ ws, cons
 
 // Wide rounds a forest of M nodes takes, of those launched (wide_rounds): six up to kWideNodesSix
 // nodes, of which they leave 0.035 or 0.04 at most (noise on a checkerboard; white noise 0.017 to
-// 0.02), two more for each doubling.  (A round less than launched is two idle launches, 7 us; a round
-// not needed takes 25 us at 1.6M voxels.)
+// 0.02), two more for each doubling.  (A round launched but not taken is two idle launches, 5 to 9 us;
+// a round taken but not needed 25 us at 1.6M voxels.)
 constexpr int64_t kWideNodesSix = 450000 >> FC_WIDE_SHIFT;
 __device__ __forceinline__ int rounds_for(int M) {
     int r = kWideRoundsMin;
@@ -4084,7 +4084,7 @@ int run(int n, const void *d_imgs, const int64_t *d_img_off, const ph_shape *d_s
     const int rl = multi ? kSortRun : kSortCap;
     const int64_t runs = (ml + rl - 1) / rl;
     // (two workgroups a compute unit where shares are likely, one else: those without a run take a
-    // slot of its LDS all the same, 110^3 noise 48 us of k_sort_lists with 512 a list, 34 with 256)
+    // slot of its LDS all the same, 110^3 noise 48 us of k_sort_lists with 512 a list, 43 with 256)
     const int all = wide && mv >= 4 * kWideVoxels ? 512 : 256;
     const unsigned sr = multi ? (unsigned)std::min<int64_t>(runs, std::max<int64_t>(wide ? 16 : 1, all / n)) : 1u;
     FC_LAUNCH(K_SORT, hipLaunchKernelGGL(k_sort_lists, dim3(sr, n, 4), dim3(kSortThreads), 0, st, ws, n, rl, passes));
