@@ -187,12 +187,12 @@ FC_HD int64_t list_cap(int64_t worst, int k) {
 #define FC_WIDE_SHIFT 0
 #endif
 
-// How a long list of m keys is cut into sorted runs of up to `most` (a power of two) keys and merged in `passes`
-// passes (as many as pay, of those launched), each over groups of `fan` of the last one's results (fan2
-// in the second of three), the last over all that are left.  One pass up to 16 runs, two up to 64, else three: a key's place in
-// one pass takes one binary search in each other run of its group, so the searches, 12
-// instructions a step, bound a long list: noise 128^3 (690k edges in 338 runs, and the other lists)
-// takes 319 us in two passes over 19 runs each, 202 us in three over 7.
+// How a long list of m keys is cut into sorted runs of up to `most` (a power of two) keys and merged
+// in `passes` passes (as many as pay, of those launched), each over groups of `fan` of the last one's
+// results (fan2 in the second of three), the last over all that are left.  One pass up to 16 runs,
+// two up to 64, else three: a key's place in one pass takes one binary search in each other run of
+// its group, so the searches, 12 instructions a step, bound a long list: noise 128^3 (690k edges in
+// 338 runs, and the other lists) takes 319 us in two passes over 19 runs each, 202 us in three over 7.
 // All runs have the same length (but for one key), and every group as many of them: a key of a short
 // run or group has long windows in all the others, so a workgroup with its 256 keys goes through
 // the whole list (4096^2 noise under PH_WIDE, a last group of one run of 78 keys: a pass of 11.4 ms,
